@@ -246,13 +246,28 @@ int check_shape(int B, int H, int N, int d, sattn_dtype dt) {
 }
 
 // ---------------------------------------------------------------- forward
-template <int D>
-int launch_fwd_f32(F32Params p, int causal, bool alibi, hipStream_t st) {
-  p.n_blocks = (p.N + 127) / 128;
-  dim3 grid(p.n_blocks * p.B * p.H), block(256);
+// Waves of an fp32 workgroup.  Eight where that still leaves no compute unit with a second
+// workgroup (half the chunks per wave), four otherwise (two workgroups per compute unit).
+int f32_waves(int64_t wgs, int cus) { return wgs <= cus ? 8 : 4; }
+
+template <int D, int MODE>
+int launch_f32_pass(const F32Params& p, int nb, int heads, int waves, int causal, bool alibi, hipStream_t st) {
+  const int64_t wgs = (int64_t)nb * heads;
+  const int cus = compute_units();
   int rc = SATTN_OK;
-  SATTN_DISPATCH2(causal, alibi, rc = launch(sigmoid_f32_kernel<D, F32_FWD, A, B2>, grid, block, 0, st, p));
+  if (waves == 8)
+    SATTN_DISPATCH2(causal, alibi, rc = launch(sigmoid_f32_kernel<D, MODE, A, B2, 8>, dim3((unsigned)wgs), dim3(512),
+                                               f32_lds_bytes<D>(8), st, p, nb, heads, cus));
+  else
+    SATTN_DISPATCH2(causal, alibi, rc = launch(sigmoid_f32_kernel<D, MODE, A, B2, 4>, dim3((unsigned)wgs), dim3(256),
+                                               f32_lds_bytes<D>(4), st, p, nb, heads, cus));
   return rc;
+}
+
+template <int D>
+int launch_fwd_f32(const F32Params& p, int causal, bool alibi, hipStream_t st) {
+  const int nb = (p.N + 31) / 32, heads = p.B * p.H;
+  return launch_f32_pass<D, F32_FWD>(p, nb, heads, f32_waves((int64_t)nb * heads, compute_units()), causal, alibi, st);
 }
 
 struct FwdArgs {
@@ -301,7 +316,7 @@ int fwd_impl(const FwdArgs& a) {
   if (a.dtype == SATTN_F32) {
     if (SOFTMAX || !PIN) return SATTN_ERR_UNSUPPORTED;  // comparison kernels and twins: bf16 only
     F32Params p{};
-    p.q = q; p.k = k; p.v = v; p.out0 = o;
+    p.q = q; p.k = k; p.v = v; p.o = o;
     p.slopes = a.slopes; p.B = a.B; p.H = a.H; p.N = a.N;
     p.scale = inv_sqrt_d; p.bias = a.bias;
     p.cu_seqlens = a.cu_seqlens; p.bias_vec = a.bias_vec;
@@ -337,23 +352,24 @@ int fwd_impl(const FwdArgs& a) {
 
 // ---------------------------------------------------------------- backward
 template <int D>
-int launch_bwd_f32(F32Params p, int causal, bool alibi, int parts, TensorRef dq, TensorRef dk, TensorRef dv,
-                   hipStream_t st) {
-  // the dQ pass runs one workgroup per query head and 128 queries, the dK/dV pass one per K/V
-  // head and 128 keys
-  const int nb_q = (p.N + 127) / 128, nb_k = ((p.Nk > 0 ? p.Nk : p.N) + 127) / 128;
-  dim3 grid_q(nb_q * p.B * p.H), grid_kv(nb_k * p.B * (p.H / p.kv_group)), block(256);
+int launch_bwd_f32(const F32Params& p, int causal, bool alibi, int parts, hipStream_t st) {
+  // the dQ pass runs one workgroup per query head and 32 queries, the dK/dV pass one per K/V
+  // head and 32 keys
+  const int nb_q = (p.N + 31) / 32, nb_k = ((p.Nk > 0 ? p.Nk : p.N) + 31) / 32;
+  const int heads_q = p.B * p.H, heads_k = p.B * (p.H / p.kv_group);
+  const int64_t wgs = (int64_t)nb_q * heads_q + (int64_t)nb_k * heads_k;
+  if (wgs > 0x7fffffffLL) return SATTN_ERR_SHAPE;
+  const int cus = compute_units();
+  const int waves = f32_waves(wgs, cus);  // the same for a pass alone: its sums then run in the same order
+  if (parts == kBwdDkDv) return launch_f32_pass<D, F32_DKDV>(p, nb_k, heads_k, waves, causal, alibi, st);
+  if (parts == kBwdDq) return launch_f32_pass<D, F32_DQ>(p, nb_q, heads_q, waves, causal, alibi, st);
   int rc = SATTN_OK;
-  if (parts & kBwdDkDv) {
-    p.n_blocks = nb_k;
-    p.out0 = dk; p.out1 = dv;
-    SATTN_DISPATCH2(causal, alibi, rc = launch(sigmoid_f32_kernel<D, F32_DKDV, A, B2>, grid_kv, block, 0, st, p));
-  }
-  if (rc == SATTN_OK && (parts & kBwdDq)) {
-    p.n_blocks = nb_q;
-    p.out0 = dq; p.out1 = TensorRef{};
-    SATTN_DISPATCH2(causal, alibi, rc = launch(sigmoid_f32_kernel<D, F32_DQ, A, B2>, grid_q, block, 0, st, p));
-  }
+  if (waves == 8)
+    SATTN_DISPATCH2(causal, alibi, rc = launch(sigmoid_f32_bwd_kernel<D, A, B2, 8>, dim3((unsigned)wgs), dim3(512),
+                                               f32_lds_bytes<D>(8), st, p, nb_k, nb_q, cus));
+  else
+    SATTN_DISPATCH2(causal, alibi, rc = launch(sigmoid_f32_bwd_kernel<D, A, B2, 4>, dim3((unsigned)wgs), dim3(256),
+                                               f32_lds_bytes<D>(4), st, p, nb_k, nb_q, cus));
   return rc;
 }
 
@@ -395,7 +411,7 @@ int bwd_impl(const BwdArgs& a) {
   if (a.dtype == SATTN_F32) {
     if (SOFTMAX || !PIN) return SATTN_ERR_UNSUPPORTED;  // comparison kernels and twins: bf16 only
     F32Params p{};
-    p.q = q; p.k = k; p.v = v; p.dout = dout;
+    p.q = q; p.k = k; p.v = v; p.dout = dout; p.dq = dq; p.dk = dk; p.dv = dv;
     p.slopes = a.slopes; p.B = a.B; p.H = a.H; p.N = a.N;
     p.scale = inv_sqrt_d; p.bias = a.bias;
     p.cu_seqlens = a.cu_seqlens; p.bias_vec = a.bias_vec;
@@ -404,8 +420,8 @@ int bwd_impl(const BwdArgs& a) {
     p.qoff = a.end_aligned ? Nk - a.N : 0;
     p.db_rows = a.db_rows; p.db_sb = (int64_t)a.H * a.N; p.db_sh = a.N;
     if (a.cu_seqlens && a.db_rows) { p.db_sb = 0; p.db_sh = a.db_tokens; }  // [H, tokens], as in the bf16 path
-    if (a.d == 128) rc = launch_bwd_f32<128>(p, a.causal, alibi, a.parts, dq, dk, dv, st);
-    else rc = launch_bwd_f32<64>(p, a.causal, alibi, a.parts, dq, dk, dv, st);
+    if (a.d == 128) rc = launch_bwd_f32<128>(p, a.causal, alibi, a.parts, st);
+    else rc = launch_bwd_f32<64>(p, a.causal, alibi, a.parts, st);
     if (rc == SATTN_OK && a.db) {
       if (a.cu_seqlens)
         rc = launch(rowsum_reduce_varlen_kernel, dim3(a.B * a.H), dim3(256), 0, st, (const float*)a.db_rows, a.db,
