@@ -202,7 +202,8 @@ int sattn_headconcat_norm_bwd(const void* x, const void* dy, const float* stats,
  * non-causal ALiBi run the 8-wave shape where 64 is returned); sattn_fwd_v_slots returns the V
  * ring depth (3; 2: two 4-wave workgroups per compute unit); both return a negative error code
  * for bad arguments.  The outputs are bit-identical for all shapes: the arithmetic of a query
- * row does not depend on which rows share its workgroup. */
+ * row does not depend on which rows share its workgroup.  (Fewer queries than a quarter of the
+ * keys may take a kernel that sums over the keys in another order; a forced shape overrides it.) */
 int sattn_fwd_waves(int B, int H, int N, int d, int causal);
 int sattn_fwd_v_slots(int B, int H, int N, int d, int causal);
 
@@ -291,6 +292,23 @@ int sigmoid_attn_cross_aligned_bwd(const void* q, const void* k, const void* v, 
                                    const sattn_strides* sv, const sattn_strides* sdout,
                                    const sattn_strides* sdq, const sattn_strides* sdk,
                                    const sattn_strides* sdv, void* stream);
+
+/* sigmoid_attn_cross_aligned_fwd (and, without mask and ALiBi, sigmoid_attn_cross_fwd) for few
+ * queries and many keys: where the queries alone leave compute units idle the keys are split over
+ * several workgroups that write fp32 partial outputs to `workspace` (device memory, 16-byte
+ * aligned, at least ..._workspace_bytes(...) bytes, contents undefined before and after), added
+ * up and rounded to bf16 once by a second kernel.  ..._workspace_bytes returns 0 where the library
+ * would not split (enough queries, few keys, fp32, invalid arguments): the call then
+ * equals sigmoid_attn_cross_aligned_fwd and workspace may be NULL.  The results differ from that
+ * call's only in the order of the fp32 sums over the keys.  SATTN_ERR_WORKSPACE if the workspace
+ * is NULL or too small where one is needed. */
+size_t sigmoid_attn_cross_aligned_fwd_workspace_bytes(int B, int H, int Nq, int Nk, int d, sattn_dtype dtype);
+int sigmoid_attn_cross_aligned_fwd_split(const void* q, const void* k, const void* v, void* o,
+                                         int B, int H, int Nq, int Nk, int d, sattn_dtype dtype, float bias,
+                                         int causal, const float* alibi_slopes,
+                                         const sattn_strides* sq, const sattn_strides* sk,
+                                         const sattn_strides* sv, const sattn_strides* so,
+                                         void* workspace, size_t workspace_bytes, void* stream);
 
 /* Backward with the gradient of a learnable bias (Section 5.4 and Appendix G.4 train with a
  * learnable scalar b, one per layer; Appendix F.1 backward table: T = S + b, so dL/db is the

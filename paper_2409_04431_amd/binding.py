@@ -64,6 +64,10 @@ def load_library():
     lib.sigmoid_attn_cross_bwd.restype = i
     lib.sigmoid_attn_cross_aligned_fwd.argtypes = [_vp, _vp, _vp, _vp, i, i, i, i, i, i, f, i, _vp, _SP, _SP, _SP, _SP, _vp]
     lib.sigmoid_attn_cross_aligned_fwd.restype = i
+    lib.sigmoid_attn_cross_aligned_fwd_split.argtypes = lib.sigmoid_attn_cross_aligned_fwd.argtypes[:-1] + [_vp, sz, _vp]
+    lib.sigmoid_attn_cross_aligned_fwd_split.restype = i
+    lib.sigmoid_attn_cross_aligned_fwd_workspace_bytes.argtypes = [i, i, i, i, i, i]
+    lib.sigmoid_attn_cross_aligned_fwd_workspace_bytes.restype = sz
     lib.sigmoid_attn_cross_aligned_bwd.argtypes = [_vp] * 7 + [i, i, i, i, i, i, f, i, _vp] + [_SP] * 7 + [_vp]
     lib.sigmoid_attn_cross_aligned_bwd.restype = i
     lib.sigmoid_attn_bwd_bias_grad.argtypes = [_vp] * 9 + [i, i, i, i, i, f, i, _vp] + [_SP] * 7 + [_vp]
@@ -303,14 +307,34 @@ def _check_cross(q, kv, *qlike):
     return B, H, Nq, Nk, d
 
 
-def sigmoid_attn_cross_fwd(q, k, v, o, bias):
-    """Plain sigmoid attention with Nq queries and Nk keys: q, o [B,H,Nq,d]; k, v [B,H,Nk,d]."""
+def sigmoid_attn_cross_aligned_fwd_workspace_bytes(B, H, Nq, Nk, d, dtype=torch.bfloat16):
+    """Bytes of workspace sigmoid_attn_cross_aligned_fwd_split wants for this problem (0: it would not split)."""
+    code = SATTN_BF16 if dtype == torch.bfloat16 else SATTN_F32
+    return int(load_library().sigmoid_attn_cross_aligned_fwd_workspace_bytes(B, H, Nq, Nk, d, code))
+
+
+def sigmoid_attn_cross_aligned_fwd_split(q, k, v, o, bias, causal=False, alibi_slopes=None, workspace=None):
+    """sigmoid_attn_cross_aligned_fwd with the keys split over several workgroups where queries are few
+    (fp32 partial outputs in `workspace`, allocated here when not given)."""
     lib = load_library()
     B, H, Nq, Nk, d = _check_cross(q, (k, v), o)
-    rc = lib.sigmoid_attn_cross_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), B, H, Nq, Nk, d,
-                                    _dtype_code(q), float(bias), _st(q), _st(k), _st(v), _st(o), _stream())
-    _raise(rc, "sigmoid_attn_cross_fwd")
+    code = _dtype_code(q)
+    need = lib.sigmoid_attn_cross_aligned_fwd_workspace_bytes(B, H, Nq, Nk, d, code)
+    if workspace is None and need:
+        workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
+    wp = workspace.data_ptr() if workspace is not None else None
+    wb = workspace.numel() * workspace.element_size() if workspace is not None else 0
+    rc = lib.sigmoid_attn_cross_aligned_fwd_split(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), B, H, Nq, Nk, d,
+                                                  code, float(bias), int(bool(causal)), _slopes_ptr(alibi_slopes, H),
+                                                  _st(q), _st(k), _st(v), _st(o), wp, wb, _stream())
+    _raise(rc, "sigmoid_attn_cross_aligned_fwd_split")
     return o
+
+
+def sigmoid_attn_cross_fwd(q, k, v, o, bias):
+    """Plain sigmoid attention with Nq queries and Nk keys: q, o [B,H,Nq,d]; k, v [B,H,Nk,d]."""
+    # (positions do not matter without a mask and ALiBi)
+    return sigmoid_attn_cross_aligned_fwd_split(q, k, v, o, bias)
 
 
 def sigmoid_attn_cross_bwd(q, k, v, dout, dq, dk, dv, bias):
@@ -327,13 +351,7 @@ def sigmoid_attn_cross_bwd(q, k, v, dout, dq, dk, dv, bias):
 def sigmoid_attn_cross_aligned_fwd(q, k, v, o, bias, causal=False, alibi_slopes=None):
     """Sigmoid attention of Nq queries placed at the end of an Nk-key sequence (query i at position
     i + Nk - Nq), with the causal mask and ALiBi of that placement: q, o [B,H,Nq,d]; k, v [B,H,Nk,d]."""
-    lib = load_library()
-    B, H, Nq, Nk, d = _check_cross(q, (k, v), o)
-    rc = lib.sigmoid_attn_cross_aligned_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), B, H, Nq, Nk, d,
-                                            _dtype_code(q), float(bias), int(bool(causal)), _slopes_ptr(alibi_slopes, H),
-                                            _st(q), _st(k), _st(v), _st(o), _stream())
-    _raise(rc, "sigmoid_attn_cross_aligned_fwd")
-    return o
+    return sigmoid_attn_cross_aligned_fwd_split(q, k, v, o, bias, causal, alibi_slopes)
 
 
 def sigmoid_attn_cross_aligned_bwd(q, k, v, dout, dq, dk, dv, bias, causal=False, alibi_slopes=None):

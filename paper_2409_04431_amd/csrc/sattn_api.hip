@@ -270,6 +270,28 @@ int launch_fwd_f32(const F32Params& p, int causal, bool alibi, hipStream_t st) {
   return launch_f32_pass<D, F32_FWD>(p, nb, heads, f32_waves((int64_t)nb * heads, compute_units()), causal, alibi, st);
 }
 
+// The forward kernel for few queries (sattn_few.hpp: 32 query rows per workgroup, keys split over
+// its eight waves and over n_split workgroups), or n_split = 0 for the kernels of 128 or 256 rows.
+// It reads K and V from the L2 once per 32 rows, they once per 128, so it only pays while its
+// blocks leave the chip unfilled.  Measured (us, the 128-row kernel / this one): up to one block
+// per compute unit it wins -- one query, 4001 keys, d 128: 128 heads 63 / 50, 16 heads 61 / 14; 64
+// queries, 8256 keys, 16 heads 125 / 23; 512 queries, 8704 keys, 8 heads (128 blocks) 139 / 48 --
+// and at two blocks per unit it is at par for one query (512 heads, 1000 and 2000 keys 26 / 28,
+// 48 / 48) and behind for more (256 queries, 4352 keys, 64 heads 75 / 103).
+// Splits: as many as give every compute unit one workgroup and every wave a chunk; below 32 chunks
+// the second kernel that adds the partial outputs up (3-4 us) costs what the split gains.
+// From four keys per query on only: closer to the square every forward shape gives the same bits,
+// which sums over the keys in another order would not.
+// Without a workspace a single split has too few bytes in flight once a quarter of the units is
+// busy with one block per head (128 heads: 63 / 69).
+int few_splits(int B, int H, int N, int Nk, bool workspace) {
+  const int64_t nb = (N + 31) / 32, blocks = (int64_t)B * H * nb, cus = compute_units();
+  if (blocks > cus || (int64_t)Nk < 4 * (int64_t)N) return 0;
+  const int64_t chunks = ((int64_t)Nk + 31) / 32;
+  if (!workspace) return nb > 1 || blocks <= cus / 4 || chunks < 32 ? 1 : 0;
+  return chunks < 32 ? 1 : (int)std::min(cus / blocks, chunks / 8);
+}
+
 struct FwdArgs {
   const void *q, *k, *v; void* o; float* lse;
   int B, H, N, d; sattn_dtype dtype; float bias; int causal; const float* slopes;
@@ -278,6 +300,8 @@ struct FwdArgs {
   int Hkv = 0;                                                       // K/V heads (0: one per query head)
   int Nk = 0;                                                        // keys (0: as many as queries)
   bool end_aligned = false;                                          // queries = the last N positions of the key sequence
+  bool split = false;                                                // few queries: the keys may be split over workgroups (workspace)
+  void* workspace = nullptr; size_t workspace_bytes = 0;
 };
 
 // A key count that differs from the query count: sigmoid attention with one K/V head per query
@@ -339,6 +363,17 @@ int fwd_impl(const FwdArgs& a) {
   p.clock = clock_probe();
   // the 64-row waves exist for the pinned sigmoid kernel at d = 128, ALiBi only in its causal form
   const bool has64 = !SOFTMAX && PIN && a.d == 128 && !(alibi && !a.causal);
+  if (!SOFTMAX && PIN && Nk != a.N && g_fwd_waves.load(std::memory_order_relaxed) == 0) {
+    p.n_split = few_splits(a.B, a.H, a.N, Nk, a.split);
+    if (p.n_split > 1) {
+      const size_t need = (size_t)p.n_split * a.B * a.H * a.N * a.d * sizeof(float);
+      if (!a.workspace || a.workspace_bytes < need) return SATTN_ERR_WORKSPACE;
+      if (((uintptr_t)a.workspace & 15) != 0) return SATTN_ERR_ALIGN;
+      p.part = (float*)a.workspace;
+    }
+    if (p.n_split > 0)
+      return a.d == 128 ? launch_fwd_few<128>(p, a.causal, alibi, st) : launch_fwd_few<64>(p, a.causal, alibi, st);
+  }
   const FwdShape shape = pick_fwd_shape(a.B, a.H, a.N, a.d, a.causal, has64);
   // The 64-row causal kernel deals a head's blocks out in pairs of equal work (longest with
   // shortest) where that still leaves a workgroup per compute unit.  Measured against single
@@ -812,6 +847,28 @@ int sigmoid_attn_cross_aligned_fwd(const void* q, const void* k, const void* v, 
   FwdArgs a{q, k, v, o, nullptr, B, H, Nq, d, dtype, bias, causal, alibi_slopes, sq, sk, sv, so, stream};
   a.Nk = Nk;
   a.end_aligned = true;
+  return fwd_impl<false>(a);
+}
+
+size_t sigmoid_attn_cross_aligned_fwd_workspace_bytes(int B, int H, int Nq, int Nk, int d, sattn_dtype dtype) {
+  if (check_shape(B, H, Nq, d, dtype) != SATTN_OK || check_shape(B, H, Nk, d, dtype) != SATTN_OK || Nq == Nk ||
+      dtype != SATTN_BF16)
+    return 0;
+  const int s = few_splits(B, H, Nq, Nk, true);
+  return s > 1 ? (size_t)s * B * H * Nq * d * sizeof(float) : 0;
+}
+
+int sigmoid_attn_cross_aligned_fwd_split(const void* q, const void* k, const void* v, void* o, int B, int H, int Nq,
+                                         int Nk, int d, sattn_dtype dtype, float bias, int causal,
+                                         const float* alibi_slopes, const sattn_strides* sq, const sattn_strides* sk,
+                                         const sattn_strides* sv, const sattn_strides* so, void* workspace,
+                                         size_t workspace_bytes, void* stream) {
+  if (Nk <= 0) return SATTN_ERR_SHAPE;
+  FwdArgs a{q, k, v, o, nullptr, B, H, Nq, d, dtype, bias, causal, alibi_slopes, sq, sk, sv, so, stream};
+  a.Nk = Nk;
+  a.end_aligned = true;
+  a.split = true;
+  a.workspace = workspace; a.workspace_bytes = workspace_bytes;
   return fwd_impl<false>(a);
 }
 

@@ -48,6 +48,10 @@ struct FwdParams {
   // 64-row causal kernel: every workgroup handles two query blocks of its head, the r-th longest
   // and the r-th shortest (n_qblocks even), so that all workgroups of a launch do the same work
   int pair;
+  // kernel for few queries: workgroups that share the keys of a query block (>= 1), and with more
+  // than one their fp32 partial outputs, part[split][B*H][N][d]
+  int n_split;
+  float* part;
   ClockProbe clock;  // measurement aid, {nullptr, 0} otherwise
 };
 

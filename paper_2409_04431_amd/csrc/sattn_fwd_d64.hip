@@ -2,3 +2,4 @@
 #include "sattn_fwd_launch.hpp"
 
 template int sattn::launch_fwd_bf16<64>(sattn::FwdParams, int, int, bool, bool, int, bool, hipStream_t);
+template int sattn::launch_fwd_few<64>(sattn::FwdParams, int, bool, hipStream_t);

@@ -1,5 +1,6 @@
 // Definition of launch_fwd_bf16<D>; included by the one translation unit that instantiates it.
 #pragma once
+#include "sattn_few.hpp"
 #include "sattn_fwd64.hpp"
 #include "sattn_launch.hpp"
 
@@ -64,6 +65,21 @@ int launch_fwd_bf16(FwdParams p, int waves, int v_slots, bool softmax, bool pin,
     return launch_fwd_shape<D, 4, 3>(p, softmax, pin, causal, alibi, st);
   }
   return launch_fwd_shape<D, 8, 3>(p, softmax, pin, causal, alibi, st);
+}
+
+template <int D>
+int launch_fwd_few(FwdParams p, int causal, bool alibi, hipStream_t st) {
+  constexpr int NW = 8;
+  p.n_qblocks = (p.N + 31) / 32;
+  dim3 grid(p.n_qblocks * p.n_split * p.B * p.H), block(64 * NW);
+  int rc = SATTN_OK;
+  SATTN_DISPATCH2(causal, alibi, rc = launch(attn_fwd_few_kernel<D, A, B2, NW>, grid, block, few_lds_bytes<D>(NW), st, p));
+  if (rc == SATTN_OK && p.n_split > 1) {
+    const int64_t threads = (int64_t)p.B * p.H * p.N * (D / 4);
+    rc = launch(few_partials_reduce_kernel<D>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st,
+                (const float*)p.part, p.o, p.n_split, p.B, p.H, p.N);
+  }
+  return rc;
 }
 
 }  // namespace sattn

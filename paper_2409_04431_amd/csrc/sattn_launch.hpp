@@ -66,6 +66,10 @@ template <int D>
 int launch_fwd_bf16(FwdParams p, int waves, int v_slots, bool softmax, bool pin, int causal, bool alibi,
                     hipStream_t st);
 
+// Forward with 32 query rows per workgroup whose waves (and p.n_split workgroups) split the keys.
+template <int D>
+int launch_fwd_few(FwdParams p, int causal, bool alibi, hipStream_t st);
+
 // Backward: `parts` is a mask of BwdPart; p.db_rows selects the dQ pass with row sums; `merged`
 // lets the two passes of the pinned sigmoid backward share one grid where that form exists.
 template <int D>

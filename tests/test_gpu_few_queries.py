@@ -1,0 +1,51 @@
+"""The forward kernel for few queries (32 rows per workgroup, the keys split over its waves and over
+workgroups): parity with the fp64 oracle at the edges of its range."""
+import math
+
+import pytest
+import torch
+
+import paper_2409_04431_amd as sa
+from oracle import sattn_oracle as orc
+from paper_2409_04431_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+TOL = 2e-2  # of max |reference|: the bf16 bar of the library (P and O are rounded to bf16, 2^-9 each)
+
+
+@pytest.mark.parametrize("B,H,Nq,Nk,d,causal,alibi,split", [
+    (1, 1, 1, 2, 128, False, False, 1),        # one chunk for eight waves, two keys
+    (2, 2, 1, 225, 64, False, True, 1),        # eight chunks, the last with one key
+    (1, 3, 1, 1023, 128, False, True, 4),      # 32 chunks: the fewest that are split, ragged
+    (1, 2, 33, 33 + 64 * 32, 64, True, True, 8),    # a second block of one row, masked chunks, split
+    (1, 2, 100, 420, 128, True, False, 1),     # four blocks, the last of four rows
+    (1, 16, 512, 2048, 128, True, False, 1),   # 256 blocks and four keys per query: the last that take this kernel
+    (1, 16, 513, 2081, 128, True, False, 0),   # 272 blocks: the first that do not
+    (1, 2, 257, 993, 64, True, False, 0),      # less than four keys per query
+])
+def test_few_queries_match_oracle(B, H, Nq, Nk, d, causal, alibi, split):
+    g = torch.Generator().manual_seed(17 + Nq + Nk)
+    q = torch.randn(B, H, Nq, d, generator=g).bfloat16()
+    k, v = (torch.randn(B, H, Nk, d, generator=g).bfloat16() for _ in range(2))
+    slopes = W.alibi_slopes(H) if alibi else None
+    sl = slopes.cuda() if alibi else None
+    bias = -math.log(Nk)
+    Q, K, V = q.cuda(), k.cuda(), v.cuda()
+    need = sa.sigmoid_attn_cross_aligned_fwd_workspace_bytes(B, H, Nq, Nk, d)
+    cus, _ = sa.sattn_device_info()
+    if cus == 256:
+        assert need == (split * B * H * Nq * d * 4 if split > 1 else 0)
+    o, o1 = (torch.full_like(Q, float("nan")) for _ in range(2))
+    sa.sigmoid_attn_cross_aligned_fwd(Q, K, V, o, bias, causal, sl)
+    ws = torch.full((max(need, 4) // 4,), float("nan"), dtype=torch.float32, device="cuda")
+    sa.sigmoid_attn_cross_aligned_fwd_split(Q, K, V, o1, bias, causal, sl, workspace=ws)
+    torch.cuda.synchronize()
+    assert torch.equal(o, o1)
+    slo = slopes.double().numpy() if alibi else None
+    ref = orc.sigmoid_attn_cross_fwd(q.double().numpy(), k.double().numpy(), v.double().numpy(), bias, causal, slo)
+    err = abs(o.double().cpu().numpy() - ref).max() / abs(ref).max()
+    assert err <= TOL, f"{err:.3e}"
+    if need:
+        with pytest.raises(sa.SattnError):
+            sa.sigmoid_attn_cross_aligned_fwd_split(Q, K, V, o1, bias, causal, sl, workspace=ws[:-1])
