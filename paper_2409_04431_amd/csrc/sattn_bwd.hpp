@@ -205,6 +205,12 @@ __device__ __forceinline__ bf16x8 pack8(const float* x) {
   return as_bf16x8(w);
 }
 
+// Causal ALiBi: whether the register part of slope*(i-j) sits in the S accumulators from the start
+// (no instruction per element, sixteen registers for the initial value).  At d = 64 those
+// registers are what keeps a kernel from a second workgroup per compute unit, which is worth more.
+template <int D>
+constexpr bool kFoldAcc = D == 128;
+
 // Per-wave pipeline state.
 template <int D, int MODE>
 struct BwdWave {
@@ -213,7 +219,8 @@ struct BwdWave {
   uint32_t row1[KD];    // same in tile t+1
   uint32_t tr[DT][2];   // LDS address of the transposed-read pair for d-tile dt in tile t-1 (tensor 1)
   bf16x8 x1[KD], x2[KD];  // stationary B operands of the first products
-  bf16x8 F[2 * KD];       // streamed row fragments: F[2kk] from tensor 1, F[2kk+1] from tensor 2
+  static constexpr int WIN = 4;
+  bf16x8 F[2 * KD];       // streamed row fragments: F[2kk] from tensor 1, F[2kk+1] from tensor 2 (or a window of WIN)
   f32x16 acc0[DT];        // DQ: dQ^T ; DKDV: dK^T
   f32x16 acc1[MODE == BWD_DKDV ? DT : 1];  // DKDV: dV^T
   f32x16 s[2], dp[2];     // first products of chunk c in [c&1]
@@ -282,7 +289,7 @@ __device__ __forceinline__ void bwd_step(BwdWave<D, MODE>& W, bool doA, bool doS
   // slope*(i - j) splits into a per-lane, per-step part added to the bias and a per-register
   // part that is a constant of the kernel and sits in the S accumulators from the start
   // (W.cinit, already divided by the logit scale): no ALiBi arithmetic per element.
-  constexpr bool FOLD = !SOFTMAX && CAUSAL && ALIBI;
+  constexpr bool FOLD = !SOFTMAX && CAUSAL && ALIBI && kFoldAcc<D>;
   if (doA) {
     if constexpr (FOLD) b_mfma_vinit(W.s[PAR], W.F[0], W.x1[0], W.cinit);
     else b_mfma_v0<true>(W.s[PAR], W.F[0], W.x1[0]);
@@ -403,10 +410,19 @@ __device__ __forceinline__ void bsig_load_stats(BsigStats& st) {
   st.l[G] = *(SATTN_LDS(f32x4)*)(uintptr_t)(st.stat + off);
   st.d[G] = *(SATTN_LDS(f32x4)*)(uintptr_t)(st.stat + off + 256);
 }
-template <int D, int MODE, bool ALIBI, bool MASK, bool SMX, int I>
+// How the ALiBi term enters the element stream.  kAlAbs: slope*|i-j| per element (two instructions
+// more than without; the register's key offset is a literal).  kAlSigned: every unmasked pair has
+// its key at or before its query, so the per-lane, per-step part of slope*(i-j) is already in
+// nbias_v and one instruction adds the register's part.
+enum AlibiForm { kAlNone = 0, kAlAbs = 1, kAlSigned = 2 };
+template <int MODE>
+constexpr int key_offset_bits(int e) {  // +-key_of_reg(e) as fp32 bits: DKDV streams queries (+), DQ keys (-)
+  return __builtin_bit_cast(int, MODE == BWD_DKDV ? (float)key_of_reg(e) : -(float)key_of_reg(e));
+}
+template <int D, int MODE, int AL, bool MASK, bool SMX, int I>
 __device__ __forceinline__ void bsig_op(BwdWave<D, MODE>& W, const f32x16& s, const f32x16& dp, float (&u)[16],
                                         float (&v)[16], uint32_t (&wp)[8], uint32_t (&wd)[8], uint64_t (&km)[16],
-                                        float nbias_v, float sl2_v, float dist0, float dstep, int thr, float dstat_v,
+                                        float nbias_v, float sl2_v, float dist0, int thr, float dstat_v,
                                         BsigStats& st) {
   using L = BsigLayout<MODE, MASK, SMX>;
   constexpr int G = I / L::OPG, i = I % L::OPG, e = 4 * G + (i & 3);
@@ -417,10 +433,14 @@ __device__ __forceinline__ void bsig_op(BwdWave<D, MODE>& W, const f32x16& s, co
     if constexpr (i >= L::oQ && i < L::oM) dstat_v = st.d[G][i & 3];
   }
   if constexpr (i < L::oX) {
-    if constexpr (ALIBI) {
+    if constexpr (AL == kAlSigned) {
+      static_assert(!SMX, "softmax: ALiBi in its |i-j| form");
+      float w;
+      asm volatile("v_fmamk_f32 %0, %1, %2, %3" : "=v"(w) : "v"(sl2_v), "n"(key_offset_bits<MODE>(e)), "v"(nbias_v));
+      asm volatile("v_fma_f32 %0, %1, %2, %3" : "=v"(u[e]) : "v"(s[e]), "s"(W.nscale), "v"(w));
+    } else if constexpr (AL == kAlAbs) {
       float t, w;
-      const float keyf = (float)key_of_reg(e);
-      asm volatile("v_fma_f32 %0, %1, %2, %3" : "=v"(t) : "v"(dstep), "v"(keyf), "v"(dist0));
+      asm volatile("v_add_f32 %0, %1, %2" : "=v"(t) : "n"(key_offset_bits<MODE>(e)), "v"(dist0));
       asm volatile("v_fma_f32 %0, %1, |%2|, %3" : "=v"(w) : "v"(sl2_v), "v"(t), "v"(nbias_v));
       if constexpr (SMX) asm volatile("v_fma_f32 %0, %1, -%2, %3" : "=v"(u[e]) : "v"(s[e]), "s"(W.nscale), "v"(w));
       else asm volatile("v_fma_f32 %0, %1, %2, %3" : "=v"(u[e]) : "v"(s[e]), "s"(W.nscale), "v"(w));
@@ -458,22 +478,22 @@ __device__ __forceinline__ void bsig_op(BwdWave<D, MODE>& W, const f32x16& s, co
     asm volatile("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(wd[j]) : "v"(v[2 * j]), "v"(v[2 * j + 1]));
   }
 }
-template <int D, int MODE, bool ALIBI, bool MASK, bool SMX, int LO, int HI>
+template <int D, int MODE, int AL, bool MASK, bool SMX, int LO, int HI>
 __device__ __forceinline__ void bsig_ops(BwdWave<D, MODE>& W, const f32x16& s, const f32x16& dp, float (&u)[16],
                                          float (&v)[16], uint32_t (&wp)[8], uint32_t (&wd)[8], uint64_t (&km)[16],
-                                         float nbias_v, float sl2_v, float dist0, float dstep, int thr, float dstat_v,
+                                         float nbias_v, float sl2_v, float dist0, int thr, float dstat_v,
                                          BsigStats& st) {
   if constexpr (LO < HI) {
-    bsig_op<D, MODE, ALIBI, MASK, SMX, LO>(W, s, dp, u, v, wp, wd, km, nbias_v, sl2_v, dist0, dstep, thr, dstat_v, st);
-    bsig_ops<D, MODE, ALIBI, MASK, SMX, LO + 1, HI>(W, s, dp, u, v, wp, wd, km, nbias_v, sl2_v, dist0, dstep, thr, dstat_v, st);
+    bsig_op<D, MODE, AL, MASK, SMX, LO>(W, s, dp, u, v, wp, wd, km, nbias_v, sl2_v, dist0, thr, dstat_v, st);
+    bsig_ops<D, MODE, AL, MASK, SMX, LO + 1, HI>(W, s, dp, u, v, wp, wd, km, nbias_v, sl2_v, dist0, thr, dstat_v, st);
   }
 }
 
-template <int D, int MODE, bool ALIBI, int PAR, bool DMA, bool MASK, bool FOLD, bool GUARD, bool SMX, int K>
+template <int D, int MODE, int AL, int PAR, bool DMA, bool MASK, bool FOLD, bool GUARD, bool SMX, int K>
 __device__ __forceinline__ void bwd_full_subslots(BwdWave<D, MODE>& W, uint32_t trimm, const uint32_t* nextrow,
                                                   uint32_t nextimm, float (&u)[16], float (&v)[16], uint32_t (&wp)[8],
                                                   uint32_t (&wd)[8], uint64_t (&km)[16], float nbias_v, float sl2_v,
-                                                  float dist0, float dstep, int thr, float dstat_v, BsigStats& stats,
+                                                  float dist0, int thr, float dstat_v, BsigStats& stats,
                                                   const DmaStagerX<D, 4>& st1,
                                                   const DmaStagerX<D, 4>& st2, uint32_t dma_lds, int uwave) {
   constexpr int KD = D / 16, DT = D / 32;
@@ -521,9 +541,9 @@ __device__ __forceinline__ void bwd_full_subslots(BwdWave<D, MODE>& W, uint32_t 
         W.F[2 * j] = as_bf16x8(lds_read_b128(nextrow[j] + nextimm));
       }
     }
-    bsig_ops<D, MODE, ALIBI, MASK, SMX, (K * NOPS) / NSUB, ((K + 1) * NOPS) / NSUB>(W, W.s[PAR ^ 1], W.dp[PAR ^ 1], u, v, wp,
-                                                                                    wd, km, nbias_v, sl2_v, dist0, dstep,
-                                                                                    thr, dstat_v, stats);
+    bsig_ops<D, MODE, AL, MASK, SMX, (K * NOPS) / NSUB, ((K + 1) * NOPS) / NSUB>(W, W.s[PAR ^ 1], W.dp[PAR ^ 1], u, v, wp,
+                                                                                 wd, km, nbias_v, sl2_v, dist0, thr, dstat_v,
+                                                                                 stats);
     if constexpr (DMA) {
       // one staging instruction of the tile two ahead every DSTEP sub-slots
       constexpr int NI = DmaStagerX<D, 4>::NI, DSTEP = NSUB / (2 * NI);
@@ -533,9 +553,9 @@ __device__ __forceinline__ void bwd_full_subslots(BwdWave<D, MODE>& W, uint32_t 
         else st2.template issue_one<n - NI>(dma_lds + 64 * D * 2, uwave);
       }
     }
-    bwd_full_subslots<D, MODE, ALIBI, PAR, DMA, MASK, FOLD, GUARD, SMX, K + 1>(W, trimm, nextrow, nextimm, u, v, wp, wd, km,
-                                                                               nbias_v, sl2_v, dist0, dstep, thr, dstat_v,
-                                                                               stats, st1, st2, dma_lds, uwave);
+    bwd_full_subslots<D, MODE, AL, PAR, DMA, MASK, FOLD, GUARD, SMX, K + 1>(W, trimm, nextrow, nextimm, u, v, wp, wd, km,
+                                                                            nbias_v, sl2_v, dist0, thr, dstat_v, stats, st1,
+                                                                            st2, dma_lds, uwave);
   }
 }
 
@@ -546,7 +566,7 @@ __device__ __forceinline__ void bwd_full_subslots(BwdWave<D, MODE>& W, uint32_t 
 // which waits once after the loop).
 // SMX: the softmax arithmetic (dQ pass: W.nlse and W.dstat hold the lane's row statistics; dK/dV
 // pass: `stat` = LDS address of the statistics of the lane's first query in the chunk).
-template <int D, int MODE, bool ALIBI, bool FOLD, int PAR, bool DMA, bool MASK = false, bool SETTLE = true, bool GUARD = false,
+template <int D, int MODE, int AL, int PAR, bool DMA, bool MASK = false, bool SETTLE = true, bool GUARD = false,
           bool SMX = false>
 __device__ __forceinline__ void bwd_step_full_pinned(BwdWave<D, MODE>& W, uint32_t trimm, const uint32_t* nextrow,
                                                      uint32_t nextimm, int cs, const DmaStagerX<D, 4>& st1,
@@ -560,16 +580,14 @@ __device__ __forceinline__ void bwd_step_full_pinned(BwdWave<D, MODE>& W, uint32
   // |i-j| of register r: DKDV streams queries (b - a), DQ streams keys (a - b)
   const int bl = cs + 8 * W.h;
   const float dist0 = MODE == BWD_DKDV ? (float)(bl - W.ai) : (float)(W.ai - bl);
-  const float dstep = MODE == BWD_DKDV ? 1.0f : -1.0f;
-  static_assert(!SMX || !FOLD, "softmax: ALiBi in its |i-j| form");
-  if constexpr (FOLD)  // the per-element arithmetic is the one without ALiBi, on a per-step bias
-    bwd_full_subslots<D, MODE, false, PAR, DMA, MASK, true, GUARD, false, 0>(W, trimm, nextrow, nextimm, u, v, wp, wd, km,
-                                                                      __builtin_fmaf(W.sl2, dist0, W.nbias), W.sl2, dist0,
-                                                                      dstep, thr, 0.f, stats, st1, st2, dma_lds, uwave);
-  else
-    bwd_full_subslots<D, MODE, ALIBI, PAR, DMA, MASK, false, GUARD, SMX, 0>(W, trimm, nextrow, nextimm, u, v, wp, wd, km,
-                                                                     SMX ? W.nlse : W.nbias, SMX ? -W.sl2 : W.sl2, dist0,
-                                                                     dstep, thr, W.dstat, stats, st1, st2, dma_lds, uwave);
+  static_assert(!SMX || AL != kAlSigned, "softmax: ALiBi in its |i-j| form");
+  // signed form: the per-lane, per-step part joins the bias; the register part sits in the S
+  // accumulators (kFoldAcc) or costs an instruction per element
+  constexpr bool ACC = AL == kAlSigned && kFoldAcc<D>;
+  const float nbias_v = AL == kAlSigned ? __builtin_fmaf(W.sl2, dist0, W.nbias) : (SMX ? W.nlse : W.nbias);
+  bwd_full_subslots<D, MODE, ACC ? kAlNone : AL, PAR, DMA, MASK, ACC, GUARD, SMX, 0>(
+      W, trimm, nextrow, nextimm, u, v, wp, wd, km, nbias_v, SMX ? -W.sl2 : W.sl2, dist0, thr, W.dstat, stats, st1, st2,
+      dma_lds, uwave);
   // The compiler does not know that the asm statements above are MFMAs: let the last ones
   // retire before it may touch their accumulators (copies at the join with the other path).
   if constexpr (SETTLE) mfma_settle();
@@ -579,6 +597,186 @@ __device__ __forceinline__ void bwd_step_full_pinned(BwdWave<D, MODE>& W, uint32
   }
   W.dsb[PAR ^ 1][0] = as_bf16x8(u32x4{wd[0], wd[1], wd[2], wd[3]});
   W.dsb[PAR ^ 1][1] = as_bf16x8(u32x4{wd[4], wd[5], wd[6], wd[7]});
+}
+
+// ---- The same pipeline within 256 registers (sigmoid passes at d = 64) ----
+// A step runs the second products of chunk s-2 first and the first products of chunk s last, so
+// that P and dS of one chunk only are alive (the second products have read a word before the
+// element stream of chunk s-1 writes the word that follows it), and the operand fragments come
+// through a window of four slots instead of eight: the fragment of the MFMA four places on is
+// fetched into the slot of the MFMA just issued, which with another workgroup's wave on the same
+// SIMD is ahead enough.  At the start of a step the window holds the first four transposed
+// fragments of chunk s-2.  The rows of chunk s are read in step s from tile t, the transposed
+// fragments of chunk s-2 from tile t-1; the odd step of a tile turns the addresses on by one ring
+// slot (`turn_tr`, `turn_row`) as soon as their last reads of the tile have been issued.
+// Bound: vector-instruction issue (7 instructions per element against half the matrix work of
+// d = 128), of which a lone wave reaches about one in six cycles; the second wave per SIMD is what
+// the registers are saved for: dK/dV 292-324 -> 240-252 of 512, dQ 248-276 -> 204-216, one grid
+// 300-320 -> 244-248.  Measured (us, eight-slot form / this one): dK/dV B32 H12 N4096 causal
+// 1997 / 1621, B32 H12 N1024 272 / 214, B32 H12 N250 39 / 30, B1 H16 N2048 causal 42 / 40; dQ
+// unchanged; one grid B4 H12 N1024 69 / 57.
+template <int D, int MODE, int AL, int PAR, bool DMA, bool MASK, bool GUARD, int K>
+__device__ __forceinline__ void bwd_window_subslots(BwdWave<D, MODE>& W, f32x16& s_new, f32x16& dp_new, int turn_tr,
+                                                    int turn_row, float (&u)[16], float (&v)[16], uint32_t (&wp)[8],
+                                                    uint32_t (&wd)[8], uint64_t (&km)[16], float nbias_v, float dist0,
+                                                    int thr, BsigStats& stats, const DmaStagerX<D, 4>& st1,
+                                                    const DmaStagerX<D, 4>& st2, uint32_t dma_lds, int uwave) {
+  constexpr int KD = D / 16, DT = D / 32, WIN = BwdWave<D, MODE>::WIN;
+  constexpr uint32_t T2OFF = 64 * D * 2, CHUNK = 32 * D * 2;
+  // second-product MFMAs (NT of them per half chunk and d-tile), all MFMAs
+  constexpr int NT = MODE == BWD_DKDV ? 2 : 1, NB = NT * KD, NSUB = NB + 2 * KD;
+  constexpr int NOPS = BsigLayout<MODE, MASK, false>::NOPS;
+  static_assert(2 * DT == KD && NB >= WIN, "second products: (tensor, d-tile, half chunk)");
+  if constexpr (K < NSUB) {
+    if constexpr (K < NB) {
+      constexpr int j = K / NT;
+      if constexpr (K % NT == 0) b_mfma_a<GUARD>(W.acc0[j % DT], W.F[K % WIN], W.dsb[0][j / DT]);  // dK^T += Q^T dS, dQ^T += K^T dS^T
+      else b_mfma_a<GUARD>(W.acc1[j % DT], W.F[K % WIN], W.pb[0][j / DT]);                         // dV^T += dO^T P
+    } else {
+      constexpr int kk = (K - NB) / 2;
+      if constexpr (((K - NB) & 1) == 0) {
+        if constexpr (kk == 0) b_mfma_v0<GUARD>(s_new, W.F[K % WIN], W.x1[kk]);
+        else b_mfma_v<GUARD>(s_new, W.F[K % WIN], W.x1[kk]);
+      } else {
+        if constexpr (kk == 0) b_mfma_v0<GUARD>(dp_new, W.F[K % WIN], W.x2[kk]);
+        else b_mfma_v<GUARD>(dp_new, W.F[K % WIN], W.x2[kk]);
+      }
+    }
+    constexpr int M = K + WIN;  // the MFMA whose fragment is fetched now
+    if constexpr (M < NB) {
+      constexpr int j = M / NT;
+      constexpr uint32_t off = PAR * CHUNK + (j / DT) * 16 * (D * 2) + (M % NT) * T2OFF;
+      W.F[M % WIN] = join_tr(lds_read_tr16(W.tr[j % DT][0] + off), lds_read_tr16(W.tr[j % DT][1] + off));
+    } else if constexpr (M < NSUB) {
+      W.F[M % WIN] = as_bf16x8(lds_read_b128(W.row0[(M - NB) / 2] + PAR * CHUNK + ((M - NB) & 1) * T2OFF));
+    } else {  // the next step's: chunk s-1, second half of tile t-1 or first half of tile t
+      constexpr int j = (M - NSUB) / NT;
+      constexpr uint32_t off = (PAR ^ 1) * CHUNK + (j / DT) * 16 * (D * 2) + ((M - NSUB) % NT) * T2OFF;
+      W.F[M % WIN] = join_tr(lds_read_tr16(W.tr[j % DT][0] + off), lds_read_tr16(W.tr[j % DT][1] + off));
+    }
+    if constexpr (PAR == 1 && K == NB - WIN) {
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) { W.tr[dt][0] += turn_tr; W.tr[dt][1] += turn_tr; }
+    }
+    if constexpr (PAR == 1 && M == NSUB - 1) {
+#pragma unroll
+      for (int kk = 0; kk < KD; ++kk) W.row0[kk] += turn_row;
+    }
+    bsig_ops<D, MODE, AL, MASK, false, (K * NOPS) / NSUB, ((K + 1) * NOPS) / NSUB>(W, W.s[0], W.dp[0], u, v, wp, wd, km, nbias_v,
+                                                                                  W.sl2, dist0, thr, 0.f, stats);
+    if constexpr (DMA) {
+      // one staging instruction of the tile two ahead every DSTEP sub-slots
+      constexpr int NI = DmaStagerX<D, 4>::NI, DSTEP = NSUB / (2 * NI);
+      if constexpr (K % DSTEP == 1 && K / DSTEP < 2 * NI) {
+        constexpr int n = K / DSTEP;
+        if constexpr (n < NI) st1.template issue_one<n>(dma_lds, uwave);
+        else st2.template issue_one<n - NI>(dma_lds + 64 * D * 2, uwave);
+      }
+    }
+    bwd_window_subslots<D, MODE, AL, PAR, DMA, MASK, GUARD, K + 1>(W, s_new, dp_new, turn_tr, turn_row, u, v, wp, wd, km,
+                                                                   nbias_v, dist0, thr, stats, st1, st2, dma_lds, uwave);
+  }
+}
+
+// The pinned step in this order; thr, MASK, GUARD and SETTLE as in bwd_step_full_pinned.
+template <int D, int MODE, int AL, int PAR, bool DMA, bool MASK, bool SETTLE, bool GUARD>
+__device__ __forceinline__ void bwd_window_step_pinned(BwdWave<D, MODE>& W, int turn_tr, int turn_row, int cs,
+                                                       const DmaStagerX<D, 4>& st1, const DmaStagerX<D, 4>& st2,
+                                                       uint32_t dma_lds, int uwave, int thr) {
+  static_assert(AL != kAlSigned || !kFoldAcc<D>, "the register part of ALiBi is an instruction per element here");
+  float u[16], v[16];
+  uint32_t wp[8], wd[8];
+  uint64_t km[16];
+  BsigStats stats;
+  f32x16 s_new, dp_new;
+  const int bl = cs + 8 * W.h;
+  const float dist0 = MODE == BWD_DKDV ? (float)(bl - W.ai) : (float)(W.ai - bl);
+  const float nbias_v = AL == kAlSigned ? __builtin_fmaf(W.sl2, dist0, W.nbias) : W.nbias;
+  bwd_window_subslots<D, MODE, AL, PAR, DMA, MASK, GUARD, 0>(W, s_new, dp_new, turn_tr, turn_row, u, v, wp, wd, km, nbias_v,
+                                                             dist0, thr, stats, st1, st2, dma_lds, uwave);
+  if constexpr (SETTLE) mfma_settle(s_new, dp_new);
+  W.s[0] = s_new;
+  W.dp[0] = dp_new;
+  if (MODE == BWD_DKDV) {
+    W.pb[0][0] = as_bf16x8(u32x4{wp[0], wp[1], wp[2], wp[3]});
+    W.pb[0][1] = as_bf16x8(u32x4{wp[4], wp[5], wp[6], wp[7]});
+  }
+  W.dsb[0][0] = as_bf16x8(u32x4{wd[0], wd[1], wd[2], wd[3]});
+  W.dsb[0][1] = as_bf16x8(u32x4{wd[4], wd[5], wd[6], wd[7]});
+}
+
+// The window's first four transposed fragments, chunk half HALF of the tile W.tr points at.
+template <int D, int MODE, int HALF>
+__device__ __forceinline__ void bwd_window_fill(BwdWave<D, MODE>& W) {
+  constexpr int DT = D / 32, NT = MODE == BWD_DKDV ? 2 : 1;
+  constexpr uint32_t T2OFF = 64 * D * 2, CHUNK = 32 * D * 2;
+#pragma unroll
+  for (int m = 0; m < BwdWave<D, MODE>::WIN; ++m) {
+    const uint32_t off = HALF * CHUNK + (m / NT / DT) * 16 * (D * 2) + (m % NT) * T2OFF;
+    W.F[m] = join_tr(lds_read_tr16(W.tr[m / NT % DT][0] + off), lds_read_tr16(W.tr[m / NT % DT][1] + off));
+  }
+}
+
+// The flag-driven, compiler-scheduled step in this order: second products of chunk s-2, p / dS of
+// chunk s-1, first products of chunk s, each only where its flag is set.
+template <int D, int MODE, bool CAUSAL, bool ALIBI, int PAR>
+__device__ __forceinline__ void bwd_window_step(BwdWave<D, MODE>& W, bool doA, bool doS, bool doB, bool mask, int turn_tr,
+                                                int turn_row, int cs, int N) {
+  constexpr int KD = D / 16, DT = D / 32;
+  constexpr uint32_t T2OFF = 64 * D * 2, CHUNK = 32 * D * 2;
+  if (doB) {
+#pragma unroll
+    for (int j = 0; j < 2 * DT; ++j) {
+      const uint32_t off = PAR * CHUNK + (j / DT) * 16 * (D * 2);
+      const uint32_t a0 = W.tr[j % DT][0] + off, a1 = W.tr[j % DT][1] + off;
+      if (MODE == BWD_DKDV) {
+        bf16x8 ado = join_tr(lds_read_tr16(a0 + T2OFF), lds_read_tr16(a1 + T2OFF));
+        b_mfma_a<true>(W.acc1[j % DT], ado, W.pb[0][j / DT]);
+      }
+      bf16x8 a1t = join_tr(lds_read_tr16(a0), lds_read_tr16(a1));
+      b_mfma_a<true>(W.acc0[j % DT], a1t, W.dsb[0][j / DT]);
+    }
+    mfma_settle();
+  }
+  if (doS) {
+    const int bl = cs + 8 * W.h;
+    float pr[16], ds[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int b = bl + key_of_reg(r);
+      const int qrow = MODE == BWD_DKDV ? b : W.ai, krow = MODE == BWD_DKDV ? W.ai : b;
+      float w = W.nbias;
+      if (ALIBI) w = __builtin_fmaf(W.sl2, __builtin_fabsf((float)(qrow - krow)), w);
+      const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(W.s[0][r], W.nscale, w));
+      pr[r] = __builtin_amdgcn_rcpf(1.0f + e);
+      ds[r] = __builtin_fmaf(-pr[r], pr[r], pr[r]) * W.dp[0][r];
+      if (mask) {
+        const bool keep = b < N && (!CAUSAL || krow <= qrow);
+        pr[r] = keep ? pr[r] : 0.f;
+        ds[r] = keep ? ds[r] : 0.f;
+      }
+      if (MODE == BWD_DQ_DB) W.dbs[r & 3] += ds[r];
+    }
+    if (MODE == BWD_DKDV) { W.pb[0][0] = pack8(pr); W.pb[0][1] = pack8(pr + 8); }
+    W.dsb[0][0] = pack8(ds); W.dsb[0][1] = pack8(ds + 8);
+  }
+  if (doA) {
+#pragma unroll
+    for (int kk = 0; kk < KD; ++kk) {
+      const bf16x8 f1 = as_bf16x8(lds_read_b128(W.row0[kk] + PAR * CHUNK));
+      const bf16x8 f2 = as_bf16x8(lds_read_b128(W.row0[kk] + PAR * CHUNK + T2OFF));
+      if (kk == 0) { b_mfma_v0<true>(W.s[0], f1, W.x1[0]); b_mfma_v0<true>(W.dp[0], f2, W.x2[0]); }
+      else { b_mfma_v<true>(W.s[0], f1, W.x1[kk]); b_mfma_v<true>(W.dp[0], f2, W.x2[kk]); }
+    }
+    mfma_settle(W.s[0], W.dp[0]);
+  }
+  if constexpr (PAR == 1) {
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) { W.tr[dt][0] += turn_tr; W.tr[dt][1] += turn_tr; }
+#pragma unroll
+    for (int kk = 0; kk < KD; ++kk) W.row0[kk] += turn_row;
+  }
+  bwd_window_fill<D, MODE, PAR ^ 1>(W);
 }
 
 // PIN = false runs every step in its compiler-scheduled form (the form the softmax variant
@@ -593,7 +791,10 @@ __device__ __forceinline__ void attn_bwd_body(const BwdParams& p, const int bh, 
                                               const int tid) {
   static_assert(!GROUPS || MODE == BWD_DKDV, "only the dK/dV pass iterates over query heads");
   constexpr int NW = 4, BS = 32 * NW, BC = 64, KD = D / 16, DT = D / 32;
-  constexpr bool FOLD = !SOFTMAX && CAUSAL && ALIBI;  // see bwd_step
+  constexpr bool FOLD = !SOFTMAX && CAUSAL && ALIBI && kFoldAcc<D>;  // see bwd_step
+  // the order of a step that fits 256 registers, so that two workgroups share a compute unit
+  constexpr bool kWindow = D == 64 && PIN && !SOFTMAX;
+  constexpr int AL = !ALIBI ? kAlNone : (CAUSAL && !SOFTMAX ? kAlSigned : kAlAbs);  // the pinned steps' ALiBi form
   // kernels that carry the pinned steps; kStats: the softmax dK/dV pass, whose pinned steps read
   // the row statistics of the streamed queries from a side ring in LDS
   constexpr bool kPinned = PIN;
@@ -787,11 +988,15 @@ __device__ __forceinline__ void attn_bwd_body(const BwdParams& p, const int bh, 
   }
   __syncthreads();
   clock_probe_mark(p.clock, clk, kMarkFirstProduct);
-  // rows of chunk 2*t_lo for the first step
+  if constexpr (kWindow) {
+    bwd_window_fill<D, MODE, 0>(W);  // (zeros: the empty second-product stage of the first step)
+  } else {
+    // rows of chunk 2*t_lo for the first step
 #pragma unroll
-  for (int kk = 0; kk < KD; ++kk) {
-    W.F[2 * kk] = as_bf16x8(lds_read_b128(W.row0[kk]));
-    W.F[2 * kk + 1] = as_bf16x8(lds_read_b128(W.row0[kk] + TILE));
+    for (int kk = 0; kk < KD; ++kk) {
+      W.F[2 * kk] = as_bf16x8(lds_read_b128(W.row0[kk]));
+      W.F[2 * kk + 1] = as_bf16x8(lds_read_b128(W.row0[kk] + TILE));
+    }
   }
 
   // Iteration t runs steps 2t and 2t+1 with one barrier between them.  Tile t+2 is staged
@@ -849,6 +1054,9 @@ __device__ __forceinline__ void attn_bwd_body(const BwdParams& p, const int bh, 
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) { W.tr[dt][0] += advt; W.tr[dt][1] += advt; }
   };
+  // (window form: what the odd step of tile t adds to the addresses)
+  auto turn_tr = [&](int t) { return t % NSLOT == 0 ? -(NSLOT - 1) * SLOT : SLOT; };
+  auto turn_row = [&](int t) { return t % NSLOT == NSLOT - 1 ? -(NSLOT - 1) * SLOT : SLOT; };
   int t = t_lo;
   int general_end = t_s0 < t_hi + 1 ? t_s0 : t_hi + 1;
   for (int phase = 0; phase < 2; ++phase) {
@@ -862,9 +1070,12 @@ __device__ __forceinline__ void attn_bwd_body(const BwdParams& p, const int bh, 
         int thr;
         step_kind(s, pin_s, thr);
         // (the other kernels do not carry the pinned code at all)
-        if (kPinned && lane_flag(pin_s)) {
+        if constexpr (kWindow) {
+          if (lane_flag(pin_s)) bwd_window_step_pinned<D, MODE, AL, 0, false, true, true, GROUPS>(W, 0, 0, 32 * (s - 1), st1, st2, 0, uwave, thr);
+          else bwd_window_step<D, MODE, CAUSAL, ALIBI, 0>(W, lane_flag(doA_s), lane_flag(doS_s), lane_flag(doB_s), lane_flag(mask_s), 0, 0, 32 * (s - 1), Nt);
+        } else if (kPinned && lane_flag(pin_s)) {
           if constexpr (kPinned)
-            bwd_step_full_pinned<D, MODE, ALIBI, FOLD, 0, false, true, true, GROUPS, SOFTMAX>(W, 0, W.row0, CHUNK, 32 * (s - 1), st1, st2, 0, uwave, thr, stat_of_chunk(s - 1));
+            bwd_step_full_pinned<D, MODE, AL, 0, false, true, true, GROUPS, SOFTMAX>(W, 0, W.row0, CHUNK, 32 * (s - 1), st1, st2, 0, uwave, thr, stat_of_chunk(s - 1));
         } else
           bwd_step<D, MODE, CAUSAL, ALIBI, SOFTMAX, 0>(W, lane_flag(doA_s), lane_flag(doS_s), lane_flag(doB_s),
                                                        lane_flag(mask_s), 0, W.row0, CHUNK, 32 * (s - 1), Nt, stat_l, stat_d);
@@ -889,14 +1100,17 @@ __device__ __forceinline__ void attn_bwd_body(const BwdParams& p, const int bh, 
         }
         // rows of chunk s+1 come from tile t+1 (first half); transposed reads of chunk s-2 from tile t-1 (second half)
         // (the other kernels do not carry the pinned code at all)
-        if (kPinned && lane_flag(pin_s)) {
+        if constexpr (kWindow) {
+          if (lane_flag(pin_s)) bwd_window_step_pinned<D, MODE, AL, 1, false, true, true, GROUPS>(W, turn_tr(t), turn_row(t), 32 * (s - 1), st1, st2, 0, uwave, thr);
+          else bwd_window_step<D, MODE, CAUSAL, ALIBI, 1>(W, lane_flag(doA_s), lane_flag(doS_s), lane_flag(doB_s), lane_flag(mask_s), turn_tr(t), turn_row(t), 32 * (s - 1), Nt);
+        } else if (kPinned && lane_flag(pin_s)) {
           if constexpr (kPinned)
-            bwd_step_full_pinned<D, MODE, ALIBI, FOLD, 1, false, true, true, GROUPS, SOFTMAX>(W, CHUNK, W.row1, 0, 32 * (s - 1), st1, st2, 0, uwave, thr, stat_of_chunk(s - 1));
+            bwd_step_full_pinned<D, MODE, AL, 1, false, true, true, GROUPS, SOFTMAX>(W, CHUNK, W.row1, 0, 32 * (s - 1), st1, st2, 0, uwave, thr, stat_of_chunk(s - 1));
         } else
           bwd_step<D, MODE, CAUSAL, ALIBI, SOFTMAX, 1>(W, lane_flag(doA_s), lane_flag(doS_s), lane_flag(doB_s),
                                                        lane_flag(mask_s), CHUNK, W.row1, 0, 32 * (s - 1), Nt, stat_l, stat_d);
       }
-      rotate(t);
+      if constexpr (!kWindow) rotate(t);
     }
     if constexpr (kPinned) if (phase == 0) {
       const bool any_steady = t <= t_s1;
@@ -909,16 +1123,24 @@ __device__ __forceinline__ void attn_bwd_body(const BwdParams& p, const int bh, 
         st2.step_back_inside(n_sat);
       }
       for (; t <= t_s1; ++t) {
-        bwd_step_full_pinned<D, MODE, ALIBI, FOLD, 0, false, false, false, false, SOFTMAX>(W, 0, W.row0, CHUNK, 32 * (2 * t - 1), st1, st2, 0, uwave, 0, stat_of_chunk(2 * t - 1));
-        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): tile t+1 has landed
-        __builtin_amdgcn_s_barrier();
-        stage_stats(st1.j0 / BC, t + 2);  // (the tile the stager is at: t + 2, or the last one again, see above)
-        bwd_step_full_pinned<D, MODE, ALIBI, FOLD, 1, true, false, false, false, SOFTMAX>(W, CHUNK, W.row1, 0, 32 * (2 * t), st1, st2,
-                                                                    lds0 + ((t + 2) % NSLOT) * SLOT, uwave, 0,
-                                                                    stat_of_chunk(2 * t));
+        if constexpr (kWindow) {
+          bwd_window_step_pinned<D, MODE, AL, 0, false, false, false, false>(W, 0, 0, 32 * (2 * t - 1), st1, st2, 0, uwave, 0);
+          __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): tile t+1 has landed
+          __builtin_amdgcn_s_barrier();
+          bwd_window_step_pinned<D, MODE, AL, 1, true, false, false, false>(W, turn_tr(t), turn_row(t), 32 * (2 * t), st1, st2,
+                                                                      lds0 + ((t + 2) % NSLOT) * SLOT, uwave, 0);
+        } else {
+          bwd_step_full_pinned<D, MODE, AL, 0, false, false, false, false, SOFTMAX>(W, 0, W.row0, CHUNK, 32 * (2 * t - 1), st1, st2, 0, uwave, 0, stat_of_chunk(2 * t - 1));
+          __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): tile t+1 has landed
+          __builtin_amdgcn_s_barrier();
+          stage_stats(st1.j0 / BC, t + 2);  // (the tile the stager is at: t + 2, or the last one again, see above)
+          bwd_step_full_pinned<D, MODE, AL, 1, true, false, false, false, SOFTMAX>(W, CHUNK, W.row1, 0, 32 * (2 * t), st1, st2,
+                                                                      lds0 + ((t + 2) % NSLOT) * SLOT, uwave, 0,
+                                                                      stat_of_chunk(2 * t));
+        }
         st1.advance_inside(n_sat);
         st2.advance_inside(n_sat);
-        rotate(t);
+        if constexpr (!kWindow) rotate(t);
       }
       if (any_steady) mfma_settle();  // once for the whole loop of pinned steps
       clock_probe_mark(p.clock, clk, kMarkSteadyEnd);
@@ -990,9 +1212,10 @@ __device__ __forceinline__ int bwd_block_of_rank(const BwdParams& p, int rank) {
 }
 
 // At d = 64 the ring takes 64 KB, so two workgroups fit a compute unit if the kernel stays within
-// 256 registers.  The compiler-scheduled forms (softmax, PIN = false) need that second wave per
-// SIMD to hide their schedule and sit right at the limit, so they are held to it; the pinned
-// forms use more VGPRs than a two-wave split of the register file leaves (128 + 128).
+// 256 registers.  The compiler-scheduled forms (PIN = false) need that second wave per SIMD to
+// hide their schedule and sit right at the limit, so they are held to it; the pinned sigmoid forms
+// stay below it by themselves (138-156 VGPRs and 64 or 96 AGPRs; a launch bound would split the
+// file 128 + 128), the grouped dK/dV pass and the softmax one do not.
 template <int D, int MODE, bool CAUSAL, bool ALIBI, bool SOFTMAX, bool PIN = true, bool GROUPS = false>
 __global__ void __launch_bounds__(256, ((D == 64 && !PIN) ? 2 : 1))
 attn_bwd_kernel(const BwdParams p) {
