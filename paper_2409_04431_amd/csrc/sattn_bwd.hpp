@@ -1230,7 +1230,8 @@ attn_bwd_kernel(const BwdParams p) {
   const int places = pair ? p.n_blocks / 2 : p.n_blocks;
   const int total = places * p.B * (MODE == BWD_DKDV ? p.H / kv_group : p.H) * ((GROUPS && p.n_split > 1) ? p.n_split : 1);
   int bh, rank;
-  bwd_place<MODE, CAUSAL, GROUPS>(p, xcd_remap(blockIdx.x, total), places, bh, rank);
+  if (!GROUPS && p.cu_seqlens) packed_place(p.cu_seqlens, p.B, p.H, places, bh, rank);
+  else bwd_place<MODE, CAUSAL, GROUPS>(p, xcd_remap(blockIdx.x, total), places, bh, rank);
   if constexpr (!kCanPair) {
     attn_bwd_body<D, MODE, CAUSAL, ALIBI, SOFTMAX, PIN, GROUPS>(p, bh, bwd_block_of_rank<MODE, CAUSAL>(p, rank),
                                                                 (int)blockIdx.x, (int)threadIdx.x);
@@ -1261,13 +1262,19 @@ template <int D, bool CAUSAL, bool ALIBI, bool SOFTMAX = false>
 __global__ void __launch_bounds__(256, 1)
 attn_bwd_merged_kernel(const BwdParams p) {
   const int total = p.n_blocks * p.B * p.H;
-  const int logical = xcd_remap(blockIdx.x, 2 * total);
-  int bh, rank;
-  if (logical & 1) {
-    bwd_place<BWD_DQ, CAUSAL, false>(p, logical >> 1, p.n_blocks, bh, rank);
+  int bh, rank, pass;
+  if (p.cu_seqlens) {
+    packed_place(p.cu_seqlens, p.B, p.H, 2 * p.n_blocks, bh, rank);
+    pass = rank & 1;
+    rank >>= 1;
+  } else {
+    const int logical = xcd_remap(blockIdx.x, 2 * total);
+    pass = logical & 1;
+    bwd_place<BWD_DQ, CAUSAL, false>(p, logical >> 1, p.n_blocks, bh, rank);  // (the same for both passes)
+  }
+  if (pass) {
     attn_bwd_body<D, BWD_DQ, CAUSAL, ALIBI, SOFTMAX, true, false>(p, bh, bwd_block_of_rank<BWD_DQ, CAUSAL>(p, rank), (int)blockIdx.x, (int)threadIdx.x);
   } else {
-    bwd_place<BWD_DKDV, CAUSAL, false>(p, logical >> 1, p.n_blocks, bh, rank);
     attn_bwd_body<D, BWD_DKDV, CAUSAL, ALIBI, SOFTMAX, true, false>(p, bh, bwd_block_of_rank<BWD_DKDV, CAUSAL>(p, rank), (int)blockIdx.x, (int)threadIdx.x);
   }
 }

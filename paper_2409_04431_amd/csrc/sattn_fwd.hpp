@@ -604,9 +604,9 @@ attn_fwd_kernel(const FwdParams p) {
   ClockStart clk = clock_probe_begin(p.clock);
 
   const int total = p.n_qblocks * p.B * p.H;
-  const int logical = xcd_remap(blockIdx.x, total);
   int bh, rank;
-  head_and_rank(logical, p.n_qblocks, p.B * p.H, CAUSAL ? p.head_group : 1, bh, rank);
+  if (p.cu_seqlens) packed_place(p.cu_seqlens, p.B, p.H, p.n_qblocks, bh, rank);
+  else head_and_rank(xcd_remap(blockIdx.x, total), p.n_qblocks, p.B * p.H, CAUSAL ? p.head_group : 1, bh, rank);
   // causal: heavy (late) query blocks first
   const int qb = CAUSAL ? (p.n_qblocks - 1 - rank) : rank;
   const int b = bh / p.H, hd = bh % p.H;

@@ -517,9 +517,9 @@ __global__ void __launch_bounds__(256, 1)
 attn_fwd64_kernel(const FwdParams p) {
   // blocks of a head this launch deals out: pairs (longest with shortest, ...) or single blocks
   const int places = (CAUSAL && p.pair) ? p.n_qblocks / 2 : p.n_qblocks;
-  const int logical = xcd_remap(blockIdx.x, places * p.B * p.H);
   int bh, rank;
-  head_and_rank(logical, places, p.B * p.H, CAUSAL ? p.head_group : 1, bh, rank);
+  if (p.cu_seqlens) packed_place(p.cu_seqlens, p.B, p.H, places, bh, rank);
+  else head_and_rank(xcd_remap(blockIdx.x, places * p.B * p.H), places, p.B * p.H, CAUSAL ? p.head_group : 1, bh, rank);
   // Under the causal mask block q of a head visits q + 1 key tiles (in units of the block):
   // blocks n-1-r and r together visit n + 1 whatever r is.  Equal workgroups leave no ragged
   // end of the launch, and a compute unit pays the gap between two workgroups half as often.
