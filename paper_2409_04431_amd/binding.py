@@ -388,7 +388,8 @@ def sattn_set_fwd_v_slots(v_slots):
 
 
 def sattn_bwd_merged(B, H, N, causal=False):
-    """True if sigmoid_attn_bwd runs both passes of this bf16 self-attention problem as one grid."""
+    """True if sigmoid_attn_bwd runs both passes of this bf16 self-attention problem as one grid
+    (head dimension 128; at 64 the one grid is also used for somewhat larger problems)."""
     rc = load_library().sattn_bwd_merged(int(B), int(H), int(N), int(bool(causal)))
     _raise(min(rc, 0), "sattn_bwd_merged")
     return bool(rc)

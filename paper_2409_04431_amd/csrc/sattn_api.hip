@@ -213,15 +213,28 @@ FwdShape pick_fwd_shape(int B, int H, int N, int d, int causal, bool allow64 = t
 }
 
 // The two passes of the sigmoid backward as one grid (where the launcher has that form: both
-// passes asked for, self-attention, one K/V head per query head).  It pays while a pass alone
-// cannot fill the chip: measured 10-28 % faster below two workgroups per pass and compute unit
-// (three without the causal mask), equal within 1.5 % from there to 16, and 9 % slower on very
-// large grids (48 per unit, d = 64), where the two passes compete for the L2.
-bool pick_bwd_merged(int B, int H, int N, int causal) {
+// passes asked for, self-attention, one K/V head per query head).  It pays
+//  - while a pass alone cannot fill the chip: 10-28 % faster below two workgroups per pass and
+//    compute unit (three without the causal mask);
+//  - where two workgroups share a unit (d = 64, `two_per_cu`) up to six: B32 H12 N250 54.0 -> 48.9 us,
+//    B24 H16 N384 82.9 -> 74.8, causal B6 H16 N1024 86.1 -> 70.1; from eight on two launches are 1-3 %
+//    faster without the mask;
+//  - where the causal launches, which deal blocks out in pairs, would leave more than 4 % of their
+//    rounds of pairs empty (wgs / 2 not a multiple of the units): per unit 3 workgroups d 128 156 -> 133 us,
+//    5: 237 -> 216, 9: 655 -> 630, 15: 1077 -> 1057; at multiples two launches are 4-6 % faster
+//    (2: 85 / 90, 4: 170 / 176, 6: 250 / 264);
+//  - for packed sequences, whose blocks differ in length, up to six per unit, nine at d = 64 (wgs
+//    counts the longest length's blocks): B32 H12 50 .. 500 tokens causal d 128 206 -> 171 us, d 64
+//    101 -> 89; 24 sequences of up to 1600 (9.75 per unit) d 64 259 / 273.
+bool pick_bwd_merged(int B, int H, int N, int causal, bool two_per_cu, bool packed) {
   const int mode = g_bwd_merged.load(std::memory_order_relaxed);
   if (mode) return mode == 1;
-  const int64_t wgs = (int64_t)B * H * ((N + 127) / 128), cus = compute_units();
-  return wgs < (causal ? 2 : 3) * cus;
+  const int64_t nb = (N + 127) / 128, wgs = (int64_t)B * H * nb, cus = compute_units();
+  if (wgs < (causal ? 2 : 3) * cus || (two_per_cu && wgs <= 6 * cus)) return true;
+  if (packed) return wgs <= (two_per_cu ? 9 : 6) * cus;
+  if (!causal || nb % 2 != 0 || nb < 4) return false;
+  const int64_t pairs = wgs / 2, places = (pairs + cus - 1) / cus * cus;
+  return (places - pairs) * 25 > places;
 }
 
 // Workgroups over which the dK/dV pass splits the query heads of one K/V head (a power of two
@@ -500,7 +513,7 @@ int bwd_impl(const BwdArgs& a) {
     if (rc) return rc;
     p.nlse2 = nlse2; p.dvec = dvec; p.npad = npad;
   }
-  const bool merged = pick_bwd_merged(a.B, a.H, a.N, a.causal);
+  const bool merged = pick_bwd_merged(a.B, a.H, a.N, a.causal, a.d == 64 && !SOFTMAX, a.cu_seqlens != nullptr);
   int n_split = 1;
   if (a.group_split && !SOFTMAX && PIN && Hkv != a.H && !a.cu_seqlens && Nk == a.N && (a.parts & kBwdDkDv)) {
     n_split = pick_group_split(a.B, Hkv, a.H / Hkv, a.N, a.causal);
@@ -911,7 +924,7 @@ int sattn_set_fwd_waves(int waves) {
 
 int sattn_bwd_merged(int B, int H, int N, int causal) {
   if (B <= 0 || H <= 0 || N <= 0) return SATTN_ERR_SHAPE;
-  return pick_bwd_merged(B, H, N, causal) ? 1 : 0;
+  return pick_bwd_merged(B, H, N, causal, false, false) ? 1 : 0;
 }
 
 int sattn_set_bwd_merged(int mode) {

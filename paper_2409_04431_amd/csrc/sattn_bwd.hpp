@@ -1257,8 +1257,9 @@ attn_bwd_kernel(const BwdParams p) {
 // (head, block) place, each pass in its own heavy-first order.  The grid is one launch, so a
 // pass's last, ragged round of workgroups is filled by the other pass, and a head's two
 // passes run on the same XCD next to each other and share its L2.  (SOFTMAX: the comparison
-// kernel's two passes; its pre-pass stays a launch of its own.)
-template <int D, bool CAUSAL, bool ALIBI, bool SOFTMAX = false>
+// kernel's two passes; its pre-pass stays a launch of its own.  DB: the dQ pass also writes the row
+// sums of dS.)
+template <int D, bool CAUSAL, bool ALIBI, bool SOFTMAX = false, bool DB = false>
 __global__ void __launch_bounds__(256, 1)
 attn_bwd_merged_kernel(const BwdParams p) {
   const int total = p.n_blocks * p.B * p.H;
@@ -1273,7 +1274,7 @@ attn_bwd_merged_kernel(const BwdParams p) {
     bwd_place<BWD_DQ, CAUSAL, false>(p, logical >> 1, p.n_blocks, bh, rank);  // (the same for both passes)
   }
   if (pass) {
-    attn_bwd_body<D, BWD_DQ, CAUSAL, ALIBI, SOFTMAX, true, false>(p, bh, bwd_block_of_rank<BWD_DQ, CAUSAL>(p, rank), (int)blockIdx.x, (int)threadIdx.x);
+    attn_bwd_body<D, DB ? BWD_DQ_DB : BWD_DQ, CAUSAL, ALIBI, SOFTMAX, true, false>(p, bh, bwd_block_of_rank<BWD_DQ, CAUSAL>(p, rank), (int)blockIdx.x, (int)threadIdx.x);
   } else {
     attn_bwd_body<D, BWD_DKDV, CAUSAL, ALIBI, SOFTMAX, true, false>(p, bh, bwd_block_of_rank<BWD_DKDV, CAUSAL>(p, rank), (int)blockIdx.x, (int)threadIdx.x);
   }

@@ -22,11 +22,17 @@ int launch_bwd_variant(BwdParams p, int causal, bool alibi, int parts, bool merg
   if (p.kv_group > 1 && (SOFTMAX || !PIN)) return SATTN_ERR_UNSUPPORTED;  // only the product kernels share K/V heads
   if constexpr (PIN) {
     // self-attention with one K/V head per query head and both passes wanted: one grid
-    if (parts == (kBwdDkDv | kBwdDq) && p.kv_group == 1 && nb_q == nb_k && p.Nk == 0 && !p.db_rows && merged) {
+    if (parts == (kBwdDkDv | kBwdDq) && p.kv_group == 1 && nb_q == nb_k && p.Nk == 0 && merged) {
       p.n_blocks = nb_q;
       p.head_group = heads_abreast(nb_q);
       p.pair = 0;
       dim3 grid2(2 * nb_q * p.B * p.H);
+      if constexpr (!SOFTMAX) {
+        if (p.db_rows) {
+          SATTN_DISPATCH2(causal, alibi, rc = launch(attn_bwd_merged_kernel<D, A, B2, false, true>, grid2, block, lds, st, p));
+          return rc;
+        }
+      }
       SATTN_DISPATCH2(causal, alibi, rc = launch(attn_bwd_merged_kernel<D, A, B2, SOFTMAX>, grid2, block,
                                                  lds + (SOFTMAX ? 4 * StatStager::SLOT : 0), st, p));
       return rc;
