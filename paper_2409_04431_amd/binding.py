@@ -1,9 +1,13 @@
-"""ctypes binding of libsattn.so: argument marshalling only.
+"""Binding of libsattn.so: argument marshalling only.
 
 Every function mirrors the C entry point of the same name in include/sattn.h.  Tensors are
 torch CUDA tensors of shape [B, H, N, d] (any strides with a contiguous last dimension);
 PyTorch is used for device memory and the current stream, nothing else.  There is no CPU
 fallback: if the library cannot be loaded the call raises.
+
+The calls of a training or serving loop go through `_native` (csrc/binding_native.cpp), which does
+the checks and the marshalling in C++; it returns None for arguments that it does not take (anything
+but plain CUDA tensors of the expected form), and the ctypes path below it then raises or calls.
 """
 import ctypes
 import os
@@ -12,7 +16,9 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libsattn.so")
+_NATIVE_PATH = os.path.join(_HERE, "_native.so")
 _lib = None
+_native = None
 
 SATTN_BF16, SATTN_F32 = 0, 1
 
@@ -35,11 +41,12 @@ def library_path():
 
 def load_library():
     """Load libsattn.so (built by paper_2409_04431_amd.build / __graft_entry__.build)."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
-    if not os.path.exists(_LIB_PATH):
-        raise SattnError(f"{_LIB_PATH} is missing: build it first (python -m paper_2409_04431_amd.build)")
+    for path in (_LIB_PATH, _NATIVE_PATH):
+        if not os.path.exists(path):
+            raise SattnError(f"{path} is missing: build it first (python -m paper_2409_04431_amd.build)")
     lib = ctypes.CDLL(_LIB_PATH)
     i, f, sz = ctypes.c_int, ctypes.c_float, ctypes.c_size_t
     lib.sigmoid_attn_fwd.argtypes = [_vp, _vp, _vp, _vp, i, i, i, i, i, f, i, _vp, _SP, _SP, _SP, _SP, _vp]
@@ -127,7 +134,8 @@ def load_library():
     lib.sattn_device_info.restype = i
     lib.sattn_version.argtypes = []
     lib.sattn_version.restype = i
-    _lib = lib
+    from . import _native as native
+    _lib, _native = lib, native
     return lib
 
 
@@ -158,6 +166,10 @@ def sigmoid_attn_varlen_fwd(q, k, v, o, cu_seqlens, max_seqlen, bias, causal=Fal
                             bias_per_seq=None):
     """Forward over B packed sequences ([tokens, H, d] tensors, offsets in cu_seqlens)."""
     lib = load_library()
+    rc = _native.varlen_fwd(q, k, v, o, cu_seqlens, max_seqlen, bias_per_seq, bias, causal, alibi_slopes)
+    if rc is not None:
+        _raise(rc, "sigmoid_attn_varlen_fwd")
+        return o
     B = _check_varlen(cu_seqlens, bias_per_seq, q, k, v, o)
     _, H, d = q.shape
     bp = _vp(bias_per_seq.data_ptr()) if bias_per_seq is not None else None
@@ -173,6 +185,10 @@ def sigmoid_attn_varlen_bwd(q, k, v, dout, dq, dk, dv, cu_seqlens, max_seqlen, b
                             alibi_slopes=None, bias_per_seq=None):
     """Backward over B packed sequences ([tokens, H, d] tensors, offsets in cu_seqlens)."""
     lib = load_library()
+    rc = _native.varlen_bwd(q, k, v, dout, dq, dk, dv, cu_seqlens, max_seqlen, bias_per_seq, bias, causal, alibi_slopes)
+    if rc is not None:
+        _raise(rc, "sigmoid_attn_varlen_bwd")
+        return dq, dk, dv
     B = _check_varlen(cu_seqlens, bias_per_seq, q, k, v, dout, dq, dk, dv)
     _, H, d = q.shape
     bp = _vp(bias_per_seq.data_ptr()) if bias_per_seq is not None else None
@@ -189,6 +205,11 @@ def sigmoid_attn_varlen_bwd_bias_grad(q, k, v, dout, dq, dk, dv, db_rows, cu_seq
                                       alibi_slopes=None, bias_per_seq=None, db=None):
     """sigmoid_attn_varlen_bwd plus db_rows[h, t] = sum_j dS_tj (fp32 [H, tokens]) and, if given, db[b, h]."""
     lib = load_library()
+    rc = _native.varlen_bwd_bias_grad(q, k, v, dout, dq, dk, dv, cu_seqlens, max_seqlen, bias_per_seq, bias, causal,
+                                      alibi_slopes, db_rows, db)
+    if rc is not None:
+        _raise(rc, "sigmoid_attn_varlen_bwd_bias_grad")
+        return dq, dk, dv, db_rows, db
     B = _check_varlen(cu_seqlens, bias_per_seq, q, k, v, dout, dq, dk, dv)
     total, H, d = q.shape
     for t, shape, what in ((db_rows, (H, total), "db_rows"), (db, (B, H), "db")):
@@ -221,6 +242,10 @@ def _check_mqa(q, kv, *qlike):
 def sigmoid_attn_mqa_fwd(q, k, v, o, bias, causal=False, alibi_slopes=None):
     """Forward with shared K/V heads: q, o [B,H,N,d]; k, v [B,Hkv,N,d], Hkv divides H."""
     lib = load_library()
+    rc = _native.mqa_fwd(q, k, v, o, bias, causal, alibi_slopes)
+    if rc is not None:
+        _raise(rc, "sigmoid_attn_mqa_fwd")
+        return o
     B, H, Hkv, N, d = _check_mqa(q, (k, v), o)
     rc = lib.sigmoid_attn_mqa_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), B, H, Hkv, N, d,
                                   _dtype_code(q), float(bias), int(bool(causal)), _slopes_ptr(alibi_slopes, H),
@@ -251,6 +276,10 @@ def sigmoid_attn_mqa_bwd_split(q, k, v, dout, dq, dk, dv, bias, causal=False, al
     """sigmoid_attn_mqa_bwd with a group's query heads split over several workgroups where K/V heads are
     few (fp32 partial sums in `workspace`, allocated here when not given)."""
     lib = load_library()
+    rc = _native.mqa_bwd_split(q, k, v, dout, dq, dk, dv, bias, causal, alibi_slopes, workspace)
+    if rc is not None:
+        _raise(rc, "sigmoid_attn_mqa_bwd_split")
+        return dq, dk, dv
     B, H, Hkv, N, d = _check_mqa(q, (k, v, dk, dv), dout, dq)
     need = sigmoid_attn_mqa_bwd_workspace_bytes(B, H, Hkv, N, d, q.dtype, causal)
     if workspace is None and need:
@@ -276,6 +305,10 @@ def _check_stats(stats, B, N):
 def sattn_headconcat_norm_fwd(x, y, stats, kind="layer", eps=1e-5):
     """LayerNorm / RMSNorm of a [B,H,N,d] bf16 tensor over each token's H*d features; fills stats [B,N,2]."""
     lib = load_library()
+    rc = _native.norm_fwd(x, y, stats, _NORM_KINDS.get(kind), eps)
+    if rc is not None:
+        _raise(rc, "sattn_headconcat_norm_fwd")
+        return y, stats
     _check(x, y)
     B, H, N, d = x.shape
     _check_stats(stats, B, N)
@@ -288,6 +321,10 @@ def sattn_headconcat_norm_fwd(x, y, stats, kind="layer", eps=1e-5):
 def sattn_headconcat_norm_bwd(x, dy, stats, dx, kind="layer"):
     """Gradient of sattn_headconcat_norm_fwd with respect to x, from x, dy and the forward statistics."""
     lib = load_library()
+    rc = _native.norm_bwd(x, dy, dx, stats, _NORM_KINDS.get(kind))
+    if rc is not None:
+        _raise(rc, "sattn_headconcat_norm_bwd")
+        return dx
     _check(x, dy, dx)
     B, H, N, d = x.shape
     _check_stats(stats, B, N)
@@ -317,6 +354,10 @@ def sigmoid_attn_cross_aligned_fwd_split(q, k, v, o, bias, causal=False, alibi_s
     """sigmoid_attn_cross_aligned_fwd with the keys split over several workgroups where queries are few
     (fp32 partial outputs in `workspace`, allocated here when not given)."""
     lib = load_library()
+    rc = _native.cross_aligned_fwd_split(q, k, v, o, bias, causal, alibi_slopes, workspace)
+    if rc is not None:
+        _raise(rc, "sigmoid_attn_cross_aligned_fwd_split")
+        return o
     B, H, Nq, Nk, d = _check_cross(q, (k, v), o)
     code = _dtype_code(q)
     need = lib.sigmoid_attn_cross_aligned_fwd_workspace_bytes(B, H, Nq, Nk, d, code)
@@ -470,11 +511,13 @@ def _raise(rc, what):
 def sigmoid_attn_fwd(q, k, v, o, bias, causal=False, alibi_slopes=None, _entry="sigmoid_attn_fwd"):
     """O = sigmoid(Q K^T/sqrt(d) + bias [- slope|i-j|], causal mask) V, written into `o`."""
     lib = load_library()
-    _check(q, k, v, o)
-    B, H, N, d = q.shape
-    rc = getattr(lib, _entry)(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), B, H, N, d, _dtype_code(q),
-                              float(bias), int(bool(causal)), _slopes_ptr(alibi_slopes, H),
-                              _st(q), _st(k), _st(v), _st(o), _stream())
+    rc = _native.fwd(q, k, v, o, bias, causal, alibi_slopes) if _entry == "sigmoid_attn_fwd" else None
+    if rc is None:
+        _check(q, k, v, o)
+        B, H, N, d = q.shape
+        rc = getattr(lib, _entry)(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), B, H, N, d, _dtype_code(q),
+                                  float(bias), int(bool(causal)), _slopes_ptr(alibi_slopes, H),
+                                  _st(q), _st(k), _st(v), _st(o), _stream())
     _raise(rc, _entry)
     return o
 
@@ -493,6 +536,11 @@ def sigmoid_attn_bwd(q, k, v, dout, dq, dk, dv, bias, causal=False, alibi_slopes
                      _entry="sigmoid_attn_bwd"):
     """dQ, dK, dV of sigmoid attention from Q, K, V, dO (P is recomputed), written in place."""
     lib = load_library()
+    if workspace is None and _entry == "sigmoid_attn_bwd":
+        rc = _native.bwd(q, k, v, dout, dq, dk, dv, bias, causal, alibi_slopes)
+        if rc is not None:
+            _raise(rc, _entry)
+            return dq, dk, dv
     _check(q, k, v, dout, dq, dk, dv)
     B, H, N, d = q.shape
     need = sigmoid_attn_bwd_workspace_bytes(B, H, N, d, q.dtype)
@@ -511,6 +559,10 @@ def sigmoid_attn_bwd(q, k, v, dout, dq, dk, dv, bias, causal=False, alibi_slopes
 def sigmoid_attn_bwd_bias_grad(q, k, v, dout, dq, dk, dv, db_rows, bias, causal=False, alibi_slopes=None, db=None):
     """sigmoid_attn_bwd plus db_rows[b,h,i] = sum_j dS_ij (fp32 [B,H,N]) and, if given, db[b,h] = sum_i db_rows."""
     lib = load_library()
+    rc = _native.bwd_bias_grad(q, k, v, dout, dq, dk, dv, db_rows, db, bias, causal, alibi_slopes)
+    if rc is not None:
+        _raise(rc, "sigmoid_attn_bwd_bias_grad")
+        return dq, dk, dv, db_rows, db
     _check(q, k, v, dout, dq, dk, dv)
     B, H, N, d = q.shape
     for t, shape, what in ((db_rows, (B, H, N), "db_rows"), (db, (B, H), "db")):
