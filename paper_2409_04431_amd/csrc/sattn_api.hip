@@ -215,7 +215,9 @@ FwdShape pick_fwd_shape(int B, int H, int N, int d, int causal, bool allow64 = t
 // The two passes of the sigmoid backward as one grid (where the launcher has that form: both
 // passes asked for, self-attention, one K/V head per query head).  It pays
 //  - while a pass alone cannot fill the chip: 10-28 % faster below two workgroups per pass and
-//    compute unit (three without the causal mask);
+//    compute unit under the causal mask; without it (equal workgroups) below three, where the one
+//    grid takes fewer rounds than the two launches (per unit, d 128: 0.47 workgroups 18.7 -> 10.8 us,
+//    but 1.83: 36.2 / 39.0, 1: 67.1 / 69.2, 2: 132 / 134);
 //  - where two workgroups share a unit (d = 64, `two_per_cu`) up to six: B32 H12 N250 54.0 -> 48.9 us,
 //    B24 H16 N384 82.9 -> 74.8, causal B6 H16 N1024 86.1 -> 70.1; from eight on two launches are 1-3 %
 //    faster without the mask;
@@ -230,9 +232,11 @@ bool pick_bwd_merged(int B, int H, int N, int causal, bool two_per_cu, bool pack
   const int mode = g_bwd_merged.load(std::memory_order_relaxed);
   if (mode) return mode == 1;
   const int64_t nb = (N + 127) / 128, wgs = (int64_t)B * H * nb, cus = compute_units();
-  if (wgs < (causal ? 2 : 3) * cus || (two_per_cu && wgs <= 6 * cus)) return true;
   if (packed) return wgs <= (two_per_cu ? 9 : 6) * cus;
-  if (!causal || nb % 2 != 0 || nb < 4) return false;
+  if (two_per_cu && wgs <= 6 * cus) return true;
+  if (!causal || nb == 1) return wgs < 3 * cus && (2 * wgs + cus - 1) / cus < 2 * ((wgs + cus - 1) / cus);
+  if (wgs < 2 * cus) return true;
+  if (nb % 2 != 0 || nb < 4) return false;
   const int64_t pairs = wgs / 2, places = (pairs + cus - 1) / cus * cus;
   return (places - pairs) * 25 > places;
 }

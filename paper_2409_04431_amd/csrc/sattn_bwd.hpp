@@ -1214,10 +1214,13 @@ __device__ __forceinline__ int bwd_block_of_rank(const BwdParams& p, int rank) {
 // At d = 64 the ring takes 64 KB, so two workgroups fit a compute unit if the kernel stays within
 // 256 registers.  The compiler-scheduled forms (PIN = false) need that second wave per SIMD to
 // hide their schedule and sit right at the limit, so they are held to it; the pinned sigmoid forms
-// stay below it by themselves (138-156 VGPRs and 64 or 96 AGPRs; a launch bound would split the
-// file 128 + 128), the grouped dK/dV pass and the softmax one do not.
+// stay below it by themselves (138-156 VGPRs and 64 or 96 AGPRs).  The grouped dK/dV pass, with its
+// loop over query heads at 264-288, is held to it: the bound splits the file 128 + 128, which costs
+// 32-104 bytes of scratch in the set-up of a head, nothing in the pinned steps (dK/dV + dQ, us:
+// B7 H16 N5119 causal with one K/V head 2155 -> 1771, B3 H32 N3000 causal with four 707 -> 578).  The pinned
+// softmax pass stays above it.
 template <int D, int MODE, bool CAUSAL, bool ALIBI, bool SOFTMAX, bool PIN = true, bool GROUPS = false>
-__global__ void __launch_bounds__(256, ((D == 64 && !PIN) ? 2 : 1))
+__global__ void __launch_bounds__(256, ((D == 64 && (!PIN || GROUPS)) ? 2 : 1))
 attn_bwd_kernel(const BwdParams p) {
   const int kv_group = (MODE == BWD_DKDV && !GROUPS) ? 1 : p.kv_group;
   // Under the causal mask the r-th longest and the r-th shortest block of a head together stream

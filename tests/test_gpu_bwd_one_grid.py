@@ -14,6 +14,8 @@ def test_one_grid_where_the_paired_launches_leave_places_empty():
     assert not sa.sattn_bwd_merged(4, 16, 2048, True) and not sa.sattn_bwd_merged(64, 12, 2048, True)  # 4, 48
     assert not sa.sattn_bwd_merged(3, 16, 2176, True)     # 17 blocks per head: not dealt out in pairs
     assert not sa.sattn_bwd_merged(3, 16, 2048, False)
+    # equal workgroups: only where one grid takes fewer rounds
+    assert sa.sattn_bwd_merged(3, 16, 1024) and not sa.sattn_bwd_merged(4, 16, 1024) and not sa.sattn_bwd_merged(39, 12, 64, True)
 
 
 @pytest.mark.gpu
