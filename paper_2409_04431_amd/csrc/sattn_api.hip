@@ -246,10 +246,15 @@ bool pick_bwd_merged(int B, int H, int N, int causal, bool two_per_cu, bool pack
 // are few K/V heads -- with one K/V head, 8 sequences of 4096 tokens make 256 workgroups of
 // unequal causal work -- so the group is split until the pass has two workgroups per compute
 // unit under the causal mask (enough to deal the blocks out in pairs of equal work), one without.
-int pick_group_split(int B, int Hkv, int group, int N, int causal) {
+// At d = 64, where two workgroups share a unit, it is split once more if that leaves some units with
+// two (pairs of) workgroups and others with one: B7 H16 N5119 causal with one K/V head 1771 -> 1626 us,
+// B3 H32 N3000 with four 578 -> 544; with one on each, a second one gains nothing (B4 H16 N2048 with one
+// 166 / 168, B8 H32 N1024 with eight 187 / 190).
+int pick_group_split(int B, int Hkv, int group, int N, int d, int causal) {
   const int64_t wgs = (int64_t)B * Hkv * ((N + 127) / 128), want = (int64_t)(causal ? 2 : 1) * compute_units();
   int s = 1;
   while (wgs * s < want && group % (2 * s) == 0) s *= 2;
+  if (d == 64 && wgs * s > want && wgs * s < 2 * want && group % (2 * s) == 0) s *= 2;
   return s;
 }
 
@@ -520,9 +525,14 @@ int bwd_impl(const BwdArgs& a) {
   const bool merged = pick_bwd_merged(a.B, a.H, a.N, a.causal, a.d == 64 && !SOFTMAX, a.cu_seqlens != nullptr);
   int n_split = 1;
   if (a.group_split && !SOFTMAX && PIN && Hkv != a.H && !a.cu_seqlens && Nk == a.N && (a.parts & kBwdDkDv)) {
-    n_split = pick_group_split(a.B, Hkv, a.H / Hkv, a.N, a.causal);
+    n_split = pick_group_split(a.B, Hkv, a.H / Hkv, a.N, a.d, a.causal);
     if (n_split > 1) {
-      const size_t need = 2 * (size_t)n_split * a.B * Hkv * a.N * a.d * sizeof(float);
+      size_t need = 2 * (size_t)n_split * a.B * Hkv * a.N * a.d * sizeof(float);
+      const int fewer = pick_group_split(a.B, Hkv, a.H / Hkv, a.N, 128, a.causal);
+      if (fewer > 1 && fewer < n_split && a.workspace_bytes < need) {  // (room for the smaller split only)
+        need = need / n_split * fewer;
+        n_split = fewer;
+      }
       if (!a.workspace || a.workspace_bytes < need) return SATTN_ERR_WORKSPACE;
       if (((uintptr_t)a.workspace & 15) != 0) return SATTN_ERR_ALIGN;
       p.n_split = n_split;
@@ -817,7 +827,7 @@ int sigmoid_attn_mqa_bwd(const void* q, const void* k, const void* v, const void
 
 size_t sigmoid_attn_mqa_bwd_workspace_bytes(int B, int H, int Hkv, int N, int d, sattn_dtype dtype, int causal) {
   if (check_shape(B, H, N, d, dtype) != SATTN_OK || Hkv <= 0 || H % Hkv || Hkv == H || dtype != SATTN_BF16) return 0;
-  const int s = pick_group_split(B, Hkv, H / Hkv, N, causal);
+  const int s = pick_group_split(B, Hkv, H / Hkv, N, d, causal);
   return s > 1 ? 2 * (size_t)s * B * Hkv * N * d * sizeof(float) : 0;
 }
 

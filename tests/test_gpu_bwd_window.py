@@ -30,3 +30,28 @@ def test_dkdv_at_d64_matches_oracle(N, causal, alibi):
     for x, r in ((dk, rk), (dv, rv)):
         err = abs(x.double().cpu().numpy() - r).max() / max(abs(r).max(), 1e-12)
         assert err <= TOL, f"{err:.3e}"
+
+
+def test_shared_heads_at_d64_split_once_more_or_with_room_for_less():
+    # 3 x 17 key blocks: 8 workgroups a group make 408, more than one and fewer than two per compute unit
+    B, H, N, d = 3, 16, 2100, 64
+    if sa.sattn_device_info()[0] != 256:
+        pytest.skip("sizes chosen for 256 compute units")
+    g = torch.Generator(device="cuda").manual_seed(4)
+    q, do = (torch.randn(B, H, N, d, generator=g, device="cuda").bfloat16() for _ in range(2))
+    k, v = (torch.randn(B, 1, N, d, generator=g, device="cuda").bfloat16() for _ in range(2))
+    need = sa.sigmoid_attn_mqa_bwd_workspace_bytes(B, H, 1, N, d)
+    assert need == 2 * 16 * B * N * d * 4
+    out = []
+    for room in (need, need // 2):
+        ws = torch.full((room,), 255, dtype=torch.uint8, device="cuda")
+        out.append([torch.full_like(x, float("nan")) for x in (q, k, v)])
+        sa.sigmoid_attn_mqa_bwd_split(q, k, v, do, *out[-1], -math.log(N), workspace=ws)
+    ref = [torch.empty_like(x) for x in (q, k, v)]
+    sa.sigmoid_attn_mqa_bwd(q, k, v, do, *ref, -math.log(N))
+    with pytest.raises(sa.SattnError):
+        sa.sigmoid_attn_mqa_bwd_split(q, k, v, do, *out[0], -math.log(N), workspace=ws[: need // 2 - 16])
+    for got in out:
+        assert torch.equal(got[0], ref[0])
+        for x, r in zip(got[1:], ref[1:]):  # two bf16 roundings of sums in another order
+            assert ((x.double() - r.double()).abs().amax(-1) / r.double().abs().amax(-1)).max() <= 2 ** -7
