@@ -560,12 +560,14 @@ template <bool RMS, bool BACKWARD>
 int launch_norm(const NormParams& p, hipStream_t st) {
   const int nchunks = p.H * (p.d / 8);
   const int64_t tokens = (int64_t)p.B * p.N;
-  dim3 grid((unsigned)((tokens + 3) / 4)), block(256);
-  if (nchunks <= 64) return launch(headconcat_norm_kernel<1, RMS, BACKWARD>, grid, block, 0, st, p);
-  if (nchunks <= 128) return launch(headconcat_norm_kernel<2, RMS, BACKWARD>, grid, block, 0, st, p);
-  if (nchunks <= 256) return launch(headconcat_norm_kernel<4, RMS, BACKWARD>, grid, block, 0, st, p);
-  if (nchunks <= 512) return launch(headconcat_norm_kernel<8, RMS, BACKWARD>, grid, block, 0, st, p);
-  return launch(headconcat_norm_kernel<16, RMS, BACKWARD>, grid, block, 0, st, p);
+  dim3 grid((unsigned)((tokens + 3) / 4)), grid2((unsigned)((tokens + 7) / 8)), grid4((unsigned)((tokens + 15) / 16)), block(256);
+  if (nchunks <= 16) return launch(headconcat_norm_kernel<1, 16, RMS, BACKWARD>, grid4, block, 0, st, p);
+  if (nchunks <= 32) return launch(headconcat_norm_kernel<1, 32, RMS, BACKWARD>, grid2, block, 0, st, p);
+  if (nchunks <= 64) return launch(headconcat_norm_kernel<1, 64, RMS, BACKWARD>, grid, block, 0, st, p);
+  if (nchunks <= 128) return launch(headconcat_norm_kernel<2, 64, RMS, BACKWARD>, grid, block, 0, st, p);
+  if (nchunks <= 256) return launch(headconcat_norm_kernel<4, 64, RMS, BACKWARD>, grid, block, 0, st, p);
+  if (nchunks <= 512) return launch(headconcat_norm_kernel<8, 64, RMS, BACKWARD>, grid, block, 0, st, p);
+  return launch(headconcat_norm_kernel<16, 64, RMS, BACKWARD>, grid, block, 0, st, p);
 }
 
 int norm_impl(bool backward, const void* x, const void* dy, void* out, float* stats, int B, int H, int N, int d,
