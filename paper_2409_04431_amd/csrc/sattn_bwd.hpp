@@ -66,6 +66,8 @@ struct BwdParams {
   // causal passes: every workgroup handles two blocks of its head, the r-th longest and the r-th
   // shortest (n_blocks even), so that all workgroups of a launch do the same work
   int pair;
+  // one grid with both passes: all dK/dV places before the dQ places instead of alternating with them
+  int in_turn;
   ClockProbe clock;  // measurement aid, {nullptr, 0} otherwise
 };
 
@@ -1257,7 +1259,8 @@ attn_bwd_kernel(const BwdParams p) {
 
 // Both passes of the pinned backward in one grid (self-attention, one K/V head per query
 // head): even places run the dK/dV workgroup, odd places the dQ workgroup of the same
-// (head, block) place, each pass in its own heavy-first order.  The grid is one launch, so a
+// (head, block) place, each pass in its own heavy-first order; or (p.in_turn) the dK/dV workgroups,
+// which take longer, all come first.  The grid is one launch, so a
 // pass's last, ragged round of workgroups is filled by the other pass, and a head's two
 // passes run on the same XCD next to each other and share its L2.  (SOFTMAX: the comparison
 // kernel's two passes; its pre-pass stays a launch of its own.  DB: the dQ pass also writes the row
@@ -1272,9 +1275,16 @@ attn_bwd_merged_kernel(const BwdParams p) {
     pass = rank & 1;
     rank >>= 1;
   } else {
-    const int logical = xcd_remap(blockIdx.x, 2 * total);
-    pass = logical & 1;
-    bwd_place<BWD_DQ, CAUSAL, false>(p, logical >> 1, p.n_blocks, bh, rank);  // (the same for both passes)
+    int place;
+    if (p.in_turn) {
+      pass = (int)blockIdx.x >= total;
+      place = xcd_remap((int)blockIdx.x - pass * total, total);
+    } else {
+      const int logical = xcd_remap(blockIdx.x, 2 * total);
+      pass = logical & 1;
+      place = logical >> 1;
+    }
+    bwd_place<BWD_DQ, CAUSAL, false>(p, place, p.n_blocks, bh, rank);  // (the same for both passes)
   }
   if (pass) {
     attn_bwd_body<D, DB ? BWD_DQ_DB : BWD_DQ, CAUSAL, ALIBI, SOFTMAX, true, false>(p, bh, bwd_block_of_rank<BWD_DQ, CAUSAL>(p, rank), (int)blockIdx.x, (int)threadIdx.x);

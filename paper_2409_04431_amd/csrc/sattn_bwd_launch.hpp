@@ -26,6 +26,12 @@ int launch_bwd_variant(BwdParams p, int causal, bool alibi, int parts, bool merg
       p.n_blocks = nb_q;
       p.head_group = heads_abreast(nb_q);
       p.pair = 0;
+      // Equal workgroups (no mask) and short causal heads: the longer pass first, so that what runs
+      // last is short (us, alternating / in turn: B4 H12 N1024 d64 61.5 / 58.8, B3 H16 N1024 d128 101 / 96,
+      // causal B6 H16 N1024 d128 132 / 122, B2 H24 N700 d64 33.6 / 29.8).  Longer causal heads alternate: a
+      // head's late query blocks and early key blocks both run long, and next to each other on one
+      // XCD (causal B1 H16 N2048 d64 46 / 55, B3 H12 N4096 d128 537 / 542; B6 H16 N1024 d64 70 / 72).
+      p.in_turn = !causal || nb_q <= (D == 64 ? 6 : 8);
       dim3 grid2(2 * nb_q * p.B * p.H);
       if constexpr (!SOFTMAX) {
         if (p.db_rows) {
