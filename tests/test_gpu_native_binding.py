@@ -99,3 +99,47 @@ def test_native_half_takes_no_cpu_tensor_and_no_other_object():
     assert binding._native.fwd(1, x, None, "y", 0.0, False, None) is None
     with pytest.raises(TypeError):
         binding._native.fwd(x)
+
+
+@pytest.mark.gpu
+def test_calls_on_a_side_stream_and_under_capture():
+    """The calls go to torch's current stream: captured there, every replay gives the eager result."""
+    B, H, N, d = 2, 12, 333, 64
+    g = torch.Generator(device="cuda").manual_seed(9)
+    q, k, v, do = (torch.randn(B, H, N, d, generator=g, device="cuda").bfloat16() for _ in range(4))
+    kl, vl = (torch.randn(B, H, 1200, d, generator=g, device="cuda").bfloat16() for _ in range(2))
+    pk = [torch.randn(N, H, d, generator=g, device="cuda").bfloat16() for _ in range(4)]
+    cu = torch.tensor([0, 100, N], dtype=torch.int32, device="cuda")
+    e, f = torch.empty_like, lambda *s: torch.empty(*s, device="cuda")
+    out = [e(q), e(q), e(q), e(q), e(q[:, :, :1]), e(q), f(B, N, 2)] + [e(x) for x in pk[:3]] + [f(B, H, N), f(B, H)]
+
+    def work():
+        o, dq, dk, dv, o1, y, st, pq, pk_, pv, rows, db = out
+        sa.sigmoid_attn_fwd(q, k, v, o, -5.0, True)
+        sa.sigmoid_attn_bwd_bias_grad(q, k, v, do, dq, dk, dv, rows, -5.0, True, db=db)
+        sa.sigmoid_attn_cross_aligned_fwd(q[:, :, :1], kl, vl, o1, -7.0)   # takes a workspace
+        sa.sattn_headconcat_norm_fwd(o, y, st)
+        sa.sigmoid_attn_varlen_bwd(*pk, pq, pk_, pv, cu, 233, -5.0)
+
+    work()
+    torch.cuda.synchronize()
+    want = [x.clone() for x in out]
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        for x in out:
+            x.zero_()
+        work()
+    side.synchronize()
+    assert all(torch.equal(x, y) for x, y in zip(out, want))
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        work()
+    for _ in range(3):
+        for x in out:
+            x.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(x, y) for x, y in zip(out, want))
+        q.copy_(q.flip(0).contiguous())  # eager work between the replays, undone at once
+        q.copy_(q.flip(0).contiguous())
