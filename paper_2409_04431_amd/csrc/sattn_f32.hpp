@@ -100,12 +100,14 @@ struct F32Seq {
 template <int D>
 constexpr size_t f32_lds_bytes(int nw) { return sizeof(float) * (nw * 32 * (D + 4) + nw * 32); }
 
-// 1 / (1 + exp(-x)) with full fp32 precision.  The exponential is capped at 2^126 so that the
-// refinement stays finite; the result is then below the smallest normal number times two.
+// 1 / (1 + exp(-x)) with full fp32 precision.  The refinement needs a finite denominator with a normal
+// reciprocal; above 2^126, infinity among it, the result (below the smallest normal number) is
+// zero.  A NaN fails the comparison and comes out of the refinement as one.
 __device__ __forceinline__ float f32_sigmoid(float x) {
-  const float q = 1.0f + __builtin_fminf(expf(-x), 0x1p126f);
+  const float q = 1.0f + expf(-x);
   const float r = __builtin_amdgcn_rcpf(q);
-  return __builtin_fmaf(__builtin_fmaf(-q, r, 1.0f), r, r);
+  const float p = __builtin_fmaf(__builtin_fmaf(-q, r, 1.0f), r, r);
+  return q > 0x1p126f ? 0.f : p;
 }
 
 // One block of 32 stationary rows: `bh` counts (batch, query head), in the dK/dV pass (batch, K/V
