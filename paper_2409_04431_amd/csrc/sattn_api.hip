@@ -527,16 +527,18 @@ int bwd_impl(const BwdArgs& a) {
   if (a.group_split && !SOFTMAX && PIN && Hkv != a.H && !a.cu_seqlens && Nk == a.N && (a.parts & kBwdDkDv)) {
     n_split = pick_group_split(a.B, Hkv, a.H / Hkv, a.N, a.d, a.causal);
     if (n_split > 1) {
-      size_t need = 2 * (size_t)n_split * a.B * Hkv * a.N * a.d * sizeof(float);
+      const size_t one = 2 * (size_t)a.B * Hkv * a.N * a.d * sizeof(float);  // fp32 dK, dV of one split
+      const bool room = a.workspace && a.workspace_bytes >= one * n_split, aligned = ((uintptr_t)a.workspace & 15) == 0;
+      // The further split of d = 64 is taken only where the workspace serves it: what the rule of d = 128
+      // asks for is enough, nothing where that does not split.
       const int fewer = pick_group_split(a.B, Hkv, a.H / Hkv, a.N, 128, a.causal);
-      if (fewer > 1 && fewer < n_split && a.workspace_bytes < need) {  // (room for the smaller split only)
-        need = need / n_split * fewer;
-        n_split = fewer;
+      if (!room || !aligned) n_split = fewer;
+      if (n_split > 1) {
+        if (!a.workspace || a.workspace_bytes < one * n_split) return SATTN_ERR_WORKSPACE;
+        if (!aligned) return SATTN_ERR_ALIGN;
+        p.n_split = n_split;
+        p.part = (float*)a.workspace;
       }
-      if (!a.workspace || a.workspace_bytes < need) return SATTN_ERR_WORKSPACE;
-      if (((uintptr_t)a.workspace & 15) != 0) return SATTN_ERR_ALIGN;
-      p.n_split = n_split;
-      p.part = (float*)a.workspace;
     }
   }
   // causal passes deal a head's blocks out in pairs of equal work (longest with shortest) where

@@ -55,3 +55,26 @@ def test_shared_heads_at_d64_split_once_more_or_with_room_for_less():
         assert torch.equal(got[0], ref[0])
         for x, r in zip(got[1:], ref[1:]):  # two bf16 roundings of sums in another order
             assert ((x.double() - r.double()).abs().amax(-1) / r.double().abs().amax(-1)).max() <= 2 ** -7
+
+
+@pytest.mark.parametrize("B,Hkv,N,causal", [
+    (33, 16, 100, True),    # 528 blocks: more than two per compute unit, so only the further split would take a workspace
+    (17, 16, 65, False),    # 272: the same without the mask
+])
+def test_shared_heads_at_d64_without_room_run_unsplit_where_only_the_further_split_asks_for_it(B, Hkv, N, causal):
+    if sa.sattn_device_info()[0] != 256:
+        pytest.skip("sizes chosen for 256 compute units")
+    H, d = 2 * Hkv, 64
+    g = torch.Generator(device="cuda").manual_seed(6)
+    q, do = (torch.randn(B, H, N, d, generator=g, device="cuda").bfloat16() for _ in range(2))
+    k, v = (torch.randn(B, Hkv, N, d, generator=g, device="cuda").bfloat16() for _ in range(2))
+    need = sa.sigmoid_attn_mqa_bwd_workspace_bytes(B, H, Hkv, N, d, causal=causal)
+    assert need == 2 * 2 * B * Hkv * N * d * 4
+    ref = [torch.empty_like(x) for x in (q, k, v)]
+    sa.sigmoid_attn_mqa_bwd(q, k, v, do, *ref, -math.log(N), causal)
+    for ws in (torch.empty(0, dtype=torch.uint8, device="cuda"), torch.empty(need - 16, dtype=torch.uint8, device="cuda"),
+               torch.empty(need + 4, dtype=torch.uint8, device="cuda")[4:]):  # none, too little, misaligned
+        got = [torch.full_like(x, float("nan")) for x in (q, k, v)]
+        sa.sigmoid_attn_mqa_bwd_split(q, k, v, do, *got, -math.log(N), causal, workspace=ws)
+        for x, r in zip(got, ref):
+            assert torch.equal(x, r)
