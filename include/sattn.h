@@ -22,6 +22,7 @@
  * Conventions for every entry point
  *  - All tensor pointers are DEVICE pointers.  The caller owns every buffer; the library
  *    never allocates, frees or keeps device memory.
+ *  - dq of a backward pass may be q or dout itself (same pointer and strides).
  *  - Tensors are [B, H, N, d] with the last dimension contiguous.  A NULL strides pointer
  *    means fully contiguous [B, H, N, d]; otherwise strides are in ELEMENTS and must be
  *    multiples of 8 (bf16) or 4 (f32) so that rows stay 16-byte aligned.  Base pointers

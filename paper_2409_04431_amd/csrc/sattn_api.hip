@@ -409,9 +409,9 @@ int fwd_impl(const FwdArgs& a) {
 
 // ---------------------------------------------------------------- backward
 template <int D>
-int launch_bwd_f32(const F32Params& p, int causal, bool alibi, int parts, hipStream_t st) {
+int launch_bwd_f32(const F32Params& p, int causal, bool alibi, int parts, bool one_grid, hipStream_t st) {
   // the dQ pass runs one workgroup per query head and 32 queries, the dK/dV pass one per K/V
-  // head and 32 keys
+  // head and 32 keys; without `one_grid` after one another
   const int nb_q = (p.N + 31) / 32, nb_k = ((p.Nk > 0 ? p.Nk : p.N) + 31) / 32;
   const int heads_q = p.B * p.H, heads_k = p.B * (p.H / p.kv_group);
   const int64_t wgs = (int64_t)nb_q * heads_q + (int64_t)nb_k * heads_k;
@@ -421,6 +421,10 @@ int launch_bwd_f32(const F32Params& p, int causal, bool alibi, int parts, hipStr
   if (parts == kBwdDkDv) return launch_f32_pass<D, F32_DKDV>(p, nb_k, heads_k, waves, causal, alibi, st);
   if (parts == kBwdDq) return launch_f32_pass<D, F32_DQ>(p, nb_q, heads_q, waves, causal, alibi, st);
   int rc = SATTN_OK;
+  if (!one_grid) {
+    rc = launch_f32_pass<D, F32_DKDV>(p, nb_k, heads_k, waves, causal, alibi, st);
+    return rc == SATTN_OK ? launch_f32_pass<D, F32_DQ>(p, nb_q, heads_q, waves, causal, alibi, st) : rc;
+  }
   if (waves == 8)
     SATTN_DISPATCH2(causal, alibi, rc = launch(sigmoid_f32_bwd_kernel<D, A, B2, 8>, dim3((unsigned)wgs), dim3(512),
                                                f32_lds_bytes<D>(8), st, p, nb_k, nb_q, cus));
@@ -465,6 +469,9 @@ int bwd_impl(const BwdArgs& a) {
   hipStream_t st = (hipStream_t)a.stream;
   const bool alibi = a.slopes != nullptr;
   const float inv_sqrt_d = 1.0f / sqrtf((float)a.d);
+  // dQ may replace Q or dO: a workgroup of the dQ pass reads only its own rows of them, but the
+  // dK/dV pass reads all rows and has to be through before
+  const bool in_place = (a.parts & kBwdDq) && (a.dq == a.q || a.dq == a.dout);
   if (a.dtype == SATTN_F32) {
     if (SOFTMAX || !PIN) return SATTN_ERR_UNSUPPORTED;  // comparison kernels and twins: bf16 only
     F32Params p{};
@@ -477,8 +484,8 @@ int bwd_impl(const BwdArgs& a) {
     p.qoff = a.end_aligned ? Nk - a.N : 0;
     p.db_rows = a.db_rows; p.db_sb = (int64_t)a.H * a.N; p.db_sh = a.N;
     if (a.cu_seqlens && a.db_rows) { p.db_sb = 0; p.db_sh = a.db_tokens; }  // [H, tokens], as in the bf16 path
-    if (a.d == 128) rc = launch_bwd_f32<128>(p, a.causal, alibi, a.parts, st);
-    else rc = launch_bwd_f32<64>(p, a.causal, alibi, a.parts, st);
+    if (a.d == 128) rc = launch_bwd_f32<128>(p, a.causal, alibi, a.parts, !in_place, st);
+    else rc = launch_bwd_f32<64>(p, a.causal, alibi, a.parts, !in_place, st);
     if (rc == SATTN_OK && a.db) {
       if (a.cu_seqlens)
         rc = launch(rowsum_reduce_varlen_kernel, dim3(a.B * a.H), dim3(256), 0, st, (const float*)a.db_rows, a.db,
@@ -522,7 +529,7 @@ int bwd_impl(const BwdArgs& a) {
     if (rc) return rc;
     p.nlse2 = nlse2; p.dvec = dvec; p.npad = npad;
   }
-  const bool merged = pick_bwd_merged(a.B, a.H, a.N, a.causal, a.d == 64 && !SOFTMAX, a.cu_seqlens != nullptr);
+  const bool merged = !in_place && pick_bwd_merged(a.B, a.H, a.N, a.causal, a.d == 64 && !SOFTMAX, a.cu_seqlens != nullptr);
   int n_split = 1;
   if (a.group_split && !SOFTMAX && PIN && Hkv != a.H && !a.cu_seqlens && Nk == a.N && (a.parts & kBwdDkDv)) {
     n_split = pick_group_split(a.B, Hkv, a.H / Hkv, a.N, a.d, a.causal);
