@@ -272,18 +272,30 @@ int check_shape(int B, int H, int N, int d, sattn_dtype dt) {
 // workgroup (half the chunks per wave), four otherwise (two workgroups per compute unit).
 int f32_waves(int64_t wgs, int cus) { return wgs <= cus ? 8 : 4; }
 
+// Runs `one(first workgroup, grid)` for a grid of `wgs` workgroups: the runtime counts the work-items
+// of a launch in 32 bits, which packed batches with a large max_seqlen exceed (their workgroups
+// beyond a sequence's end return at once).
+template <typename Launch>
+int launch_f32_grid(int64_t wgs, int threads, Launch one) {
+  const int64_t most = ((int64_t)1 << 31) / threads;
+  for (int64_t first = 0; first < wgs; first += most)
+    if (int rc = one((int)first, dim3((unsigned)std::min(most, wgs - first)))) return rc;
+  return SATTN_OK;
+}
+
 template <int D, int MODE>
 int launch_f32_pass(const F32Params& p, int nb, int heads, int waves, int causal, bool alibi, hipStream_t st) {
-  const int64_t wgs = (int64_t)nb * heads;
   const int cus = compute_units();
-  int rc = SATTN_OK;
-  if (waves == 8)
-    SATTN_DISPATCH2(causal, alibi, rc = launch(sigmoid_f32_kernel<D, MODE, A, B2, 8>, dim3((unsigned)wgs), dim3(512),
-                                               f32_lds_bytes<D>(8), st, p, nb, heads, cus));
-  else
-    SATTN_DISPATCH2(causal, alibi, rc = launch(sigmoid_f32_kernel<D, MODE, A, B2, 4>, dim3((unsigned)wgs), dim3(256),
-                                               f32_lds_bytes<D>(4), st, p, nb, heads, cus));
-  return rc;
+  return launch_f32_grid((int64_t)nb * heads, 64 * waves, [&](int first, dim3 grid) {
+    int rc = SATTN_OK;
+    if (waves == 8)
+      SATTN_DISPATCH2(causal, alibi, rc = launch(sigmoid_f32_kernel<D, MODE, A, B2, 8>, grid, dim3(512), f32_lds_bytes<D>(8),
+                                                 st, p, nb, heads, cus, first));
+    else
+      SATTN_DISPATCH2(causal, alibi, rc = launch(sigmoid_f32_kernel<D, MODE, A, B2, 4>, grid, dim3(256), f32_lds_bytes<D>(4),
+                                                 st, p, nb, heads, cus, first));
+    return rc;
+  });
 }
 
 template <int D>
@@ -420,18 +432,20 @@ int launch_bwd_f32(const F32Params& p, int causal, bool alibi, int parts, bool o
   const int waves = f32_waves(wgs, cus);  // the same for a pass alone: its sums then run in the same order
   if (parts == kBwdDkDv) return launch_f32_pass<D, F32_DKDV>(p, nb_k, heads_k, waves, causal, alibi, st);
   if (parts == kBwdDq) return launch_f32_pass<D, F32_DQ>(p, nb_q, heads_q, waves, causal, alibi, st);
-  int rc = SATTN_OK;
   if (!one_grid) {
-    rc = launch_f32_pass<D, F32_DKDV>(p, nb_k, heads_k, waves, causal, alibi, st);
+    const int rc = launch_f32_pass<D, F32_DKDV>(p, nb_k, heads_k, waves, causal, alibi, st);
     return rc == SATTN_OK ? launch_f32_pass<D, F32_DQ>(p, nb_q, heads_q, waves, causal, alibi, st) : rc;
   }
-  if (waves == 8)
-    SATTN_DISPATCH2(causal, alibi, rc = launch(sigmoid_f32_bwd_kernel<D, A, B2, 8>, dim3((unsigned)wgs), dim3(512),
-                                               f32_lds_bytes<D>(8), st, p, nb_k, nb_q, cus));
-  else
-    SATTN_DISPATCH2(causal, alibi, rc = launch(sigmoid_f32_bwd_kernel<D, A, B2, 4>, dim3((unsigned)wgs), dim3(256),
-                                               f32_lds_bytes<D>(4), st, p, nb_k, nb_q, cus));
-  return rc;
+  return launch_f32_grid(wgs, 64 * waves, [&](int first, dim3 grid) {
+    int rc = SATTN_OK;
+    if (waves == 8)
+      SATTN_DISPATCH2(causal, alibi, rc = launch(sigmoid_f32_bwd_kernel<D, A, B2, 8>, grid, dim3(512), f32_lds_bytes<D>(8), st,
+                                                 p, nb_k, nb_q, cus, first));
+    else
+      SATTN_DISPATCH2(causal, alibi, rc = launch(sigmoid_f32_bwd_kernel<D, A, B2, 4>, grid, dim3(256), f32_lds_bytes<D>(4), st,
+                                                 p, nb_k, nb_q, cus, first));
+    return rc;
+  });
 }
 
 struct BwdArgs {

@@ -378,12 +378,13 @@ __device__ __forceinline__ void f32_place(int wg, int n_blocks, int n_heads, int
   blk = MODE != F32_DKDV ? n_blocks - 1 - rank : rank;
 }
 
+// One pass.  `first`: the number of the launch's first workgroup, where the grid takes several launches.
 template <int D, int MODE, bool CAUSAL, bool ALIBI, int NW>
 __global__ void __launch_bounds__(64 * NW, 2)
-sigmoid_f32_kernel(const F32Params p, int n_blocks, int n_heads, int cus) {
+sigmoid_f32_kernel(const F32Params p, int n_blocks, int n_heads, int cus, int first) {
   extern __shared__ __attribute__((aligned(16))) float smem_f32[];
   int bh, blk;
-  f32_place<MODE, CAUSAL>(blockIdx.x, n_blocks, n_heads, cus, bh, blk);
+  f32_place<MODE, CAUSAL>(first + (int)blockIdx.x, n_blocks, n_heads, cus, bh, blk);
   f32_block<D, MODE, CAUSAL, ALIBI, NW>(p, bh, blk, smem_f32);
 }
 
@@ -391,15 +392,15 @@ sigmoid_f32_kernel(const F32Params p, int n_blocks, int n_heads, int cus) {
 // compute units as the former run out.
 template <int D, bool CAUSAL, bool ALIBI, int NW>
 __global__ void __launch_bounds__(64 * NW, 2)
-sigmoid_f32_bwd_kernel(const F32Params p, int nb_k, int nb_q, int cus) {
+sigmoid_f32_bwd_kernel(const F32Params p, int nb_k, int nb_q, int cus, int first) {
   extern __shared__ __attribute__((aligned(16))) float smem_f32[];
-  const int heads_k = p.B * (p.H / p.kv_group), heads_q = p.B * p.H, n_k = nb_k * heads_k;
+  const int heads_k = p.B * (p.H / p.kv_group), heads_q = p.B * p.H, n_k = nb_k * heads_k, wg = first + (int)blockIdx.x;
   int bh, blk;
-  if ((int)blockIdx.x < n_k) {
-    f32_place<F32_DKDV, CAUSAL>(blockIdx.x, nb_k, heads_k, cus, bh, blk);
+  if (wg < n_k) {
+    f32_place<F32_DKDV, CAUSAL>(wg, nb_k, heads_k, cus, bh, blk);
     f32_block<D, F32_DKDV, CAUSAL, ALIBI, NW>(p, bh, blk, smem_f32);
   } else {
-    f32_place<F32_DQ, CAUSAL>((int)blockIdx.x - n_k, nb_q, heads_q, nb_q * heads_q, bh, blk);
+    f32_place<F32_DQ, CAUSAL>(wg - n_k, nb_q, heads_q, nb_q * heads_q, bh, blk);
     f32_block<D, F32_DQ, CAUSAL, ALIBI, NW>(p, bh, blk, smem_f32);
   }
 }
