@@ -353,10 +353,15 @@ def sigmoid_attn_cross_aligned_fwd_workspace_bytes(B, H, Nq, Nk, d, dtype=torch.
 def sigmoid_attn_cross_aligned_fwd_split(q, k, v, o, bias, causal=False, alibi_slopes=None, workspace=None):
     """sigmoid_attn_cross_aligned_fwd with the keys split over several workgroups where queries are few
     (fp32 partial outputs in `workspace`, allocated here when not given)."""
+    return _cross_fwd("sigmoid_attn_cross_aligned_fwd_split", q, k, v, o, bias, causal, alibi_slopes, workspace)
+
+
+def _cross_fwd(what, q, k, v, o, bias, causal=False, alibi_slopes=None, workspace=None):
+    """The entry point with a workspace on behalf of the function `what`, whose name errors carry."""
     lib = load_library()
     rc = _native.cross_aligned_fwd_split(q, k, v, o, bias, causal, alibi_slopes, workspace)
     if rc is not None:
-        _raise(rc, "sigmoid_attn_cross_aligned_fwd_split")
+        _raise(rc, what)
         return o
     B, H, Nq, Nk, d = _check_cross(q, (k, v), o)
     code = _dtype_code(q)
@@ -368,14 +373,14 @@ def sigmoid_attn_cross_aligned_fwd_split(q, k, v, o, bias, causal=False, alibi_s
     rc = lib.sigmoid_attn_cross_aligned_fwd_split(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), B, H, Nq, Nk, d,
                                                   code, float(bias), int(bool(causal)), _slopes_ptr(alibi_slopes, H),
                                                   _st(q), _st(k), _st(v), _st(o), wp, wb, _stream())
-    _raise(rc, "sigmoid_attn_cross_aligned_fwd_split")
+    _raise(rc, what)
     return o
 
 
 def sigmoid_attn_cross_fwd(q, k, v, o, bias):
     """Plain sigmoid attention with Nq queries and Nk keys: q, o [B,H,Nq,d]; k, v [B,H,Nk,d]."""
     # (positions do not matter without a mask and ALiBi)
-    return sigmoid_attn_cross_aligned_fwd_split(q, k, v, o, bias)
+    return _cross_fwd("sigmoid_attn_cross_fwd", q, k, v, o, bias)
 
 
 def sigmoid_attn_cross_bwd(q, k, v, dout, dq, dk, dv, bias):
@@ -392,7 +397,7 @@ def sigmoid_attn_cross_bwd(q, k, v, dout, dq, dk, dv, bias):
 def sigmoid_attn_cross_aligned_fwd(q, k, v, o, bias, causal=False, alibi_slopes=None):
     """Sigmoid attention of Nq queries placed at the end of an Nk-key sequence (query i at position
     i + Nk - Nq), with the causal mask and ALiBi of that placement: q, o [B,H,Nq,d]; k, v [B,H,Nk,d]."""
-    return sigmoid_attn_cross_aligned_fwd_split(q, k, v, o, bias, causal, alibi_slopes)
+    return _cross_fwd("sigmoid_attn_cross_aligned_fwd", q, k, v, o, bias, causal, alibi_slopes)
 
 
 def sigmoid_attn_cross_aligned_bwd(q, k, v, dout, dq, dk, dv, bias, causal=False, alibi_slopes=None):

@@ -49,3 +49,14 @@ def test_few_queries_match_oracle(B, H, Nq, Nk, d, causal, alibi, split):
     if need:
         with pytest.raises(sa.SattnError):
             sa.sigmoid_attn_cross_aligned_fwd_split(Q, K, V, o1, bias, causal, sl, workspace=ws[:-1])
+
+
+def test_errors_name_the_function_that_was_called():
+    q, k = (torch.zeros(1, 2, n, 64, device="cuda", dtype=torch.bfloat16) for n in (16, 90))
+    small = [x[..., :32].contiguous() for x in (q, k)]
+    for call, name in ((lambda: sa.sigmoid_attn_cross_fwd(small[0], small[1], small[1], small[0].clone(), 0.0), "sigmoid_attn_cross_fwd"),
+                       (lambda: sa.sigmoid_attn_cross_aligned_fwd(q, k, k, q.clone(), 0.0, True), "sigmoid_attn_cross_aligned_fwd"),
+                       (lambda: sa.sigmoid_attn_cross_aligned_fwd_split(q, k, k, q.clone(), 0.0, True),
+                        "sigmoid_attn_cross_aligned_fwd_split")):
+        with pytest.raises(sa.SattnError, match=rf"^{name} failed"):
+            call()
