@@ -60,3 +60,53 @@ def test_errors_name_the_function_that_was_called():
                         "sigmoid_attn_cross_aligned_fwd_split")):
         with pytest.raises(sa.SattnError, match=rf"^{name} failed"):
             call()
+
+
+@pytest.mark.parametrize("B,H,Nq,Nk,d,causal,alibi,takes", [
+    (1, 2, 1, 1300, 128, False, False, True),     # few blocks, more keys than a wave walks alone
+    (3, 12, 1, 1201, 64, False, True, True),      # 36 blocks, up to a quarter of the units
+    (2, 16, 40, 2600, 64, True, False, True),     # two blocks a head, the second of eight rows
+    (9, 8, 32, 1056, 128, True, True, False),     # 72 blocks, one a head: the kernel of 128 rows
+    (9, 8, 1, 1000, 128, False, False, True),     # the same with fewer than 32 chunks of keys
+])
+def test_c_entry_points_without_a_workspace_match_oracle(B, H, Nq, Nk, d, causal, alibi, takes):
+    """sigmoid_attn_cross_aligned_fwd (and sigmoid_attn_cross_fwd) as C callers have them: the keys of a block are
+    not split over workgroups, and where that would not pay the other forward kernels run."""
+    if sa.sattn_device_info()[0] != 256:
+        pytest.skip("sizes chosen for 256 compute units")
+    lib = sa.load_library()
+    g = torch.Generator().manual_seed(23 + Nk)
+    q = torch.randn(B, H, Nq, d, generator=g).bfloat16()
+    k, v = (torch.randn(B, H, Nk, d, generator=g).bfloat16() for _ in range(2))
+    slopes = W.alibi_slopes(H) if alibi else None
+    sl = slopes.cuda() if alibi else None
+    bias = -math.log(Nk)
+    Q, K, V = q.cuda(), k.cuda(), v.cuda()
+    stream = torch.cuda.current_stream().cuda_stream
+    none = [None] * 4  # contiguous
+
+    def aligned():
+        o = torch.full_like(Q, float("nan"))
+        assert lib.sigmoid_attn_cross_aligned_fwd(Q.data_ptr(), K.data_ptr(), V.data_ptr(), o.data_ptr(), B, H, Nq, Nk, d, 0, bias,
+                                                  int(causal), sl.data_ptr() if alibi else None, *none, stream) == 0
+        torch.cuda.synchronize()
+        return o
+
+    o = aligned()
+    ref = orc.sigmoid_attn_cross_fwd(q.double().numpy(), k.double().numpy(), v.double().numpy(), bias, causal,
+                                     slopes.double().numpy() if alibi else None)
+    err = abs(o.double().cpu().numpy() - ref).max() / abs(ref).max()
+    assert err <= TOL, f"{err:.3e}"
+    if not causal and not alibi:
+        o1 = torch.full_like(Q, float("nan"))
+        assert lib.sigmoid_attn_cross_fwd(Q.data_ptr(), K.data_ptr(), V.data_ptr(), o1.data_ptr(), B, H, Nq, Nk, d, 0, bias, *none,
+                                          stream) == 0
+        torch.cuda.synchronize()
+        assert torch.equal(o, o1)
+    if not takes:
+        try:
+            sa.sattn_set_fwd_waves(4)  # keeps the call to the kernels of 128 rows, whose bits are the same in every shape
+            wide = aligned()
+        finally:
+            sa.sattn_set_fwd_waves(0)
+        assert torch.equal(o, wide)
