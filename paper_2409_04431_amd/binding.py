@@ -8,15 +8,17 @@ fallback: if the library cannot be loaded the call raises.
 The calls of a training or serving loop go through `_native` (csrc/binding_native.cpp), which does
 the checks and the marshalling in C++; it returns None for arguments that it does not take (anything
 but plain CUDA tensors of the expected form), and the ctypes path below it then raises or calls.
+Where it cannot be loaded (it is tied to one torch build, libsattn.so to none) a warning says so and
+every call takes the ctypes path to the same kernels.
 """
 import ctypes
 import os
+import warnings
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libsattn.so")
-_NATIVE_PATH = os.path.join(_HERE, "_native.so")
 _lib = None
 _native = None
 
@@ -35,6 +37,13 @@ _SP = ctypes.POINTER(_Strides)
 _vp = ctypes.c_void_p
 
 
+class _CtypesOnly:
+    """Stands in for `_native` and takes no call."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
 def library_path():
     return _LIB_PATH
 
@@ -44,9 +53,8 @@ def load_library():
     global _lib, _native
     if _lib is not None:
         return _lib
-    for path in (_LIB_PATH, _NATIVE_PATH):
-        if not os.path.exists(path):
-            raise SattnError(f"{path} is missing: build it first (python -m paper_2409_04431_amd.build)")
+    if not os.path.exists(_LIB_PATH):
+        raise SattnError(f"{_LIB_PATH} is missing: build it first (python -m paper_2409_04431_amd.build)")
     lib = ctypes.CDLL(_LIB_PATH)
     i, f, sz = ctypes.c_int, ctypes.c_float, ctypes.c_size_t
     lib.sigmoid_attn_fwd.argtypes = [_vp, _vp, _vp, _vp, i, i, i, i, i, f, i, _vp, _SP, _SP, _SP, _SP, _vp]
@@ -134,8 +142,14 @@ def load_library():
     lib.sattn_device_info.restype = i
     lib.sattn_version.argtypes = []
     lib.sattn_version.restype = i
-    from . import _native as native
-    _lib, _native = lib, native
+    try:
+        from . import _native as native
+    except ImportError as e:
+        warnings.warn(f"the C++ half of the binding cannot be loaded, calls take about 10 us longer: {e}; "
+                      "build it with python -m paper_2409_04431_amd.build", RuntimeWarning, stacklevel=2)
+        native = _CtypesOnly()
+    _native = native  # (before _lib, which other threads look at)
+    _lib = lib
     return lib
 
 

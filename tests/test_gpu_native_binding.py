@@ -143,3 +143,18 @@ def test_calls_on_a_side_stream_and_under_capture():
         assert all(torch.equal(x, y) for x, y in zip(out, want))
         q.copy_(q.flip(0).contiguous())  # eager work between the replays, undone at once
         q.copy_(q.flip(0).contiguous())
+
+
+def test_library_loads_without_the_native_half(monkeypatch):
+    import sys
+    sa.load_library()
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(binding, "_native", None)
+    monkeypatch.delattr(sa, "_native", raising=False)
+    monkeypatch.setitem(sys.modules, "paper_2409_04431_amd._native", None)
+    with pytest.warns(RuntimeWarning, match="C\\+\\+ half"):
+        lib = sa.load_library()
+    assert lib.sattn_version() == sa.sattn_version()
+    with pytest.raises(sa.SattnError, match="must live on the GPU"):  # the ctypes half's checks answer
+        x = torch.zeros(1, 1, 4, 64)
+        sa.sigmoid_attn_fwd(x, x, x, x.clone(), 0.0)
