@@ -32,11 +32,11 @@ def _build_native():
     import torch
 
     root = os.path.dirname(torch.__file__)
-    return _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-w",
+    return _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
                  f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
-                 "-I" + os.path.join(root, "include"),
-                 "-I" + os.path.join(root, "include", "torch", "csrc", "api", "include"),
-                 "-I" + sysconfig.get_paths()["include"],
+                 "-isystem", os.path.join(root, "include"),
+                 "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+                 "-isystem", sysconfig.get_paths()["include"],
                  "-o", NATIVE, os.path.join(CSRC, "binding_native.cpp"),
                  "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10",
                  "-L" + HERE, "-lsattn", "-Wl,-rpath,$ORIGIN"])
