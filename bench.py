@@ -175,7 +175,7 @@ def main():
     bias = cfg.bias
 
     # small grids run the two passes of the backward as one grid (one kernel)
-    one_grid = bool(cfg.backward and cfg.dtype == torch.bfloat16 and sa.sattn_bwd_merged(cfg.B, cfg.H, cfg.N, cfg.causal))
+    one_grid = bool(cfg.backward and cfg.dtype == torch.bfloat16 and sa.sattn_bwd_merged(cfg.B, cfg.H, cfg.N, cfg.causal, cfg.d))
 
     def step(ev=None):
         if ev: ev[0].record()

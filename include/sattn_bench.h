@@ -42,9 +42,11 @@ int sattn_set_fwd_v_slots(int v_slots);
  * passes, self-attention, one K/V head per query head, dq not in the place of q or dout).
  * Results do not depend on it.  Process-wide like the setters above.  Returns 0 or SATTN_ERR_UNSUPPORTED. */
 int sattn_set_bwd_merged(int mode);
-/* 1 if sigmoid_attn_bwd on a bf16 self-attention problem of this size would run its two
- * passes as one grid, 0 if as two launches (head dimension 128; at 64 the one grid is also used
- * for somewhat larger problems); SATTN_ERR_SHAPE for non-positive sizes. */
+/* 1 if sigmoid_attn_bwd (packed: sigmoid_attn_varlen_bwd with N = max_seqlen) on a bf16
+ * self-attention problem of this size would run its two passes as one grid, 0 if as two
+ * launches; SATTN_ERR_SHAPE for non-positive sizes, SATTN_ERR_UNSUPPORTED for another d. */
+int sattn_bwd_one_grid(int B, int H, int N, int d, int causal, int packed);
+/* The same for head dimension 128, not packed (at 64 the choice is another one). */
 int sattn_bwd_merged(int B, int H, int N, int causal);
 
 /* Comparison aids (Section 4 and Appendix F.2 compare the sigmoid kernels with softmax kernels

@@ -132,6 +132,8 @@ def load_library():
     lib.sattn_set_fwd_v_slots.restype = i
     lib.sattn_set_bwd_merged.argtypes = [i]
     lib.sattn_set_bwd_merged.restype = i
+    lib.sattn_bwd_one_grid.argtypes = [i, i, i, i, i, i]
+    lib.sattn_bwd_one_grid.restype = i
     lib.sattn_bwd_merged.argtypes = [i, i, i, i]
     lib.sattn_bwd_merged.restype = i
     lib.sattn_set_clock_probe.argtypes = [_vp, i]
@@ -447,10 +449,10 @@ def sattn_set_fwd_v_slots(v_slots):
     _raise(load_library().sattn_set_fwd_v_slots(int(v_slots)), "sattn_set_fwd_v_slots")
 
 
-def sattn_bwd_merged(B, H, N, causal=False):
-    """True if sigmoid_attn_bwd runs both passes of this bf16 self-attention problem as one grid
-    (head dimension 128; at 64 the one grid is also used for somewhat larger problems)."""
-    rc = load_library().sattn_bwd_merged(int(B), int(H), int(N), int(bool(causal)))
+def sattn_bwd_merged(B, H, N, causal=False, d=128, packed=False):
+    """True if sigmoid_attn_bwd (packed: sigmoid_attn_varlen_bwd with max_seqlen N) runs both passes of this
+    bf16 self-attention problem as one grid."""
+    rc = load_library().sattn_bwd_one_grid(int(B), int(H), int(N), int(d), int(bool(causal)), int(bool(packed)))
     _raise(min(rc, 0), "sattn_bwd_merged")
     return bool(rc)
 

@@ -961,10 +961,13 @@ int sattn_set_fwd_waves(int waves) {
   return SATTN_OK;
 }
 
-int sattn_bwd_merged(int B, int H, int N, int causal) {
+int sattn_bwd_one_grid(int B, int H, int N, int d, int causal, int packed) {
   if (B <= 0 || H <= 0 || N <= 0) return SATTN_ERR_SHAPE;
-  return pick_bwd_merged(B, H, N, causal, false, false) ? 1 : 0;
+  if (d != 64 && d != 128) return SATTN_ERR_UNSUPPORTED;
+  return pick_bwd_merged(B, H, N, causal, d == 64, packed != 0) ? 1 : 0;
 }
+
+int sattn_bwd_merged(int B, int H, int N, int causal) { return sattn_bwd_one_grid(B, H, N, 128, causal, 0); }
 
 int sattn_set_bwd_merged(int mode) {
   if (mode < 0 || mode > 3) return SATTN_ERR_UNSUPPORTED;

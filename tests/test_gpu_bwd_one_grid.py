@@ -18,6 +18,17 @@ def test_one_grid_where_the_paired_launches_leave_places_empty():
     assert sa.sattn_bwd_merged(3, 16, 1024) and not sa.sattn_bwd_merged(4, 16, 1024) and not sa.sattn_bwd_merged(39, 12, 64, True)
 
 
+def test_the_choice_is_reported_for_the_head_dimension_and_for_packed_sequences():
+    # workgroups per pass and unit: 2, 6, 6.25
+    assert not sa.sattn_bwd_merged(4, 16, 1024) and sa.sattn_bwd_merged(4, 16, 1024, d=64)
+    assert sa.sattn_bwd_merged(12, 16, 1024, d=64) and not sa.sattn_bwd_merged(25, 64, 128, d=64)
+    # packed: up to 6, at d = 64 up to 9
+    assert sa.sattn_bwd_merged(12, 16, 1024, packed=True) and not sa.sattn_bwd_merged(25, 64, 128, packed=True)
+    assert sa.sattn_bwd_merged(18, 16, 1024, d=64, packed=True) and not sa.sattn_bwd_merged(37, 64, 128, d=64, packed=True)
+    lib = sa.load_library()
+    assert lib.sattn_bwd_one_grid(0, 1, 16, 64, 0, 0) == -2 and lib.sattn_bwd_one_grid(1, 1, 16, 32, 0, 0) == -3
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("causal,alibi", [(False, False), (True, False), (False, True), (True, True)])
