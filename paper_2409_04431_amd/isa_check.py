@@ -18,11 +18,16 @@ one M0 value set by an asm statement the compiler knows nothing about:
 Wait states are counted like the compiler does: one per instruction, N+1 for `s_nop N`;
 an intervening MFMA counts as its own pass count because it occupies the matrix pipe that
 long.  Only hazards with an asm MFMA on one side are reported (compiler-emitted MFMAs are
-already covered by the compiler).  The scan is linear per function, which covers the
-fall-through order in which the register allocator places its copies.
+already covered by the compiler).  The scan follows every path of a function, taken branches and
+the back edges of loops among them: the steps of the pinned loops end with MFMAs whose results the
+next trip's first vector instructions read.
+
+The register counts of the kernels are read from the same listing (kernel_registers): two workgroups
+of 256 threads share a compute unit where a kernel stays within 256.
 
 Run as a module to check the library sources:  python -m paper_2409_04431_amd.isa_check
 """
+import functools
 import os
 import re
 import subprocess
@@ -50,10 +55,10 @@ def _regs(operand):
 
 
 class Inst:
-    __slots__ = ("op", "dst", "src", "in_asm", "text", "line")
+    __slots__ = ("op", "dst", "src", "in_asm", "text", "line", "succ")
 
     def __init__(self, text, in_asm, line):
-        self.text, self.in_asm, self.line = text, in_asm, line
+        self.text, self.in_asm, self.line, self.succ = text, in_asm, line, ()
         parts = text.split(None, 1)
         self.op = parts[0]
         ops = [o.strip() for o in parts[1].split(",")] if len(parts) > 1 else []
@@ -80,69 +85,86 @@ class Inst:
         return 1
 
 
+def _link(insts, labels):
+    """Set every instruction's successors (indices into `insts`)."""
+    for i, ins in enumerate(insts):
+        nxt = [i + 1] if i + 1 < len(insts) and ins.op not in ("s_branch", "s_endpgm") else []
+        if ins.op == "s_branch" or ins.op.startswith("s_cbranch"):
+            target = labels[ins.text.split()[1]]
+            if target < len(insts):
+                nxt.append(target)
+        ins.succ = tuple(nxt)
+    return insts
+
+
 def parse_functions(asm_text):
     """Yield (name, [Inst]) for every function of an AMDGPU assembly listing."""
-    name, insts, in_asm = None, [], False
+    name, insts, labels, in_asm, in_metadata = None, [], {}, False, False
     for ln, raw in enumerate(asm_text.splitlines(), 1):
         line = raw.strip()
+        if line in (".amdgpu_metadata", ".end_amdgpu_metadata"):
+            in_metadata = line == ".amdgpu_metadata"
+        if in_metadata:
+            continue
         if line.startswith(";;#ASMSTART"):
             in_asm = True
             continue
         if line.startswith(";;#ASMEND"):
             in_asm = False
             continue
+        m = re.match(r"^([A-Za-z_.][\w$.]*):", line)
+        if m:
+            label = m.group(1)
+            if label.startswith(".Lfunc_end") or not label.startswith(".L"):
+                if name and insts:
+                    yield name, _link(insts, labels)
+                name, insts, labels = None if label.startswith(".L") else label, [], {}
+            else:
+                labels[label] = len(insts)
+            continue
         if not line or line.startswith((";", ".", "//")):
             continue
-        m = re.match(r"^([A-Za-z_][\w$.]*):", line)
-        if m:
-            if not line.startswith(".L"):
-                if name and insts:
-                    yield name, insts
-                name, insts = m.group(1), []
-            continue
         code = line.split(";")[0].strip()
-        if not code or name is None:
-            continue
-        if code.startswith("s_endpgm"):
-            if insts:
-                yield name, insts
-            name, insts = None, []
-            continue
-        insts.append(Inst(code, in_asm, ln))
+        if code and name is not None:
+            insts.append(Inst(code, in_asm, ln))
     if name and insts:
-        yield name, insts
+        yield name, _link(insts, labels)
+
+
+def kernel_registers(asm_text):
+    """{kernel: vector registers (both kinds) it takes}, from the descriptors of a listing."""
+    return {m.group(1): int(m.group(2))
+            for m in re.finditer(r"^\s*\.amdhsa_kernel (\S+)\n(?:.*\n)*?\s*\.amdhsa_next_free_vgpr (\d+)", asm_text, re.M)}
+
+
+def _reach(insts, i, need):
+    """(instruction, wait states since instruction i) for what runs on some path within `need` of them."""
+    best, todo = {}, [(j, 0) for j in insts[i].succ]
+    while todo:
+        j, ws = todo.pop()
+        if ws >= need or best.get(j, need) <= ws:
+            continue
+        best[j] = ws
+        todo.extend((k, ws + insts[j].wait_states()) for k in insts[j].succ)
+    return [(insts[j], ws) for j, ws in sorted(best.items())]
 
 
 def check_function(insts):
     """Return a list of (rule, message) violations."""
     bad = []
     for i, ins in enumerate(insts):
-        if not ins.is_mfma:
-            continue
-        # Rule A: look back
-        if ins.in_asm:
-            ws, j = 0, i - 1
-            while j >= 0 and ws < 2:
-                p = insts[j]
-                if p.is_valu and (p.dst & ins.src):
-                    bad.append(("A", f"line {p.line}: '{p.text}' feeds '{ins.text}' (line {ins.line}) after {ws} wait states"))
-                    break
-                ws += p.wait_states()
-                j -= 1
-        # Rule B: look ahead
-        if ins.in_asm:
-            need = _AFTER_MFMA[_PASSES.get(ins.op, 8)]
-            ws, j = 0, i + 1
-            while j < len(insts) and ws < need:
-                n = insts[j]
+        if ins.is_valu and ins.dst:
+            for n, ws in _reach(insts, i, 2):
+                if n.is_mfma and n.in_asm and (ins.dst & n.src):
+                    bad.append(("A", f"line {ins.line}: '{ins.text}' feeds '{n.text}' (line {n.line}) after {ws} wait states"))
+        elif ins.is_mfma and ins.in_asm:
+            for n, ws in _reach(insts, i, _AFTER_MFMA[_PASSES.get(ins.op, 8)]):
                 if not n.is_mfma and ((n.src | n.dst) & ins.dst):
                     bad.append(("B", f"line {n.line}: '{n.text}' touches the result of '{ins.text}' (line {ins.line}) after {ws} wait states"))
                     break
                 if n.is_mfma and (n.dst & ins.dst) and n.dst != ins.dst:
                     bad.append(("B", f"line {n.line}: '{n.text}' partly overlaps the result of '{ins.text}' (line {ins.line})"))
                     break
-                ws += n.wait_states()
-                j += 1
     # Rule C
     if any(i.in_asm and i.op.startswith("global_load_lds") for i in insts):
         for ins in insts:
@@ -159,6 +181,7 @@ def check_text(asm_text):
     return out
 
 
+@functools.lru_cache(maxsize=1)
 def compile_to_asm(extra_flags=()):
     """Device-only assembly of the library sources with the product's flags."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
