@@ -30,6 +30,10 @@
  *  - d must be 64 or 128.  N >= 1 need not be a multiple of any tile size.
  *  - SATTN_BF16: inputs/outputs bf16, logits, sigmoid and accumulation in fp32, P and dS
  *    rounded to bf16 before the second matrix product.  SATTN_F32: everything fp32.
+ *  - A call gives the same bits each time it is made.  With SATTN_F32, in the *_split calls and
+ *    with few queries against many keys the order of the fp32 sums depends on B and H as well
+ *    as on the sequence, which may then have other last bits in a larger or packed batch; in
+ *    all other bf16 calls it depends on the sequence alone.
  *  - bias is the scalar b in natural-log units (callers pass -log(N)); alibi_slopes is a
  *    device pointer to H floats or NULL; causal is 0 or 1.
  *  - Calls are asynchronous on `stream` (a hipStream_t; NULL = default stream) and launch on

@@ -614,7 +614,7 @@ __device__ __forceinline__ void bwd_step_full_pinned(BwdWave<D, MODE>& W, uint32
 // Bound: vector-instruction issue (7 instructions per element against half the matrix work of
 // d = 128), of which a lone wave reaches about one in six cycles; the second wave per SIMD is what
 // the registers are saved for: dK/dV 292-324 -> 240-252 of 512, dQ 248-276 -> 204-216, one grid
-// 300-320 -> 244-248.  Measured (us, eight-slot form / this one): dK/dV B32 H12 N4096 causal
+// 300-320 -> 244-252.  Measured (us, eight-slot form / this one): dK/dV B32 H12 N4096 causal
 // 1997 / 1621, B32 H12 N1024 272 / 214, B32 H12 N250 39 / 30, B1 H16 N2048 causal 42 / 40; dQ
 // unchanged; one grid B4 H12 N1024 69 / 57.
 template <int D, int MODE, int AL, int PAR, bool DMA, bool MASK, bool GUARD, int K>
@@ -1231,7 +1231,7 @@ __device__ __forceinline__ int bwd_block_of_rank(const BwdParams& p, int rank) {
 // At d = 64 the ring takes 64 KB, so two workgroups fit a compute unit if the kernel stays within
 // 256 registers.  The compiler-scheduled forms (PIN = false) need that second wave per SIMD to
 // hide their schedule and sit right at the limit, so they are held to it; the pinned sigmoid forms
-// stay below it by themselves (138-156 VGPRs and 64 or 96 AGPRs).  The grouped dK/dV pass, with its
+// stay below it by themselves (204-252; tests/test_isa_hazards.py checks the counts).  The grouped dK/dV pass, with its
 // loop over query heads at 264-288, is held to it: the bound splits the file 128 + 128, which costs
 // 32-104 bytes of scratch in the set-up of a head, nothing in the pinned steps (dK/dV + dQ, us:
 // B7 H16 N5119 causal with one K/V head 2155 -> 1771, B3 H32 N3000 causal with four 707 -> 578).  The pinned

@@ -22,10 +22,11 @@
 // backward passes, against a kernel whose four waves own 128 stationary rows and share 32-row
 // tiles through LDS between two barriers (the passes as two launches):
 //   B1 H2 N256 d64            35 + 106 -> 11 + 18        (latency: 16 and 32 workgroups)
-//   B2 H8 N1000 d128 causal  216 + 627 -> 47 + 142
+//   B2 H8 N1000 d128 causal  216 + 627 -> 47 + 143
 //   B4 H12 N1024 d64         206 + 700 -> 126 + 397
 //   B1 H8 N2048 d128         421 + 1211 -> 144 + 465     (119 TFLOP/s forward, 129 over the seven
-//                            backward products; a large library product runs at 138 on this card)
+//                            backward products; a library product of two 4096^2 matrices runs at
+//                            132 on this card, of two 8192^2 ones at 154)
 //
 // MFMA 32x32x2 fp32 fragment maps, lane l (l32 = l%32, h = l/32):
 //   A (32x2): row l32, k = h;  B (2x32): col l32, k = h;  C: col l32, row 8*(r/4)+4h+r%4.

@@ -17,7 +17,7 @@
 // d = 128) in flight.  MFMA use is wasteful with one query (one column of 32) and still takes
 // less than a tenth of the time the chunk takes to arrive.
 // Measured on one MI355X (us, the 128-row kernel -> this one with its reduction): one query, 4001
-// keys, d 128, 128 heads with ALiBi 79 -> 50 (5.2 TB/s, what a large copy reaches), 16 heads 61 ->
+// keys, d 128, 128 heads with ALiBi 79 -> 50 (262 MB; 40 of it stream them, 6.6 TB/s), 16 heads 61 ->
 // 14; one query, 32768 keys, 8 heads 468 -> 33; 64 queries, 8256 keys, 16 heads 125 -> 23; one
 // query, 244 keys 7.0 -> 5.4.
 #pragma once

@@ -10,10 +10,15 @@
 // the attention kernel is not possible: a workgroup there owns one head, the statistics span
 // all heads.  Rows of up to 16 or 32 chunks share a wave four or two at a time.
 // What it takes besides the bytes: every load of a token issued before the first is waited for, and
-// stores that do not displace what the caches hold (the output is not read back here; after a
-// forward pass its input still is, by the backward).  B8 H16 N4096 d128, forward + backward alternating:
-// 125 -> 113 us (671 MB, 6.0 TB/s; a copy of one such tensor onto another reaches 7.2); H2 d128 of 30345
-// tokens, two to a wave, 26.5 -> 14.4.
+// non-temporal stores, which leave the inputs in the caches.  B8 H16 N4096 d128, forward + backward
+// alternating: 126.0 -> 117.4 us (671 MB, 5.7 TB/s; a library's elementwise product over 1 GiB reaches
+// 6.3, over a tensor of this size, which the caches hold, 7.5); H2 d128 of 30345 tokens, two to a wave,
+// 26.5 -> 14.4.
+// What the next kernel pays for non-temporal stores (us per chain, non-temporal / plain): write x, forward,
+// residual 16 MiB 22.7 / 23.4, 64 MiB 72.0 / 72.2, 128 MiB 161 / 175, 512 MiB 689 / 682; write dy,
+// backward, read dx 23.4 / 23.8, 84.2 / 84.0, 157 / 170, 726 / 722; equal up to 8 MiB.  Between attention and
+// matrix products, forward and backward, 6 to 256 MiB: within 1 % either way.  They lose where x is
+// in the caches already and nothing but the output is read next (128 MiB 95 / 88).
 #pragma once
 #include "sattn_common.hpp"
 
