@@ -37,6 +37,7 @@ attn_fwd_few_kernel(const FwdParams p) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  ClockStart clk = clock_probe_begin(p.clock);
 
   // place -> (head, key split, query block): the query blocks of a split run next to each other
   // on one XCD and share its keys
@@ -109,6 +110,9 @@ attn_fwd_few_kernel(const FwdParams p) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) oacc[dt][r] = 0.f;
 
+  clk.tiles = clk.steady_tiles = c < n_chunks ? (n_chunks - 1 - c) / stride + 1 : 0;  // (the wave's chunks)
+  clock_probe_mark(p.clock, clk, kMarkFirstProduct);
+  clock_probe_mark(p.clock, clk, kMarkSteadyBegin);
   for (; c < n_chunks; c += stride) {
     const int nxt = c + stride < n_chunks ? c + stride : c;
     f32x16 s;
@@ -157,6 +161,7 @@ attn_fwd_few_kernel(const FwdParams p) {
     asm volatile("" ::: "memory");
   }
 
+  clock_probe_mark(p.clock, clk, kMarkSteadyEnd);
   // ---- partial outputs: register 4g+t of tile dt is O[q0 + l32][32dt + 8g + 4h + t]
   __syncthreads();
   float* const parts = (float*)smem;
@@ -170,6 +175,7 @@ attn_fwd_few_kernel(const FwdParams p) {
             f32x4{oacc[dt][4 * g], oacc[dt][4 * g + 1], oacc[dt][4 * g + 2], oacc[dt][4 * g + 3]};
   }
   __syncthreads();
+  clock_probe_mark(p.clock, clk, kMarkStore);
   for (int idx = tid; idx < rows * (D / 8); idx += NT) {
     const int r = idx / (D / 8), cc = idx % (D / 8);
     f32x4 lo = {0.f, 0.f, 0.f, 0.f}, hi = {0.f, 0.f, 0.f, 0.f};
@@ -191,6 +197,7 @@ attn_fwd_few_kernel(const FwdParams p) {
       *(u32x4*)((__bf16*)p.o.ptr + b * p.o.sb + hd * p.o.sh + (int64_t)(q0 + r) * p.o.ss + 8 * cc) = w;
     }
   }
+  clock_probe_end(p.clock, clk);
 }
 
 // O = sum of the splits' partial outputs, rounded to bf16 once.  One thread per four features.

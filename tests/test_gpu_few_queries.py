@@ -110,3 +110,21 @@ def test_c_entry_points_without_a_workspace_match_oracle(B, H, Nq, Nk, d, causal
         finally:
             sa.sattn_set_fwd_waves(0)
         assert torch.equal(o, wide)
+
+
+def test_clock_probe_records_the_workgroups_of_few_queries():
+    B, H, Nk, d = 1, 4, 1100, 64
+    q = torch.randn(B, H, 1, d, device="cuda").bfloat16()
+    k, v = (torch.randn(B, H, Nk, d, device="cuda").bfloat16() for _ in range(2))
+    splits = max(1, sa.sigmoid_attn_cross_aligned_fwd_workspace_bytes(B, H, 1, Nk, d) // (B * H * d * 4))
+    buf = torch.zeros(8 * 64, dtype=torch.int64, device="cuda")
+    try:
+        sa.sattn_set_clock_probe(buf)
+        sa.sigmoid_attn_cross_fwd(q, k, v, torch.empty_like(q), -7.0)
+        torch.cuda.synchronize()
+    finally:
+        sa.sattn_set_clock_probe(None)
+    rec = buf.cpu().view(-1, 8)
+    assert (rec[:B * H * splits, 0] > 0).all() and (rec[B * H * splits:] == 0).all()
+    marks = rec[:B * H * splits, 2:6]
+    assert (marks[:, 1:] >= marks[:, :-1]).all() and (marks[:, 3] <= rec[:B * H * splits, 1]).all()
