@@ -241,6 +241,16 @@ bool pick_bwd_merged(int B, int H, int N, int causal, bool two_per_cu, bool pack
   return (places - pairs) * 25 > places;
 }
 
+// The backward that holds a head whole (sattn_bwd_short.hpp): wherever two of its workgroups share a
+// compute unit (d = 64, 128 keys: 5.9 us against 7.5 with 16 heads of 64); the larger ones only from more
+// heads than half the units on.  Below, the two passes' four workgroups a head (two at d = 128) all find
+// a place at once and share the work further: N250 d64 16 heads 12.6 / 17.1 us, 64 heads 13.3 / 17.9, 144
+// heads 24.3 / 18.9; N128 d128 16 heads 12.0 / 12.6, 144 heads 21.2 / 14.7.
+bool pick_bwd_short(int64_t heads, int N, int d) {
+  if (g_bwd_merged.load(std::memory_order_relaxed) != 0 || N > (d == 64 ? 256 : 128)) return false;
+  return (d == 64 && N <= 128) || 2 * heads > compute_units();
+}
+
 // Workgroups over which the dK/dV pass splits the query heads of one K/V head (a power of two
 // that divides the group): one per K/V head and key block leaves compute units idle when there
 // are few K/V heads -- with one K/V head, 8 sequences of 4096 tokens make 256 workgroups of
@@ -543,6 +553,9 @@ int bwd_impl(const BwdArgs& a) {
     if (rc) return rc;
     p.nlse2 = nlse2; p.dvec = dvec; p.npad = npad;
   }
+  if (!SOFTMAX && PIN && !in_place && !alibi && !a.db_rows && Hkv == a.H && Nk == a.N && a.parts == (kBwdDkDv | kBwdDq) &&
+      pick_bwd_short((int64_t)a.B * a.H, a.N, a.d))
+    return a.d == 128 ? launch_bwd_short<128>(p, a.causal, st) : launch_bwd_short<64>(p, a.causal, st);
   const bool merged = !in_place && pick_bwd_merged(a.B, a.H, a.N, a.causal, a.d == 64 && !SOFTMAX, a.cu_seqlens != nullptr);
   int n_split = 1;
   if (a.group_split && !SOFTMAX && PIN && Hkv != a.H && !a.cu_seqlens && Nk == a.N && (a.parts & kBwdDkDv)) {

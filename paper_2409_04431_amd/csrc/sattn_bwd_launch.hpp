@@ -1,5 +1,6 @@
 // Definition of launch_bwd_bf16<D>; included by the one translation unit that instantiates it.
 #pragma once
+#include "sattn_bwd_short.hpp"
 #include "sattn_launch.hpp"
 
 namespace sattn {
@@ -79,6 +80,17 @@ int launch_bwd_variant(BwdParams p, int causal, bool alibi, int parts, bool merg
     SATTN_DISPATCH2(causal, alibi, rc = launch(attn_bwd_kernel<D, BWD_DQ, A, B2, SOFTMAX, PIN>, grid, block, lds, st, p));
   }
   return rc;
+}
+
+template <int D>
+int launch_bwd_short(const BwdParams& p, int causal, hipStream_t st) {
+  if constexpr (D == 64) {
+    if (p.N > 128)
+      return causal ? launch(attn_bwd_short_kernel<D, 8, true>, dim3(p.B * p.H), dim3(512), short_lds_bytes<D, 8>(), st, p)
+                    : launch(attn_bwd_short_kernel<D, 8, false>, dim3(p.B * p.H), dim3(512), short_lds_bytes<D, 8>(), st, p);
+  }
+  return causal ? launch(attn_bwd_short_kernel<D, 4, true>, dim3(p.B * p.H), dim3(256), short_lds_bytes<D, 4>(), st, p)
+                : launch(attn_bwd_short_kernel<D, 4, false>, dim3(p.B * p.H), dim3(256), short_lds_bytes<D, 4>(), st, p);
 }
 
 template <int D>

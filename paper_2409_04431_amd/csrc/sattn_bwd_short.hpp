@@ -1,0 +1,224 @@
+// Sigmoid-attention backward of sequences that one workgroup holds whole: up to 256 keys at d = 64,
+// 128 at d = 128 (bf16, no ALiBi).
+//
+// The two passes of sattn_bwd.hpp evaluate every logit, dP and sigmoid twice, because no workgroup
+// holds all keys a dQ row has to be summed over.  Here one does.  A wave owns 32 keys (K, V
+// fragments and the dK^T, dV^T accumulators in registers) and goes through the queries in
+// chunks of 32: S = Q K^T, dP = dO V^T, dS, dV^T += dO^T P, dK^T += Q^T dS.  It leaves dS in LDS, keys by
+// queries, and after every 128 queries the waves share out dQ^T = K^T dS^T by tiles of 32 queries x
+// 32 features, each summed over all keys in ascending order: the additions of the dQ pass, so that results are
+// the two passes' bit for bit.  Q, dO and K are in LDS once and for all, read by rows and transposed.
+//
+// What bounds it: vector issue, about 1200 cycles per 32 x 32 chunk and SIMD against 850 of its
+// instructions (the compiler's order; the second wave of a SIMD fills it), and around it 4 to 5 us of
+// first loads, one workgroup's 160 KB of LDS leaving no room for another's.  Up to 128 keys two workgroups
+// share a compute unit.  Measured (us, one grid of the two passes / this): B32 H12 N250 d64 44.0 / 38.9,
+// causal 40.9 / 33.5; B64 H16 N250 104 / 82.8; B32 H12 N128 18.4 / 14.3; B64 H16 N64 31.4 / 17.2;
+// B32 H16 N128 d128 52.9 / 35.6; B64 H32 N64 d128 137 / 69.1.
+#pragma once
+#include "sattn_bwd.hpp"
+
+namespace sattn {
+
+// LDS: Q and dO tiles of all queries, all keys, dS of 128 queries.
+template <int D, int NW>
+constexpr size_t short_lds_bytes() { return (size_t)NW * 32 * D * 2 * 3 + (size_t)NW * 32 * 128 * 2; }
+
+template <int D, int NW, bool CAUSAL>
+__global__ void __launch_bounds__(64 * NW, D == 64 ? 2 : 1) attn_bwd_short_kernel(const BwdParams p) {
+  constexpr int KD = D / 16, DT = D / 32, MAXN = 32 * NW, TILE = 64 * D * 2, SLOT = 2 * TILE;
+  constexpr int N_SUB = 4 * DT / NW, SUB_STEP = NW / DT;  // dQ tiles (32 queries x 32 features) of a wave per 128 queries
+  static_assert(NW % DT == 0 && N_SUB >= 1, "a wave keeps one tile of features");
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(SATTN_LDS(char)*)smem;
+  const uint32_t lds_k = lds0 + (MAXN / 64) * SLOT, lds_ds = lds_k + (MAXN / 64) * TILE;
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  ClockStart clk = clock_probe_begin(p.clock);
+  const int bh = blockIdx.x, b = bh / p.H, hd = bh - b * p.H;
+  int N = p.N;
+  int64_t tok0 = 0;
+  float nbias = p.nbias_log2;
+  if (p.cu_seqlens) {
+    tok0 = p.cu_seqlens[b];
+    N = min(p.cu_seqlens[b + 1] - (int)tok0, p.N);
+    if (p.bias_vec) nbias = -p.bias_vec[b] * kLog2e;
+    if (N <= 0) return;
+  }
+  auto base = [&](const TensorRef& t) { return (__bf16*)t.ptr + b * t.sb + hd * t.sh + tok0 * t.ss; };
+  const __bf16 *kb = base(p.k), *vb = base(p.v);
+
+  // ---- K, the first 128 queries and this wave's V rows; the other queries follow while these are worked on
+  const int n_tiles = (N + 63) / 64, n_chunks = (N + 31) / 32;
+  DmaStagerX<D, NW> sq, sd;
+  sq.init(base(p.q), p.q.ss, N, 0, wave, lane);
+  sd.init(base(p.dout), p.dout.ss, N, 0, wave, lane);
+  auto stage = [&](int t0, int t1) {
+    for (int t = t0; t < t1; ++t) {
+      sq.issue(lds0 + t * SLOT, N, wave, lane);
+      sd.issue(lds0 + t * SLOT + TILE, N, wave, lane);
+    }
+  };
+  {
+    DmaStagerX<D, NW> sk;
+    sk.init(kb, p.k.ss, N, 0, wave, lane);
+    for (int t = 0; t < n_tiles; ++t) sk.issue(lds_k + t * TILE, N, wave, lane);
+  }
+  stage(0, min(n_tiles, 2));
+  // Causal: wave w's keys meet the queries from theirs on; the waves of a SIMD (w, w + 4) get key
+  // blocks whose work adds up to the same.
+  const int kblk = (CAUSAL && NW == 8 && wave >= 4) ? 11 - wave : wave;
+  const int key0 = 32 * kblk, key = key0 + l32, key_ld = key < N ? key : N - 1;
+  bf16x8 x1[KD], x2[KD];
+#pragma unroll
+  for (int kk = 0; kk < KD; ++kk) {
+    // (no V row past the end: dP and dS of such a key are zero, and it adds nothing to dQ)
+    const u32x4 x = *(const u32x4*)(vb + (int64_t)key_ld * p.v.ss + 16 * kk + 8 * h);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) ((u32x4&)x2[kk])[i] = key < N ? x[i] : 0u;
+  }
+  f32x16 dk[DT], dv[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) dk[dt][r] = dv[dt][r] = 0.f;
+
+  // per-lane LDS addresses: rows of a chunk, transposed reads of a tile, of the keys and of dS
+  const int kap = kappa(l32), i16 = lane & 15, blk1 = (lane >> 4) & 1;
+  uint32_t row[KD], tr[DT][2], ds_rd[2];
+#pragma unroll
+  for (int kk = 0; kk < KD; ++kk) row[kk] = kap * (D * 2) + (((2 * kk + h) ^ SwzX<D>::f(kap)) << 4);
+#pragma unroll
+  for (int rd = 0; rd < 2; ++rd) {
+    const int r = 8 * h + 4 * rd + (i16 >> 2), c = 2 * blk1 + ((i16 & 3) >> 1);
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) tr[dt][rd] = r * (D * 2) + (((4 * dt + c) ^ SwzX<D>::f(r)) << 4) + ((i16 & 1) << 3);
+    ds_rd[rd] = r * 128 + ((c ^ SwzX<64>::f(r)) << 4) + ((i16 & 1) << 3);  // (queries 32..63 of a row: bit 6 flipped)
+  }
+  const uint32_t ds_wr = lds_ds + key * 128 + ((h ^ SwzX<64>::f(key)) << 4);
+
+  // Rows past the end are zeros in dO and K: the queries there add nothing to dK and dV, the keys
+  // nothing to dQ, without a mask.
+  auto pad = [&](uint32_t tile, int t) {
+    for (int i = tid; i < (64 * (t + 1) - N) * (D / 8); i += 64 * NW)
+      lds_write_b128(tile + ((N & 63) + i / (D / 8)) * (D * 2) + (i % (D / 8)) * 16, u32x4{0, 0, 0, 0});
+  };
+  SATTN_WAIT_VMCNT(0);
+  stage(2, n_tiles);
+  __syncthreads();
+  clock_probe_mark(p.clock, clk, kMarkFirstProduct);
+  {
+    const int at = key0 + l32;  // (rows of a wave past the end: whatever is there, nobody uses it)
+#pragma unroll
+    for (int kk = 0; kk < KD; ++kk) x1[kk] = as_bf16x8(lds_read_b128(lds_k + at * (D * 2) + (((2 * kk + h) ^ SwzX<D>::f(at)) << 4)));
+  }
+  if (n_tiles * 64 > N) {
+    pad(lds_k + (n_tiles - 1) * TILE, n_tiles - 1);
+    if (n_tiles <= 2) pad(lds0 + (n_tiles - 1) * SLOT + TILE, n_tiles - 1);
+    __syncthreads();
+  }
+
+  const int rounds = (N + 127) / 128, c_end = key0 < N ? n_chunks : 0;  // (a wave past the end has no chunk)
+  for (int rnd = 0; rnd < rounds; ++rnd) {
+    const int c_lo = CAUSAL ? max(4 * rnd, kblk) : 4 * rnd, c_hi = min(4 * rnd + 4, c_end);
+#pragma nounroll
+    for (int c = c_lo; c < c_hi; ++c) {
+      const uint32_t at = lds0 + (c >> 1) * SLOT + (c & 1) * (32 * D * 2);
+      f32x16 s, dp;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[r] = dp[r] = 0.f;
+#pragma unroll
+      for (int kk = 0; kk < KD; ++kk) {
+        s = mfma32(as_bf16x8(lds_read_b128(at + row[kk])), x1[kk], s);
+        dp = mfma32(as_bf16x8(lds_read_b128(at + TILE + row[kk])), x2[kk], dp);
+      }
+      float pr[16], ds[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], p.nscale_log2, nbias));
+        pr[r] = __builtin_amdgcn_rcpf(1.0f + e);
+        ds[r] = __builtin_fmaf(-pr[r], pr[r], pr[r]) * dp[r];
+      }
+      if (CAUSAL && c == kblk) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const bool keep = key_of_reg(r) + 8 * h >= l32;
+          pr[r] = keep ? pr[r] : 0.f;
+          ds[r] = keep ? ds[r] : 0.f;
+        }
+      }
+      bf16x8 pb[2] = {pack8(pr), pack8(pr + 8)}, dsb[2] = {pack8(ds), pack8(ds + 8)};
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) {
+          const uint32_t off = at + ks * 16 * (D * 2);
+          dv[dt] = mfma32(join_tr(lds_read_tr16(off + TILE + tr[dt][0]), lds_read_tr16(off + TILE + tr[dt][1])), pb[ks], dv[dt]);
+          dk[dt] = mfma32(join_tr(lds_read_tr16(off + tr[dt][0]), lds_read_tr16(off + tr[dt][1])), dsb[ks], dk[dt]);
+        }
+      // dS, keys by queries: rows of 64 queries of a key, two such tiles
+      const uint32_t to = (ds_wr ^ ((c & 1) << 6)) + ((c >> 1) & 1) * (MAXN * 128);
+      lds_write_b128(to, __builtin_bit_cast(u32x4, dsb[0]));
+      lds_write_b128(to ^ 32, __builtin_bit_cast(u32x4, dsb[1]));
+    }
+    if (rnd == 0) {
+      clock_probe_mark(p.clock, clk, kMarkSteadyBegin);
+      SATTN_WAIT_VMCNT(0);  // the other queries have landed
+    }
+    __syncthreads();
+    if (rnd == 0) clock_probe_mark(p.clock, clk, kMarkSteadyEnd);
+    if (rnd == 0 && n_tiles > 2 && n_tiles * 64 > N) pad(lds0 + (n_tiles - 1) * SLOT + TILE, n_tiles - 1);
+    // dQ of these 128 queries: this wave's tile of features, all keys
+    const int dt = wave % DT;
+    const uint32_t kt0 = lds_k + tr[0][0], kt1 = lds_k + tr[0][1];
+    const uint32_t flip = (uint32_t)(4 * dt) << 4;
+#pragma unroll
+    for (int i = 0; i < N_SUB; ++i) {
+      const int sub = wave / DT + i * SUB_STEP, c = 4 * rnd + sub;
+      if (c >= n_chunks) continue;
+      const int n_kb = CAUSAL ? c + 1 : n_chunks;  // blocks of 32 keys
+      const uint32_t from = lds_ds + (sub >> 1) * (MAXN * 128), half = (sub & 1) << 6;
+      f32x16 dq;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) dq[r] = 0.f;
+      bf16x8 ka[2], wa[2];
+      auto fetch = [&](int j) {
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+          const uint32_t ko = (2 * j + ks) * 16 * (D * 2), so = from + (2 * j + ks) * 16 * 128;
+          ka[ks] = join_tr(lds_read_tr16((kt0 ^ flip) + ko), lds_read_tr16((kt1 ^ flip) + ko));
+          wa[ks] = join_tr(lds_read_tr16(so + (ds_rd[0] ^ half)), lds_read_tr16(so + (ds_rd[1] ^ half)));
+        }
+      };
+      fetch(0);
+#pragma nounroll
+      for (int j = 0; j < n_kb; ++j) {
+        const bf16x8 k0 = ka[0], k1 = ka[1], w0 = wa[0], w1 = wa[1];
+        fetch(min(j + 1, n_kb - 1));
+        dq = mfma32(k0, w0, dq);
+        dq = mfma32(k1, w1, dq);
+      }
+      const int q = 32 * c + l32;
+      if (q < N) {
+        __bf16* out = base(p.dq) + (int64_t)q * p.dq.ss + 32 * dt + 4 * h;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          u32x2 w;
+          w[0] = pack_bf16(dq[4 * g] * p.inv_sqrt_d, dq[4 * g + 1] * p.inv_sqrt_d);
+          w[1] = pack_bf16(dq[4 * g + 2] * p.inv_sqrt_d, dq[4 * g + 3] * p.inv_sqrt_d);
+          *(u32x2*)(out + 8 * g) = w;
+        }
+      }
+    }
+    __syncthreads();
+  }
+  clock_probe_mark(p.clock, clk, kMarkStore);
+  const uint32_t obuf = lds0 + wave * (2 * RowStore<D>::BYTES);
+  static_assert(NW * 2 * RowStore<D>::BYTES <= short_lds_bytes<D, NW>(), "outputs leave through the same LDS");
+  RowStore<D>::run(dk, p.inv_sqrt_d, obuf, lane, base(p.dk) + (int64_t)key0 * p.dk.ss, p.dk.ss, N - key0);
+  RowStore<D>::run(dv, 1.0f, obuf + RowStore<D>::BYTES, lane, base(p.dv) + (int64_t)key0 * p.dv.ss, p.dv.ss, N - key0);
+  clk.tiles = n_tiles;
+  clock_probe_end(p.clock, clk, bh);
+}
+
+}  // namespace sattn

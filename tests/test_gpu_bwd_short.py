@@ -1,0 +1,62 @@
+"""The backward that holds a head whole (up to 256 keys at d = 64, 128 at d = 128): the two passes'
+results bit for bit, the oracle's within the bf16 bar, nothing written past the rows of a sequence."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2409_04431_amd as sa
+from oracle import sattn_oracle as orc
+
+pytestmark = pytest.mark.gpu
+TOL = 2e-2  # P, dS and the outputs are rounded to bf16
+HEADS = 17  # odd batches of it lie on both sides of the rule's line
+
+SIZES = [(64, n) for n in (1, 31, 32, 33, 64, 65, 127, 128, 129, 160, 193, 255, 256)] + [(128, n) for n in (1, 33, 64, 97, 128)]
+
+
+def _both(call, like):
+    out = []
+    try:
+        for mode in (2, 0):  # two launches, the choice
+            sa.sattn_set_bwd_merged(mode)
+            res = [torch.full_like(x, float("nan")) for x in like]
+            call(*res)
+            torch.cuda.synchronize()
+            out.append(res)
+    finally:
+        sa.sattn_set_bwd_merged(0)
+    return out
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d,N", SIZES)
+def test_dense_equals_two_launches_and_the_oracle(d, N, causal):
+    B = 9
+    g = torch.Generator().manual_seed(100 * N + d)
+    q, k, v, do = (torch.randn(B, N, HEADS, d, generator=g).bfloat16() for _ in range(4))
+    bias = -math.log(max(N, 2))
+    dev = [x.cuda().transpose(1, 2) for x in (q, k, v, do)]  # [B, N, H, d] storage
+    two, one = _both(lambda *r: sa.sigmoid_attn_bwd(*dev, *r, bias, causal), dev[:3])
+    for a, b in zip(two, one):
+        assert torch.equal(a, b) and not torch.isnan(b).any()
+    few = [x[:1, :2].contiguous() for x in dev]
+    ref = orc.sigmoid_attn_bwd(*(x.cpu() for x in few), bias, causal)
+    for x, r in zip(one, ref):
+        assert np.abs(x[:1, :2].float().cpu().numpy() - r).max() <= TOL * np.abs(r).max()
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d,lengths", [(64, [256, 1, 0, 33, 250]), (64, [128, 64, 127]), (128, [128, 5, 0, 96])])
+def test_packed_equals_two_launches_and_leaves_other_rows_alone(d, lengths, causal):
+    total, B = sum(lengths), len(lengths)
+    g = torch.Generator().manual_seed(total + d)
+    q, k, v, do = (torch.randn(total + 64, 64, d, generator=g).bfloat16().cuda() for _ in range(4))
+    cu = torch.tensor([sum(lengths[:i]) for i in range(B + 1)], dtype=torch.int32, device="cuda")
+    bias = torch.tensor([-math.log(max(n, 2)) for n in lengths], dtype=torch.float32, device="cuda")
+    two, one = _both(lambda *r: sa.sigmoid_attn_varlen_bwd(q, k, v, do, *r, cu, max(lengths), 0.0, causal, None,
+                                                           bias_per_seq=bias), [q, k, v])
+    for a, b in zip(two, one):
+        assert torch.equal(a[:total], b[:total]) and not torch.isnan(b[:total]).any()
+        assert torch.isnan(b[total:]).all()
