@@ -241,14 +241,20 @@ bool pick_bwd_merged(int B, int H, int N, int causal, bool two_per_cu, bool pack
   return (places - pairs) * 25 > places;
 }
 
-// The backward that holds a head whole (sattn_bwd_short.hpp): wherever two of its workgroups share a
-// compute unit (d = 64, 128 keys: 5.9 us against 7.5 with 16 heads of 64); the larger ones only from more
-// heads than half the units on.  Below, the two passes' four workgroups a head (two at d = 128) all find
-// a place at once and share the work further: N250 d64 16 heads 12.6 / 17.1 us, 64 heads 13.3 / 17.9, 144
-// heads 24.3 / 18.9; N128 d128 16 heads 12.0 / 12.6, 144 heads 21.2 / 14.7.
-bool pick_bwd_short(int64_t heads, int N, int d) {
+// The backward that holds a head whole (sattn_bwd_short.hpp), for every sequence short enough but where
+// the two passes' four workgroups a head all find a place at once and nothing is masked: N250 d64 16
+// heads 12.5 us against 13.2, 64 heads 13.1 / 13.8 (causal, 128 heads: 16.4 / 14.7; N128: 9.3 / 7.2).
+bool pick_bwd_short(int64_t heads, int N, int d, int causal) {
   if (g_bwd_merged.load(std::memory_order_relaxed) != 0 || N > (d == 64 ? 256 : 128)) return false;
-  return (d == 64 && N <= 128) || 2 * heads > compute_units();
+  return d == 128 || N <= 128 || causal || 2 * heads > compute_units();
+}
+// Its heads that take one workgroup.  What is left over after whole rounds of the chip takes two, one
+// for dK and dV and one for dQ, where these still fit one round (us, one / two workgroups for
+// the rest: 384 heads N250 d64 36.6 / 34.3, 16 heads 16.2 / 13.2; 384 heads N100 d128 30.6 / 28.6; where
+// they do not fit: 144 heads N250 17.9 / 22.9).
+int short_whole_heads(int64_t heads, int N, int d) {
+  const int64_t places = (int64_t)compute_units() * (d == 64 && N <= 128 ? 2 : 1), rest = heads % places;
+  return (int)(2 * rest <= places ? heads - rest : heads);
 }
 
 // Workgroups over which the dK/dV pass splits the query heads of one K/V head (a power of two
@@ -554,8 +560,11 @@ int bwd_impl(const BwdArgs& a) {
     p.nlse2 = nlse2; p.dvec = dvec; p.npad = npad;
   }
   if (!SOFTMAX && PIN && !in_place && !alibi && !a.db_rows && Hkv == a.H && Nk == a.N && a.parts == (kBwdDkDv | kBwdDq) &&
-      pick_bwd_short((int64_t)a.B * a.H, a.N, a.d))
-    return a.d == 128 ? launch_bwd_short<128>(p, a.causal, st) : launch_bwd_short<64>(p, a.causal, st);
+      pick_bwd_short((int64_t)a.B * a.H, a.N, a.d, a.causal))
+  {
+    const int whole = short_whole_heads((int64_t)a.B * a.H, a.N, a.d);
+    return a.d == 128 ? launch_bwd_short<128>(p, a.causal, whole, st) : launch_bwd_short<64>(p, a.causal, whole, st);
+  }
   const bool merged = !in_place && pick_bwd_merged(a.B, a.H, a.N, a.causal, a.d == 64 && !SOFTMAX, a.cu_seqlens != nullptr);
   int n_split = 1;
   if (a.group_split && !SOFTMAX && PIN && Hkv != a.H && !a.cu_seqlens && Nk == a.N && (a.parts & kBwdDkDv)) {

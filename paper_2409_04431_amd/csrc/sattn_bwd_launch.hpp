@@ -83,14 +83,15 @@ int launch_bwd_variant(BwdParams p, int causal, bool alibi, int parts, bool merg
 }
 
 template <int D>
-int launch_bwd_short(const BwdParams& p, int causal, hipStream_t st) {
+int launch_bwd_short(const BwdParams& p, int causal, int whole, hipStream_t st) {
+  const dim3 grid(2 * p.B * p.H - whole);
   if constexpr (D == 64) {
     if (p.N > 128)
-      return causal ? launch(attn_bwd_short_kernel<D, 8, true>, dim3(p.B * p.H), dim3(512), short_lds_bytes<D, 8>(), st, p)
-                    : launch(attn_bwd_short_kernel<D, 8, false>, dim3(p.B * p.H), dim3(512), short_lds_bytes<D, 8>(), st, p);
+      return causal ? launch(attn_bwd_short_kernel<D, 8, true>, grid, dim3(512), short_lds_bytes<D, 8>(), st, p, whole)
+                    : launch(attn_bwd_short_kernel<D, 8, false>, grid, dim3(512), short_lds_bytes<D, 8>(), st, p, whole);
   }
-  return causal ? launch(attn_bwd_short_kernel<D, 4, true>, dim3(p.B * p.H), dim3(256), short_lds_bytes<D, 4>(), st, p)
-                : launch(attn_bwd_short_kernel<D, 4, false>, dim3(p.B * p.H), dim3(256), short_lds_bytes<D, 4>(), st, p);
+  return causal ? launch(attn_bwd_short_kernel<D, 4, true>, grid, dim3(256), short_lds_bytes<D, 4>(), st, p, whole)
+                : launch(attn_bwd_short_kernel<D, 4, false>, grid, dim3(256), short_lds_bytes<D, 4>(), st, p, whole);
 }
 
 template <int D>

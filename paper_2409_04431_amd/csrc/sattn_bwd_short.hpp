@@ -9,12 +9,16 @@
 // 32 features, each summed over all keys in ascending order: the additions of the dQ pass, so that results are
 // the two passes' bit for bit.  Q, dO and K are in LDS once and for all, read by rows and transposed.
 //
-// What bounds it: vector issue, about 1200 cycles per 32 x 32 chunk and SIMD against 850 of its
-// instructions (the compiler's order; the second wave of a SIMD fills it), and around it 4 to 5 us of
-// first loads, one workgroup's 160 KB of LDS leaving no room for another's.  Up to 128 keys two workgroups
-// share a compute unit.  Measured (us, one grid of the two passes / this): B32 H12 N250 d64 44.0 / 38.9,
-// causal 40.9 / 33.5; B64 H16 N250 104 / 82.8; B32 H12 N128 18.4 / 14.3; B64 H16 N64 31.4 / 17.2;
-// B32 H16 N128 d128 52.9 / 35.6; B64 H32 N64 d128 137 / 69.1.
+// Heads beyond whole rounds of the chip leave most of a last round empty; those take two
+// workgroups, one for dK and dV and one for dQ (which then has to form S and dP again).
+//
+// What bounds it: 1350 cycles per 32 x 32 chunk and SIMD against 850 of its vector issue (the compiler's
+// order, filled by the second wave of a SIMD; the next chunk's rows are read under the arithmetic of
+// this one: N250 38.9 -> 36.5 us), and around it 4 to 5 us of first loads at the memory's rate, one
+// workgroup's 160 KB of LDS leaving no room for another's.  Up to 128 keys two workgroups share a compute unit.
+// Measured (us, one grid of the two passes / this): B32 H12 N250 d64 43.5 / 34.3, causal 40.9 / 32.7; B64 H16
+// N250 107 / 79.8; B32 H12 N128 18.1 / 13.6; B64 H16 N64 31.4 / 16.5; B4 H4 N64 7.5 / 5.3; B32 H16 N128 d128
+// 54.7 / 35.9; B16 H16 N70 d128 22.3 / 13.2; B64 H32 N64 d128 137 / 70.
 #pragma once
 #include "sattn_bwd.hpp"
 
@@ -24,35 +28,62 @@ namespace sattn {
 template <int D, int NW>
 constexpr size_t short_lds_bytes() { return (size_t)NW * 32 * D * 2 * 3 + (size_t)NW * 32 * 128 * 2; }
 
-template <int D, int NW, bool CAUSAL>
-__global__ void __launch_bounds__(64 * NW, D == 64 ? 2 : 1) attn_bwd_short_kernel(const BwdParams p) {
+// What a workgroup finds of its head.
+struct ShortHead {
+  int N;
+  float nbias;
+  int64_t tok0;
+  int b, hd;
+  __device__ __forceinline__ __bf16* of(const TensorRef& t) const { return (__bf16*)t.ptr + b * t.sb + hd * t.sh + tok0 * t.ss; }
+};
+
+// Zeros in the rows from N on of a 64-row tile that starts at row 64 t.
+template <int D, int NW>
+__device__ __forceinline__ void short_pad(uint32_t tile, int t, int N, int tid) {
+  for (int i = tid; i < (64 * (t + 1) - N) * (D / 8); i += 64 * NW)
+    lds_write_b128(tile + ((N & 63) + i / (D / 8)) * (D * 2) + (i % (D / 8)) * 16, u32x4{0, 0, 0, 0});
+}
+
+// The 32 rows of a wave.  Under the mask the waves of a SIMD (w, w + 4) get blocks whose work adds up
+// to the same.
+template <int NW, bool CAUSAL>
+__device__ __forceinline__ int short_block(int wave) { return (CAUSAL && NW == 8 && wave >= 4) ? 11 - wave : wave; }
+
+// Per-lane LDS offsets: rows of a 32-row chunk, transposed pairs of a 64-row tile.
+template <int D>
+struct ShortLanes {
+  uint32_t row[D / 16], tr[D / 32][2];
+  __device__ __forceinline__ void init(int lane) {
+    const int l32 = lane & 31, h = lane >> 5, kap = kappa(l32), i16 = lane & 15, blk1 = (lane >> 4) & 1;
+#pragma unroll
+    for (int kk = 0; kk < D / 16; ++kk) row[kk] = kap * (D * 2) + (((2 * kk + h) ^ SwzX<D>::f(kap)) << 4);
+#pragma unroll
+    for (int rd = 0; rd < 2; ++rd) {
+      const int r = 8 * h + 4 * rd + (i16 >> 2), c = 2 * blk1 + ((i16 & 3) >> 1);
+#pragma unroll
+      for (int dt = 0; dt < D / 32; ++dt) tr[dt][rd] = r * (D * 2) + (((4 * dt + c) ^ SwzX<D>::f(r)) << 4) + ((i16 & 1) << 3);
+    }
+  }
+};
+
+// dK, dV and, with DQ, dQ of a head.
+template <int D, int NW, bool CAUSAL, bool DQ>
+__device__ __forceinline__ void short_dkdv(const BwdParams& p, const ShortHead& hd, uint32_t lds0, ClockStart& clk) {
   constexpr int KD = D / 16, DT = D / 32, MAXN = 32 * NW, TILE = 64 * D * 2, SLOT = 2 * TILE;
   constexpr int N_SUB = 4 * DT / NW, SUB_STEP = NW / DT;  // dQ tiles (32 queries x 32 features) of a wave per 128 queries
   static_assert(NW % DT == 0 && N_SUB >= 1, "a wave keeps one tile of features");
-  extern __shared__ __attribute__((aligned(1024))) char smem[];
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(SATTN_LDS(char)*)smem;
   const uint32_t lds_k = lds0 + (MAXN / 64) * SLOT, lds_ds = lds_k + (MAXN / 64) * TILE;
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  ClockStart clk = clock_probe_begin(p.clock);
-  const int bh = blockIdx.x, b = bh / p.H, hd = bh - b * p.H;
-  int N = p.N;
-  int64_t tok0 = 0;
-  float nbias = p.nbias_log2;
-  if (p.cu_seqlens) {
-    tok0 = p.cu_seqlens[b];
-    N = min(p.cu_seqlens[b + 1] - (int)tok0, p.N);
-    if (p.bias_vec) nbias = -p.bias_vec[b] * kLog2e;
-    if (N <= 0) return;
-  }
-  auto base = [&](const TensorRef& t) { return (__bf16*)t.ptr + b * t.sb + hd * t.sh + tok0 * t.ss; };
-  const __bf16 *kb = base(p.k), *vb = base(p.v);
+  const int N = hd.N;
+  const float nbias = hd.nbias;
+  const __bf16 *kb = hd.of(p.k), *vb = hd.of(p.v);
 
   // ---- K, the first 128 queries and this wave's V rows; the other queries follow while these are worked on
   const int n_tiles = (N + 63) / 64, n_chunks = (N + 31) / 32;
   DmaStagerX<D, NW> sq, sd;
-  sq.init(base(p.q), p.q.ss, N, 0, wave, lane);
-  sd.init(base(p.dout), p.dout.ss, N, 0, wave, lane);
+  sq.init(hd.of(p.q), p.q.ss, N, 0, wave, lane);
+  sd.init(hd.of(p.dout), p.dout.ss, N, 0, wave, lane);
   auto stage = [&](int t0, int t1) {
     for (int t = t0; t < t1; ++t) {
       sq.issue(lds0 + t * SLOT, N, wave, lane);
@@ -65,9 +96,7 @@ __global__ void __launch_bounds__(64 * NW, D == 64 ? 2 : 1) attn_bwd_short_kerne
     for (int t = 0; t < n_tiles; ++t) sk.issue(lds_k + t * TILE, N, wave, lane);
   }
   stage(0, min(n_tiles, 2));
-  // Causal: wave w's keys meet the queries from theirs on; the waves of a SIMD (w, w + 4) get key
-  // blocks whose work adds up to the same.
-  const int kblk = (CAUSAL && NW == 8 && wave >= 4) ? 11 - wave : wave;
+  const int kblk = short_block<NW, CAUSAL>(wave);
   const int key0 = 32 * kblk, key = key0 + l32, key_ld = key < N ? key : N - 1;
   bf16x8 x1[KD], x2[KD];
 #pragma unroll
@@ -83,26 +112,20 @@ __global__ void __launch_bounds__(64 * NW, D == 64 ? 2 : 1) attn_bwd_short_kerne
 #pragma unroll
     for (int r = 0; r < 16; ++r) dk[dt][r] = dv[dt][r] = 0.f;
 
-  // per-lane LDS addresses: rows of a chunk, transposed reads of a tile, of the keys and of dS
-  const int kap = kappa(l32), i16 = lane & 15, blk1 = (lane >> 4) & 1;
-  uint32_t row[KD], tr[DT][2], ds_rd[2];
-#pragma unroll
-  for (int kk = 0; kk < KD; ++kk) row[kk] = kap * (D * 2) + (((2 * kk + h) ^ SwzX<D>::f(kap)) << 4);
+  ShortLanes<D> at_lane;
+  at_lane.init(lane);
+  const auto& row = at_lane.row;
+  const auto& tr = at_lane.tr;
+  uint32_t ds_rd[2];  // transposed reads of dS (queries 32..63 of a row: bit 6 flipped)
 #pragma unroll
   for (int rd = 0; rd < 2; ++rd) {
-    const int r = 8 * h + 4 * rd + (i16 >> 2), c = 2 * blk1 + ((i16 & 3) >> 1);
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt) tr[dt][rd] = r * (D * 2) + (((4 * dt + c) ^ SwzX<D>::f(r)) << 4) + ((i16 & 1) << 3);
-    ds_rd[rd] = r * 128 + ((c ^ SwzX<64>::f(r)) << 4) + ((i16 & 1) << 3);  // (queries 32..63 of a row: bit 6 flipped)
+    const int i16 = lane & 15, r = 8 * h + 4 * rd + (i16 >> 2), c = 2 * ((lane >> 4) & 1) + ((i16 & 3) >> 1);
+    ds_rd[rd] = r * 128 + ((c ^ SwzX<64>::f(r)) << 4) + ((i16 & 1) << 3);
   }
   const uint32_t ds_wr = lds_ds + key * 128 + ((h ^ SwzX<64>::f(key)) << 4);
 
   // Rows past the end are zeros in dO and K: the queries there add nothing to dK and dV, the keys
   // nothing to dQ, without a mask.
-  auto pad = [&](uint32_t tile, int t) {
-    for (int i = tid; i < (64 * (t + 1) - N) * (D / 8); i += 64 * NW)
-      lds_write_b128(tile + ((N & 63) + i / (D / 8)) * (D * 2) + (i % (D / 8)) * 16, u32x4{0, 0, 0, 0});
-  };
   SATTN_WAIT_VMCNT(0);
   stage(2, n_tiles);
   __syncthreads();
@@ -113,14 +136,24 @@ __global__ void __launch_bounds__(64 * NW, D == 64 ? 2 : 1) attn_bwd_short_kerne
     for (int kk = 0; kk < KD; ++kk) x1[kk] = as_bf16x8(lds_read_b128(lds_k + at * (D * 2) + (((2 * kk + h) ^ SwzX<D>::f(at)) << 4)));
   }
   if (n_tiles * 64 > N) {
-    pad(lds_k + (n_tiles - 1) * TILE, n_tiles - 1);
-    if (n_tiles <= 2) pad(lds0 + (n_tiles - 1) * SLOT + TILE, n_tiles - 1);
+    short_pad<D, NW>(lds_k + (n_tiles - 1) * TILE, n_tiles - 1, N, tid);
+    if (n_tiles <= 2) short_pad<D, NW>(lds0 + (n_tiles - 1) * SLOT + TILE, n_tiles - 1, N, tid);
     __syncthreads();
   }
 
+  bf16x8 f1[KD], f2[KD];  // row fragments of the next chunk
+  auto rows_of = [&](int c) {
+    const uint32_t at = lds0 + (c >> 1) * SLOT + (c & 1) * (32 * D * 2);
+#pragma unroll
+    for (int kk = 0; kk < KD; ++kk) {
+      f1[kk] = as_bf16x8(lds_read_b128(at + row[kk]));
+      f2[kk] = as_bf16x8(lds_read_b128(at + TILE + row[kk]));
+    }
+  };
   const int rounds = (N + 127) / 128, c_end = key0 < N ? n_chunks : 0;  // (a wave past the end has no chunk)
   for (int rnd = 0; rnd < rounds; ++rnd) {
     const int c_lo = CAUSAL ? max(4 * rnd, kblk) : 4 * rnd, c_hi = min(4 * rnd + 4, c_end);
+    if (c_lo < c_hi) rows_of(c_lo);
 #pragma nounroll
     for (int c = c_lo; c < c_hi; ++c) {
       const uint32_t at = lds0 + (c >> 1) * SLOT + (c & 1) * (32 * D * 2);
@@ -129,9 +162,20 @@ __global__ void __launch_bounds__(64 * NW, D == 64 ? 2 : 1) attn_bwd_short_kerne
       for (int r = 0; r < 16; ++r) s[r] = dp[r] = 0.f;
 #pragma unroll
       for (int kk = 0; kk < KD; ++kk) {
-        s = mfma32(as_bf16x8(lds_read_b128(at + row[kk])), x1[kk], s);
-        dp = mfma32(as_bf16x8(lds_read_b128(at + TILE + row[kk])), x2[kk], dp);
+        s = mfma32(f1[kk], x1[kk], s);
+        dp = mfma32(f2[kk], x2[kk], dp);
       }
+      // (the transposed fragments of this chunk and the rows of the next one come in under the arithmetic)
+      bf16x8 t1[2][DT], t2[2][DT];
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) {
+          const uint32_t off = at + ks * 16 * (D * 2);
+          t2[ks][dt] = join_tr(lds_read_tr16(off + TILE + tr[dt][0]), lds_read_tr16(off + TILE + tr[dt][1]));
+          t1[ks][dt] = join_tr(lds_read_tr16(off + tr[dt][0]), lds_read_tr16(off + tr[dt][1]));
+        }
+      rows_of(min(c + 1, c_hi - 1));
       float pr[16], ds[16];
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
@@ -152,14 +196,15 @@ __global__ void __launch_bounds__(64 * NW, D == 64 ? 2 : 1) attn_bwd_short_kerne
       for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) {
-          const uint32_t off = at + ks * 16 * (D * 2);
-          dv[dt] = mfma32(join_tr(lds_read_tr16(off + TILE + tr[dt][0]), lds_read_tr16(off + TILE + tr[dt][1])), pb[ks], dv[dt]);
-          dk[dt] = mfma32(join_tr(lds_read_tr16(off + tr[dt][0]), lds_read_tr16(off + tr[dt][1])), dsb[ks], dk[dt]);
+          dv[dt] = mfma32(t2[ks][dt], pb[ks], dv[dt]);
+          dk[dt] = mfma32(t1[ks][dt], dsb[ks], dk[dt]);
         }
+      if constexpr (DQ) {
       // dS, keys by queries: rows of 64 queries of a key, two such tiles
       const uint32_t to = (ds_wr ^ ((c & 1) << 6)) + ((c >> 1) & 1) * (MAXN * 128);
       lds_write_b128(to, __builtin_bit_cast(u32x4, dsb[0]));
       lds_write_b128(to ^ 32, __builtin_bit_cast(u32x4, dsb[1]));
+      }
     }
     if (rnd == 0) {
       clock_probe_mark(p.clock, clk, kMarkSteadyBegin);
@@ -167,7 +212,8 @@ __global__ void __launch_bounds__(64 * NW, D == 64 ? 2 : 1) attn_bwd_short_kerne
     }
     __syncthreads();
     if (rnd == 0) clock_probe_mark(p.clock, clk, kMarkSteadyEnd);
-    if (rnd == 0 && n_tiles > 2 && n_tiles * 64 > N) pad(lds0 + (n_tiles - 1) * SLOT + TILE, n_tiles - 1);
+    if (rnd == 0 && n_tiles > 2 && n_tiles * 64 > N) short_pad<D, NW>(lds0 + (n_tiles - 1) * SLOT + TILE, n_tiles - 1, N, tid);
+    if constexpr (DQ) {
     // dQ of these 128 queries: this wave's tile of features, all keys
     const int dt = wave % DT;
     const uint32_t kt0 = lds_k + tr[0][0], kt1 = lds_k + tr[0][1];
@@ -200,7 +246,7 @@ __global__ void __launch_bounds__(64 * NW, D == 64 ? 2 : 1) attn_bwd_short_kerne
       }
       const int q = 32 * c + l32;
       if (q < N) {
-        __bf16* out = base(p.dq) + (int64_t)q * p.dq.ss + 32 * dt + 4 * h;
+        __bf16* out = hd.of(p.dq) + (int64_t)q * p.dq.ss + 32 * dt + 4 * h;
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           u32x2 w;
@@ -210,15 +256,131 @@ __global__ void __launch_bounds__(64 * NW, D == 64 ? 2 : 1) attn_bwd_short_kerne
         }
       }
     }
+    }
     __syncthreads();
   }
   clock_probe_mark(p.clock, clk, kMarkStore);
   const uint32_t obuf = lds0 + wave * (2 * RowStore<D>::BYTES);
   static_assert(NW * 2 * RowStore<D>::BYTES <= short_lds_bytes<D, NW>(), "outputs leave through the same LDS");
-  RowStore<D>::run(dk, p.inv_sqrt_d, obuf, lane, base(p.dk) + (int64_t)key0 * p.dk.ss, p.dk.ss, N - key0);
-  RowStore<D>::run(dv, 1.0f, obuf + RowStore<D>::BYTES, lane, base(p.dv) + (int64_t)key0 * p.dv.ss, p.dv.ss, N - key0);
+  RowStore<D>::run(dk, p.inv_sqrt_d, obuf, lane, hd.of(p.dk) + (int64_t)key0 * p.dk.ss, p.dk.ss, N - key0);
+  RowStore<D>::run(dv, 1.0f, obuf + RowStore<D>::BYTES, lane, hd.of(p.dv) + (int64_t)key0 * p.dv.ss, p.dv.ss, N - key0);
   clk.tiles = n_tiles;
-  clock_probe_end(p.clock, clk, bh);
+}
+
+// dQ alone: a wave owns 32 queries (Q, dO fragments, the dQ^T accumulators) and goes through the keys,
+// whose rows P^T and dS^T have in registers: S^T = K Q^T, dP^T = V dO^T, dQ^T += K^T dS^T.
+template <int D, int NW, bool CAUSAL>
+__device__ __forceinline__ void short_dq(const BwdParams& p, const ShortHead& hd, uint32_t lds0, ClockStart& clk) {
+  constexpr int KD = D / 16, DT = D / 32, TILE = 64 * D * 2, SLOT = 2 * TILE;
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int N = hd.N, n_tiles = (N + 63) / 64, n_chunks = (N + 31) / 32;
+  {
+    DmaStagerX<D, NW> sk, sv;
+    sk.init(hd.of(p.k), p.k.ss, N, 0, wave, lane);
+    sv.init(hd.of(p.v), p.v.ss, N, 0, wave, lane);
+    for (int t = 0; t < n_tiles; ++t) {
+      sk.issue(lds0 + t * SLOT, N, wave, lane);
+      sv.issue(lds0 + t * SLOT + TILE, N, wave, lane);
+    }
+  }
+  const int qblk = short_block<NW, CAUSAL>(wave), q0 = 32 * qblk, q_ld = min(q0 + l32, N - 1);
+  const __bf16 *qb = hd.of(p.q), *dob = hd.of(p.dout);
+  bf16x8 x1[KD], x2[KD];
+#pragma unroll
+  for (int kk = 0; kk < KD; ++kk) {
+    x1[kk] = as_bf16x8(*(const u32x4*)(qb + (int64_t)q_ld * p.q.ss + 16 * kk + 8 * h));
+    x2[kk] = as_bf16x8(*(const u32x4*)(dob + (int64_t)q_ld * p.dout.ss + 16 * kk + 8 * h));
+  }
+  f32x16 dq[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) dq[dt][r] = 0.f;
+  ShortLanes<D> at_lane;
+  at_lane.init(lane);
+  SATTN_WAIT_VMCNT(0);
+  __syncthreads();
+  clock_probe_mark(p.clock, clk, kMarkFirstProduct);
+  if (n_tiles * 64 > N) {  // keys past the end add nothing
+    const uint32_t last = lds0 + (n_tiles - 1) * SLOT;
+    short_pad<D, NW>(last, n_tiles - 1, N, tid);
+    short_pad<D, NW>(last + TILE, n_tiles - 1, N, tid);
+    __syncthreads();
+  }
+  const int c_hi = q0 < N ? (CAUSAL ? qblk + 1 : n_chunks) : 0;
+  bf16x8 f1[KD], f2[KD];
+  auto rows_of = [&](int c) {
+    const uint32_t at = lds0 + (c >> 1) * SLOT + (c & 1) * (32 * D * 2);
+#pragma unroll
+    for (int kk = 0; kk < KD; ++kk) {
+      f1[kk] = as_bf16x8(lds_read_b128(at + at_lane.row[kk]));
+      f2[kk] = as_bf16x8(lds_read_b128(at + TILE + at_lane.row[kk]));
+    }
+  };
+  if (c_hi > 0) rows_of(0);
+#pragma nounroll
+  for (int c = 0; c < c_hi; ++c) {
+    const uint32_t at = lds0 + (c >> 1) * SLOT + (c & 1) * (32 * D * 2);
+    f32x16 s, dp;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = dp[r] = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < KD; ++kk) {
+      s = mfma32(f1[kk], x1[kk], s);
+      dp = mfma32(f2[kk], x2[kk], dp);
+    }
+    rows_of(min(c + 1, c_hi - 1));
+    float ds[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], p.nscale_log2, hd.nbias));
+      const float w = __builtin_amdgcn_rcpf(1.0f + e);
+      ds[r] = __builtin_fmaf(-w, w, w) * dp[r];
+    }
+    if (CAUSAL && c == qblk) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) ds[r] = key_of_reg(r) + 8 * h <= l32 ? ds[r] : 0.f;
+    }
+    const bf16x8 dsb[2] = {pack8(ds), pack8(ds + 8)};
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) {
+        const uint32_t off = at + ks * 16 * (D * 2);
+        dq[dt] = mfma32(join_tr(lds_read_tr16(off + at_lane.tr[dt][0]), lds_read_tr16(off + at_lane.tr[dt][1])), dsb[ks], dq[dt]);
+      }
+  }
+  __syncthreads();
+  clock_probe_mark(p.clock, clk, kMarkStore);
+  RowStore<D>::run(dq, p.inv_sqrt_d, lds0 + wave * RowStore<D>::BYTES, lane, hd.of(p.dq) + (int64_t)q0 * p.dq.ss, p.dq.ss, N - q0);
+  clk.tiles = n_tiles;
+}
+
+// Heads below `whole` take a workgroup each, the others two: dK and dV first, then dQ.
+template <int D, int NW, bool CAUSAL>
+__global__ void __launch_bounds__(64 * NW, D == 64 ? 2 : 1) attn_bwd_short_kernel(const BwdParams p, const int whole) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(SATTN_LDS(char)*)smem;
+  ClockStart clk = clock_probe_begin(p.clock);
+  const int rest = p.B * p.H - whole, i = (int)blockIdx.x - whole;  // i < 0: a whole head
+  const int bh = i < rest ? (int)blockIdx.x : whole + i - rest;
+  ShortHead hd;
+  hd.b = bh / p.H;
+  hd.hd = bh - hd.b * p.H;
+  hd.N = p.N;
+  hd.tok0 = 0;
+  hd.nbias = p.nbias_log2;
+  if (p.cu_seqlens) {
+    hd.tok0 = p.cu_seqlens[hd.b];
+    hd.N = min(p.cu_seqlens[hd.b + 1] - (int)hd.tok0, p.N);
+    if (p.bias_vec) hd.nbias = -p.bias_vec[hd.b] * kLog2e;
+    if (hd.N <= 0) return;
+  }
+  if (i < 0) short_dkdv<D, NW, CAUSAL, true>(p, hd, lds0, clk);
+  else if (i < rest) short_dkdv<D, NW, CAUSAL, false>(p, hd, lds0, clk);
+  else short_dq<D, NW, CAUSAL>(p, hd, lds0, clk);
+  clock_probe_end(p.clock, clk, (int)blockIdx.x);
 }
 
 }  // namespace sattn

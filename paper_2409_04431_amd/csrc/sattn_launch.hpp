@@ -76,8 +76,9 @@ template <int D>
 int launch_bwd_bf16(BwdParams p, bool softmax, bool pin, int causal, bool alibi, int parts, bool merged,
                     hipStream_t st);
 
-// Backward of sequences that one workgroup holds whole (sattn_bwd_short.hpp).
+// Backward of sequences that one workgroup holds whole (sattn_bwd_short.hpp); heads from `whole` on are
+// shared by two.
 template <int D>
-int launch_bwd_short(const BwdParams& p, int causal, hipStream_t st);
+int launch_bwd_short(const BwdParams& p, int causal, int whole, hipStream_t st);
 
 }  // namespace sattn

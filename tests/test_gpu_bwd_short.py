@@ -11,7 +11,8 @@ from oracle import sattn_oracle as orc
 
 pytestmark = pytest.mark.gpu
 TOL = 2e-2  # P, dS and the outputs are rounded to bf16
-HEADS = 17  # odd batches of it lie on both sides of the rule's line
+HEADS = 17  # on 256 compute units 3 batches of it are shared by two workgroups a head, 9 are not at N > 128
+            # (d = 128: at any N), of 21 some are
 
 SIZES = [(64, n) for n in (1, 31, 32, 33, 64, 65, 127, 128, 129, 160, 193, 255, 256)] + [(128, n) for n in (1, 33, 64, 97, 128)]
 
@@ -32,8 +33,8 @@ def _both(call, like):
 
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("d,N", SIZES)
-def test_dense_equals_two_launches_and_the_oracle(d, N, causal):
-    B = 9
+@pytest.mark.parametrize("B", [3, 9, 21])
+def test_dense_equals_two_launches_and_the_oracle(B, d, N, causal):
     g = torch.Generator().manual_seed(100 * N + d)
     q, k, v, do = (torch.randn(B, N, HEADS, d, generator=g).bfloat16() for _ in range(4))
     bias = -math.log(max(N, 2))
