@@ -243,9 +243,11 @@ bool pick_bwd_merged(int B, int H, int N, int causal, bool two_per_cu, bool pack
 
 // The backward that holds a head whole (sattn_bwd_short.hpp), for every sequence short enough but where
 // the two passes' four workgroups a head all find a place at once and nothing is masked: N250 d64 16
-// heads 12.5 us against 13.2, 64 heads 13.1 / 13.8 (causal, 128 heads: 16.4 / 14.7; N128: 9.3 / 7.2).
-bool pick_bwd_short(int64_t heads, int N, int d, int causal) {
-  if (g_bwd_merged.load(std::memory_order_relaxed) != 0 || N > (d == 64 ? 256 : 128)) return false;
+// heads 12.5 us against 13.2, 64 heads 13.1 / 13.8 (causal, 128 heads: 16.4 / 14.7; N128: 9.3 / 7.2).  With
+// the row sums of dS (`rows`) every head takes two workgroups, which pays up to 128 tokens (64 heads
+// 9.3 / 7.3, 384: 18.1 / 15.3; d128 512 heads 54.7 / 50.3), not beyond (384 heads N250 43.5 / 44.3).
+bool pick_bwd_short(int64_t heads, int N, int d, int causal, bool rows) {
+  if (g_bwd_merged.load(std::memory_order_relaxed) != 0 || N > (d == 64 && !rows ? 256 : 128)) return false;
   return d == 128 || N <= 128 || causal || 2 * heads > compute_units();
 }
 // Its heads that take one workgroup.  What is left over after whole rounds of the chip takes two, one
@@ -478,6 +480,16 @@ struct BwdArgs {
   bool group_split = false;                                          // shared K/V heads: split a group over workgroups (workspace)
 };
 
+// The bias gradient per head from the row sums of dS.
+template <typename Params>
+int reduce_rows(const BwdArgs& a, const Params& p, hipStream_t st) {
+  if (a.cu_seqlens)
+    return launch(rowsum_reduce_varlen_kernel, dim3(a.B * a.H), dim3(256), 0, st, (const float*)a.db_rows, a.db,
+                  a.cu_seqlens, a.H, a.db_tokens, a.N);
+  return launch(rowsum_reduce_kernel, dim3(a.B * a.H), dim3(256), 0, st, (const float*)a.db_rows, a.db, a.H, a.N,
+                p.db_sb, p.db_sh);
+}
+
 template <bool SOFTMAX, bool PIN = true>
 int bwd_impl(const BwdArgs& a) {
   int rc = check_shape(a.B, a.H, a.N, a.d, a.dtype);
@@ -516,14 +528,7 @@ int bwd_impl(const BwdArgs& a) {
     if (a.cu_seqlens && a.db_rows) { p.db_sb = 0; p.db_sh = a.db_tokens; }  // [H, tokens], as in the bf16 path
     if (a.d == 128) rc = launch_bwd_f32<128>(p, a.causal, alibi, a.parts, !in_place, st);
     else rc = launch_bwd_f32<64>(p, a.causal, alibi, a.parts, !in_place, st);
-    if (rc == SATTN_OK && a.db) {
-      if (a.cu_seqlens)
-        rc = launch(rowsum_reduce_varlen_kernel, dim3(a.B * a.H), dim3(256), 0, st, (const float*)a.db_rows, a.db,
-                    a.cu_seqlens, a.H, a.db_tokens, a.N);
-      else
-        rc = launch(rowsum_reduce_kernel, dim3(a.B * a.H), dim3(256), 0, st, (const float*)a.db_rows, a.db, a.H, a.N,
-                    p.db_sb, p.db_sh);
-    }
+    if (rc == SATTN_OK && a.db) rc = reduce_rows(a, p, st);
     return rc;
   }
   BwdParams p{};
@@ -559,11 +564,11 @@ int bwd_impl(const BwdArgs& a) {
     if (rc) return rc;
     p.nlse2 = nlse2; p.dvec = dvec; p.npad = npad;
   }
-  if (!SOFTMAX && PIN && !in_place && !alibi && !a.db_rows && Hkv == a.H && Nk == a.N && a.parts == (kBwdDkDv | kBwdDq) &&
-      pick_bwd_short((int64_t)a.B * a.H, a.N, a.d, a.causal))
-  {
-    const int whole = short_whole_heads((int64_t)a.B * a.H, a.N, a.d);
-    return a.d == 128 ? launch_bwd_short<128>(p, a.causal, whole, st) : launch_bwd_short<64>(p, a.causal, whole, st);
+  if (!SOFTMAX && PIN && !in_place && Hkv == a.H && Nk == a.N && a.parts == (kBwdDkDv | kBwdDq) && !(alibi && (a.causal || a.db_rows)) &&
+      pick_bwd_short((int64_t)a.B * a.H, a.N, a.d, a.causal, a.db_rows != nullptr)) {
+    const int whole = a.db_rows ? 0 : short_whole_heads((int64_t)a.B * a.H, a.N, a.d);
+    rc = a.d == 128 ? launch_bwd_short<128>(p, a.causal, alibi, whole, st) : launch_bwd_short<64>(p, a.causal, alibi, whole, st);
+    return rc == SATTN_OK && a.db ? reduce_rows(a, p, st) : rc;
   }
   const bool merged = !in_place && pick_bwd_merged(a.B, a.H, a.N, a.causal, a.d == 64 && !SOFTMAX, a.cu_seqlens != nullptr);
   int n_split = 1;
@@ -590,14 +595,7 @@ int bwd_impl(const BwdArgs& a) {
            (int64_t)a.B * Hkv * n_split * ((std::min(a.N, Nk) + 127) / 128 / 2) >= compute_units();
   if (a.d == 128) rc = launch_bwd_bf16<128>(p, SOFTMAX, PIN, a.causal, alibi, a.parts, merged, st);
   else rc = launch_bwd_bf16<64>(p, SOFTMAX, PIN, a.causal, alibi, a.parts, merged, st);
-  if (rc == SATTN_OK && a.db) {
-    if (a.cu_seqlens)
-      rc = launch(rowsum_reduce_varlen_kernel, dim3(a.B * a.H), dim3(256), 0, st, (const float*)a.db_rows, a.db,
-                  a.cu_seqlens, a.H, a.db_tokens, a.N);
-    else
-      rc = launch(rowsum_reduce_kernel, dim3(a.B * a.H), dim3(256), 0, st, (const float*)a.db_rows, a.db, a.H, a.N,
-                  p.db_sb, p.db_sh);
-  }
+  if (rc == SATTN_OK && a.db) rc = reduce_rows(a, p, st);
   return rc;
 }
 

@@ -2,4 +2,4 @@
 #include "sattn_bwd_launch.hpp"
 
 template int sattn::launch_bwd_bf16<128>(sattn::BwdParams, bool, bool, int, bool, int, bool, hipStream_t);
-template int sattn::launch_bwd_short<128>(const sattn::BwdParams&, int, int, hipStream_t);
+template int sattn::launch_bwd_short<128>(const sattn::BwdParams&, int, bool, int, hipStream_t);

@@ -83,15 +83,22 @@ int launch_bwd_variant(BwdParams p, int causal, bool alibi, int parts, bool merg
 }
 
 template <int D>
-int launch_bwd_short(const BwdParams& p, int causal, int whole, hipStream_t st) {
+int launch_bwd_short(const BwdParams& p, int causal, bool alibi, int whole, hipStream_t st) {
   const dim3 grid(2 * p.B * p.H - whole);
+  auto run = [&](auto kernel, int waves, size_t lds) { return launch(kernel, grid, dim3(64 * waves), lds, st, p, whole); };
   if constexpr (D == 64) {
-    if (p.N > 128)
-      return causal ? launch(attn_bwd_short_kernel<D, 8, true>, grid, dim3(512), short_lds_bytes<D, 8>(), st, p, whole)
-                    : launch(attn_bwd_short_kernel<D, 8, false>, grid, dim3(512), short_lds_bytes<D, 8>(), st, p, whole);
+    if (p.N > 128) {
+      if (alibi) return run(attn_bwd_short_kernel<D, 8, false, true>, 8, short_lds_bytes<D, 8>());
+      return causal ? run(attn_bwd_short_kernel<D, 8, true>, 8, short_lds_bytes<D, 8>())
+                    : run(attn_bwd_short_kernel<D, 8, false>, 8, short_lds_bytes<D, 8>());
+    }
   }
-  return causal ? launch(attn_bwd_short_kernel<D, 4, true>, grid, dim3(256), short_lds_bytes<D, 4>(), st, p, whole)
-                : launch(attn_bwd_short_kernel<D, 4, false>, grid, dim3(256), short_lds_bytes<D, 4>(), st, p, whole);
+  constexpr size_t lds = short_lds_bytes<D, 4>();
+  if (p.db_rows)
+    return causal ? run(attn_bwd_short_kernel<D, 4, true, false, true>, 4, lds)
+                  : run(attn_bwd_short_kernel<D, 4, false, false, true>, 4, lds);
+  if (alibi) return run(attn_bwd_short_kernel<D, 4, false, true>, 4, lds);
+  return causal ? run(attn_bwd_short_kernel<D, 4, true>, 4, lds) : run(attn_bwd_short_kernel<D, 4, false>, 4, lds);
 }
 
 template <int D>

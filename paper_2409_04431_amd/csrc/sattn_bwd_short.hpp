@@ -1,5 +1,5 @@
 // Sigmoid-attention backward of sequences that one workgroup holds whole: up to 256 keys at d = 64,
-// 128 at d = 128 (bf16, no ALiBi).
+// 128 at d = 128 (bf16; ALiBi without a mask only: under it the passes add its terms in orders of their own).
 //
 // The two passes of sattn_bwd.hpp evaluate every logit, dP and sigmoid twice, because no workgroup
 // holds all keys a dQ row has to be summed over.  Here one does.  A wave owns 32 keys (K, V
@@ -31,7 +31,7 @@ constexpr size_t short_lds_bytes() { return (size_t)NW * 32 * D * 2 * 3 + (size_
 // What a workgroup finds of its head.
 struct ShortHead {
   int N;
-  float nbias;
+  float nbias, sl2;  // bias and ALiBi slope in the exponent of two
   int64_t tok0;
   int b, hd;
   __device__ __forceinline__ __bf16* of(const TensorRef& t) const { return (__bf16*)t.ptr + b * t.sb + hd * t.sh + tok0 * t.ss; }
@@ -67,7 +67,7 @@ struct ShortLanes {
 };
 
 // dK, dV and, with DQ, dQ of a head.
-template <int D, int NW, bool CAUSAL, bool DQ>
+template <int D, int NW, bool CAUSAL, bool ALIBI, bool DQ>
 __device__ __forceinline__ void short_dkdv(const BwdParams& p, const ShortHead& hd, uint32_t lds0, ClockStart& clk) {
   constexpr int KD = D / 16, DT = D / 32, MAXN = 32 * NW, TILE = 64 * D * 2, SLOT = 2 * TILE;
   constexpr int N_SUB = 4 * DT / NW, SUB_STEP = NW / DT;  // dQ tiles (32 queries x 32 features) of a wave per 128 queries
@@ -179,7 +179,8 @@ __device__ __forceinline__ void short_dkdv(const BwdParams& p, const ShortHead& 
       float pr[16], ds[16];
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], p.nscale_log2, nbias));
+        const float w = ALIBI ? __builtin_fmaf(hd.sl2, __builtin_fabsf((float)(32 * c + 8 * h + key_of_reg(r) - key)), nbias) : nbias;
+        const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], p.nscale_log2, w));
         pr[r] = __builtin_amdgcn_rcpf(1.0f + e);
         ds[r] = __builtin_fmaf(-pr[r], pr[r], pr[r]) * dp[r];
       }
@@ -267,9 +268,9 @@ __device__ __forceinline__ void short_dkdv(const BwdParams& p, const ShortHead& 
   clk.tiles = n_tiles;
 }
 
-// dQ alone: a wave owns 32 queries (Q, dO fragments, the dQ^T accumulators) and goes through the keys,
+// dQ alone (DB: and the row sums of dS, in the order of the dQ pass): a wave owns 32 queries (Q, dO fragments, the dQ^T accumulators) and goes through the keys,
 // whose rows P^T and dS^T have in registers: S^T = K Q^T, dP^T = V dO^T, dQ^T += K^T dS^T.
-template <int D, int NW, bool CAUSAL>
+template <int D, int NW, bool CAUSAL, bool ALIBI, bool DB>
 __device__ __forceinline__ void short_dq(const BwdParams& p, const ShortHead& hd, uint32_t lds0, ClockStart& clk) {
   constexpr int KD = D / 16, DT = D / 32, TILE = 64 * D * 2, SLOT = 2 * TILE;
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
@@ -308,6 +309,7 @@ __device__ __forceinline__ void short_dq(const BwdParams& p, const ShortHead& hd
     short_pad<D, NW>(last + TILE, n_tiles - 1, N, tid);
     __syncthreads();
   }
+  float dbs[4] = {0.f, 0.f, 0.f, 0.f};
   const int c_hi = q0 < N ? (CAUSAL ? qblk + 1 : n_chunks) : 0;
   bf16x8 f1[KD], f2[KD];
   auto rows_of = [&](int c) {
@@ -334,13 +336,19 @@ __device__ __forceinline__ void short_dq(const BwdParams& p, const ShortHead& hd
     float ds[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], p.nscale_log2, hd.nbias));
+      const float a = ALIBI ? __builtin_fmaf(hd.sl2, __builtin_fabsf((float)(q0 + l32 - (32 * c + 8 * h + key_of_reg(r)))), hd.nbias) : hd.nbias;
+      const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], p.nscale_log2, a));
       const float w = __builtin_amdgcn_rcpf(1.0f + e);
       ds[r] = __builtin_fmaf(-w, w, w) * dp[r];
     }
     if (CAUSAL && c == qblk) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) ds[r] = key_of_reg(r) + 8 * h <= l32 ? ds[r] : 0.f;
+    }
+    if constexpr (DB) {
+#pragma clang fp contract(off)  // (dS is rounded before it is added, as in the dQ pass)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) dbs[r & 3] += ds[r];
     }
     const bf16x8 dsb[2] = {pack8(ds), pack8(ds + 8)};
 #pragma unroll
@@ -351,14 +359,20 @@ __device__ __forceinline__ void short_dq(const BwdParams& p, const ShortHead& hd
         dq[dt] = mfma32(join_tr(lds_read_tr16(off + at_lane.tr[dt][0]), lds_read_tr16(off + at_lane.tr[dt][1])), dsb[ks], dq[dt]);
       }
   }
+  if constexpr (DB) {
+    float rs = (dbs[0] + dbs[1]) + (dbs[2] + dbs[3]);
+    rs += __shfl_xor(rs, 32);  // the two halves of the wave: different keys of the same query row
+    if (h == 0 && q0 + l32 < N) p.db_rows[hd.b * p.db_sb + hd.hd * p.db_sh + hd.tok0 + q0 + l32] = rs;
+  }
   __syncthreads();
   clock_probe_mark(p.clock, clk, kMarkStore);
   RowStore<D>::run(dq, p.inv_sqrt_d, lds0 + wave * RowStore<D>::BYTES, lane, hd.of(p.dq) + (int64_t)q0 * p.dq.ss, p.dq.ss, N - q0);
   clk.tiles = n_tiles;
 }
 
-// Heads below `whole` take a workgroup each, the others two: dK and dV first, then dQ.
-template <int D, int NW, bool CAUSAL>
+// Heads below `whole` take a workgroup each, the others two: dK and dV first, then dQ.  The row sums of dS
+// come with the latter (DB: whole = 0).
+template <int D, int NW, bool CAUSAL, bool ALIBI = false, bool DB = false>
 __global__ void __launch_bounds__(64 * NW, D == 64 ? 2 : 1) attn_bwd_short_kernel(const BwdParams p, const int whole) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const uint32_t lds0 = (uint32_t)(uintptr_t)(SATTN_LDS(char)*)smem;
@@ -371,15 +385,16 @@ __global__ void __launch_bounds__(64 * NW, D == 64 ? 2 : 1) attn_bwd_short_kerne
   hd.N = p.N;
   hd.tok0 = 0;
   hd.nbias = p.nbias_log2;
+  hd.sl2 = ALIBI ? p.slopes[hd.hd] * kLog2e : 0.f;
   if (p.cu_seqlens) {
     hd.tok0 = p.cu_seqlens[hd.b];
     hd.N = min(p.cu_seqlens[hd.b + 1] - (int)hd.tok0, p.N);
     if (p.bias_vec) hd.nbias = -p.bias_vec[hd.b] * kLog2e;
     if (hd.N <= 0) return;
   }
-  if (i < 0) short_dkdv<D, NW, CAUSAL, true>(p, hd, lds0, clk);
-  else if (i < rest) short_dkdv<D, NW, CAUSAL, false>(p, hd, lds0, clk);
-  else short_dq<D, NW, CAUSAL>(p, hd, lds0, clk);
+  if (!DB && i < 0) short_dkdv<D, NW, CAUSAL, ALIBI, true>(p, hd, lds0, clk);
+  else if (i < rest) short_dkdv<D, NW, CAUSAL, ALIBI, false>(p, hd, lds0, clk);
+  else short_dq<D, NW, CAUSAL, ALIBI, DB>(p, hd, lds0, clk);
   clock_probe_end(p.clock, clk, (int)blockIdx.x);
 }
 

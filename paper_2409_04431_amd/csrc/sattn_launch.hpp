@@ -77,8 +77,8 @@ int launch_bwd_bf16(BwdParams p, bool softmax, bool pin, int causal, bool alibi,
                     hipStream_t st);
 
 // Backward of sequences that one workgroup holds whole (sattn_bwd_short.hpp); heads from `whole` on are
-// shared by two.
+// shared by two (p.db_rows: all, 128 queries at most and no ALiBi; ALiBi: no mask).
 template <int D>
-int launch_bwd_short(const BwdParams& p, int causal, int whole, hipStream_t st);
+int launch_bwd_short(const BwdParams& p, int causal, bool alibi, int whole, hipStream_t st);
 
 }  // namespace sattn

@@ -61,3 +61,34 @@ def test_packed_equals_two_launches_and_leaves_other_rows_alone(d, lengths, caus
     for a, b in zip(two, one):
         assert torch.equal(a[:total], b[:total]) and not torch.isnan(b[:total]).any()
         assert torch.isnan(b[total:]).all()
+
+
+@pytest.mark.parametrize("B", [3, 9])
+@pytest.mark.parametrize("d,N", [(64, 31), (64, 128), (64, 129), (64, 250), (128, 33), (128, 128)])
+def test_alibi_without_a_mask_equals_two_launches(B, d, N):
+    g = torch.Generator().manual_seed(N + d)
+    dev = [torch.randn(B, HEADS, N, d, generator=g).bfloat16().cuda() for _ in range(4)]
+    slopes = torch.tensor([2.0 ** (-8.0 * (h + 1) / HEADS) for h in range(HEADS)], device="cuda")
+    two, one = _both(lambda *r: sa.sigmoid_attn_bwd(*dev, *r, -math.log(max(N, 2)), False, slopes), dev[:3])
+    for a, b in zip(two, one):
+        assert torch.equal(a, b) and not torch.isnan(b).any()
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d,lengths", [(64, [128] * 5), (64, [128, 1, 0, 33]), (128, [97] * 3), (128, [64, 128])])
+def test_bias_gradient_equals_two_launches(d, lengths, causal):
+    H, total, B, longest = 3, sum(lengths), len(lengths), max(lengths)
+    g = torch.Generator().manual_seed(total)
+    q, k, v, do = (torch.randn(total, H, d, generator=g).bfloat16().cuda() for _ in range(4))
+    cu = torch.tensor([sum(lengths[:i]) for i in range(B + 1)], dtype=torch.int32, device="cuda")
+    rows, db = torch.empty(H, total, device="cuda"), torch.empty(B, H, device="cuda")
+    two, one = _both(lambda *r: sa.sigmoid_attn_varlen_bwd_bias_grad(q, k, v, do, *r[:4], cu, longest, -math.log(longest), causal,
+                                                                     None, db=r[4]), [q, k, v, rows, db])
+    for a, b in zip(two, one):
+        assert torch.equal(a, b) and not torch.isnan(b).any()
+    if len(set(lengths)) == 1:  # the dense call
+        dense = [x.view(B, longest, H, d).transpose(1, 2) for x in (q, k, v, do)]
+        like = [*(x for x in dense[:3]), torch.empty(B, H, longest, device="cuda"), db]
+        two, one = _both(lambda *r: sa.sigmoid_attn_bwd_bias_grad(*dense, *r[:4], -math.log(longest), causal, None, db=r[4]), like)
+        for a, b in zip(two, one):
+            assert torch.equal(a, b) and not torch.isnan(b).any()
