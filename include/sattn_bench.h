@@ -36,15 +36,16 @@ int sattn_set_fwd_v_slots(int v_slots);
 
 /* Force (1) or forbid (2) the one-grid form of the sigmoid backward, in which the dK/dV and
  * the dQ workgroups of Algorithm 2's two output owners share one launch; 0 = back to the
- * automatic choice; 3 = forbid it and also keep one block per workgroup in the causal passes
+ * automatic choice (the only one that also takes the kernel for sequences of at most 256
+ * tokens, 128 at d = 128, whose heads a workgroup holds whole); 3 = forbid it and also keep one block per workgroup in the causal passes
  * (which otherwise deal a long head's blocks out in pairs, longest with shortest).  Only
  * sigmoid_attn_bwd / sigmoid_attn_varlen_bwd and their _bias_grad forms have that form (both
  * passes, self-attention, one K/V head per query head, dq not in the place of q or dout).
  * Results do not depend on it.  Process-wide like the setters above.  Returns 0 or SATTN_ERR_UNSUPPORTED. */
 int sattn_set_bwd_merged(int mode);
 /* 1 if sigmoid_attn_bwd (packed: sigmoid_attn_varlen_bwd with N = max_seqlen) on a bf16
- * self-attention problem of this size would run its two passes as one grid, 0 if as two
- * launches; SATTN_ERR_SHAPE for non-positive sizes, SATTN_ERR_UNSUPPORTED for another d. */
+ * self-attention problem of this size would run its two passes, where it takes them, as one
+ * grid, 0 if as two launches; SATTN_ERR_SHAPE for non-positive sizes, SATTN_ERR_UNSUPPORTED for another d. */
 int sattn_bwd_one_grid(int B, int H, int N, int d, int causal, int packed);
 /* The same for head dimension 128, not packed (at 64 the choice is another one). */
 int sattn_bwd_merged(int B, int H, int N, int causal);

@@ -248,6 +248,7 @@ bool pick_bwd_merged(int B, int H, int N, int causal, bool two_per_cu, bool pack
 // 9.3 / 7.3, 384: 18.1 / 15.3; d128 512 heads 54.7 / 50.3), not beyond (384 heads N250 43.5 / 44.3).
 bool pick_bwd_short(int64_t heads, int N, int d, int causal, bool rows) {
   if (g_bwd_merged.load(std::memory_order_relaxed) != 0 || N > (d == 64 && !rows ? 256 : 128)) return false;
+  if (heads > (1 << 21)) return false;  // two workgroups a head of up to 512 work-items, which a launch counts in 32 bits
   return d == 128 || N <= 128 || causal || 2 * heads > compute_units();
 }
 // Its heads that take one workgroup.  What is left over after whole rounds of the chip takes two, one
