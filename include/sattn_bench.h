@@ -29,8 +29,9 @@ extern "C" {
  * query block per workgroup also under the causal mask (64 deals a head's blocks out in pairs,
  * longest with shortest, where their number is even).  The value is
  * process-wide (an atomic that every forward launch reads): set it from one thread while no
- * other thread launches, or launches in flight on other threads may take either shape.  Apart
- * from 65, results do not depend on it. */
+ * other thread launches, or launches in flight on other threads may take either shape.  0 (the
+ * automatic choice) also takes the kernel for sequences of at most 256 tokens, 128 at d = 128,
+ * whose heads a workgroup holds whole.  Apart from 65, results do not depend on it. */
 int sattn_set_fwd_waves(int waves);
 int sattn_set_fwd_v_slots(int v_slots);
 

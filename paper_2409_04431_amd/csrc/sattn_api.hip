@@ -241,6 +241,14 @@ bool pick_bwd_merged(int B, int H, int N, int causal, bool two_per_cu, bool pack
   return (places - pairs) * 25 > places;
 }
 
+// The forward that holds a head whole (sattn_fwd_short.hpp): up to 128 keys always; up to 256 at d = 64
+// from more heads than half the units on, where the two workgroups a head of the other kernels no longer
+// each find a compute unit to themselves (us, those / this: N250 16 heads 7.8 / 8.9, 144 heads 10.9 / 9.5).
+bool pick_fwd_short(int64_t heads, int N, int d) {
+  if (g_fwd_waves.load(std::memory_order_relaxed) != 0 || heads > (1 << 21)) return false;
+  return N <= 128 || (d == 64 && N <= 256 && 2 * heads > compute_units());
+}
+
 // The backward that holds a head whole (sattn_bwd_short.hpp), for every sequence short enough but where
 // the two passes' four workgroups a head all find a place at once and nothing is masked: N250 d64 16
 // heads 12.5 us against 13.2, 64 heads 13.1 / 13.8 (causal, 128 heads: 16.4 / 14.7; N128: 9.3 / 7.2).  With
@@ -427,6 +435,8 @@ int fwd_impl(const FwdArgs& a) {
     if (p.n_split > 0)
       return a.d == 128 ? launch_fwd_few<128>(p, a.causal, alibi, st) : launch_fwd_few<64>(p, a.causal, alibi, st);
   }
+  if (!SOFTMAX && PIN && Nk == a.N && Hkv == a.H && !alibi && pick_fwd_short((int64_t)a.B * a.H, a.N, a.d))
+    return a.d == 128 ? launch_fwd_short<128>(p, a.causal, st) : launch_fwd_short<64>(p, a.causal, st);
   const FwdShape shape = pick_fwd_shape(a.B, a.H, a.N, a.d, a.causal, has64);
   // The 64-row causal kernel deals a head's blocks out in pairs of equal work (longest with
   // shortest) where that still leaves a workgroup per compute unit.  Measured against single

@@ -76,6 +76,10 @@ template <int D>
 int launch_bwd_bf16(BwdParams p, bool softmax, bool pin, int causal, bool alibi, int parts, bool merged,
                     hipStream_t st);
 
+// Forward of sequences that one workgroup holds whole (sattn_fwd_short.hpp).
+template <int D>
+int launch_fwd_short(const FwdParams& p, int causal, hipStream_t st);
+
 // Backward of sequences that one workgroup holds whole (sattn_bwd_short.hpp); heads from `whole` on are
 // shared by two (p.db_rows: all, 128 queries at most and no ALiBi; ALiBi: no mask).
 template <int D>
