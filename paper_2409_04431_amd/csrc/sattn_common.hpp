@@ -195,8 +195,7 @@ __device__ __forceinline__ void packed_place(const int* cu_seqlens, int B, int H
   rank = r / m;
   const int pair = G * kXcd + (r - rank * m);
   int seq = pair / H;
-  int hd = pair - seq * H + seq % H;
-  hd = hd < H ? hd : hd - H;
+  const int hd = pair - seq * H;
   if (B <= 64) {
     const int lane = threadIdx.x & 63;
     // unique keys: equal lengths in the caller's order (lengths are below 2^24, as the API checks)
