@@ -124,8 +124,8 @@ __device__ __forceinline__ void short_dkdv(const BwdParams& p, const ShortHead& 
   }
   const uint32_t ds_wr = lds_ds + key * 128 + ((h ^ SwzX<64>::f(key)) << 4);
 
-  // Rows past the end are zeros in dO and K: the queries there add nothing to dK and dV, the keys
-  // nothing to dQ, without a mask.
+  // Rows past the end repeat row N-1 in Q and K, which waves read without a further barrier; in dO they are
+  // zeros.  dO's zeros let the queries there add nothing to dK and dV, V's above the keys nothing to dQ.
   SATTN_WAIT_VMCNT(0);
   stage(2, n_tiles);
   __syncthreads();
@@ -135,9 +135,8 @@ __device__ __forceinline__ void short_dkdv(const BwdParams& p, const ShortHead& 
 #pragma unroll
     for (int kk = 0; kk < KD; ++kk) x1[kk] = as_bf16x8(lds_read_b128(lds_k + at * (D * 2) + (((2 * kk + h) ^ SwzX<D>::f(at)) << 4)));
   }
-  if (n_tiles * 64 > N) {
-    short_pad<D, NW>(lds_k + (n_tiles - 1) * TILE, n_tiles - 1, N, tid);
-    if (n_tiles <= 2) short_pad<D, NW>(lds0 + (n_tiles - 1) * SLOT + TILE, n_tiles - 1, N, tid);
+  if (n_tiles <= 2 && n_tiles * 64 > N) {
+    short_pad<D, NW>(lds0 + (n_tiles - 1) * SLOT + TILE, n_tiles - 1, N, tid);
     __syncthreads();
   }
 
