@@ -302,14 +302,11 @@ __device__ __forceinline__ void short_dq(const BwdParams& p, const ShortHead& hd
   SATTN_WAIT_VMCNT(0);
   __syncthreads();
   clock_probe_mark(p.clock, clk, kMarkFirstProduct);
-  if (n_tiles * 64 > N) {  // keys past the end add nothing
-    const uint32_t last = lds0 + (n_tiles - 1) * SLOT;
-    short_pad<D, NW>(last, n_tiles - 1, N, tid);
-    short_pad<D, NW>(last + TILE, n_tiles - 1, N, tid);
-    __syncthreads();
-  }
   float dbs[4] = {0.f, 0.f, 0.f, 0.f};
   const int c_hi = q0 < N ? (CAUSAL ? qblk + 1 : n_chunks) : 0;
+  // Keys from N on repeat row N-1; their dS is zero by selection, whatever the logit and dP are (under the
+  // mask no query has them).
+  const int ragged = N & 31 ? N >> 5 : -1, keep = CAUSAL ? l32 + 1 : N & 31;
   bf16x8 f1[KD], f2[KD];
   auto rows_of = [&](int c) {
     const uint32_t at = lds0 + (c >> 1) * SLOT + (c & 1) * (32 * D * 2);
@@ -340,9 +337,9 @@ __device__ __forceinline__ void short_dq(const BwdParams& p, const ShortHead& hd
       const float w = __builtin_amdgcn_rcpf(1.0f + e);
       ds[r] = __builtin_fmaf(-w, w, w) * dp[r];
     }
-    if (CAUSAL && c == qblk) {
+    if (CAUSAL ? c == qblk : c == ragged) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) ds[r] = key_of_reg(r) + 8 * h <= l32 ? ds[r] : 0.f;
+      for (int r = 0; r < 16; ++r) ds[r] = key_of_reg(r) + 8 * h < keep ? ds[r] : 0.f;
     }
     if constexpr (DB) {
 #pragma clang fp contract(off)  // (dS is rounded before it is added, as in the dQ pass)

@@ -17,6 +17,9 @@ H = 17
 WHOLE = [(9, 64, 129), (9, 64, 250), (21, 64, 33), (9, 128, 33), (9, 128, 97)]  # batch, d, N: all or most heads (256
                                                                                 # compute units) take one workgroup
 
+# Two workgroups a head: all heads, or (64, 250 tokens) the 101 beyond one round of 256
+SHARED = [(3, 64, 33), (3, 64, 100), (21, 64, 250), (3, 128, 33), (3, 128, 97)]
+
 
 def _inputs(B, d, N):
     g = torch.Generator().manual_seed(1000 * B + 10 * N + d)
@@ -68,3 +71,35 @@ def test_infinite_query_element_where_one_workgroup_holds_a_head(B, d, N, row, c
     assert bool(choice[0].isfinite().all())
     _compare(choice, two, causal)
     _as_oracle(choice[0][:1, :2], _oracle(x, 0, causal)[0])
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("row", [0, -1])
+@pytest.mark.parametrize("B,d,N", SHARED)
+def test_infinite_query_element_where_two_workgroups_share_a_head(B, d, N, row, causal):
+    x = _inputs(B, d, N)
+    x[0][:, :, row, 3] = math.inf
+    choice, two = _run(x, causal)
+    assert bool(choice[0].isfinite().all())
+    _compare(choice, two, causal)
+    _as_oracle(choice[0][-1:, :2], _oracle(x, B - 1, causal)[0])
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d,N", [(64, 33), (64, 100), (128, 70)])
+def test_infinite_query_element_and_the_bias_gradient(d, N, causal):
+    x = _inputs(2, d, N)
+    x[0][:, :, N // 2, 3] = math.inf
+    q, k, v, do = (t.cuda() for t in x)
+    both = []
+    try:
+        for mode in (0, 2):
+            sa.sattn_set_bwd_merged(mode)
+            grads, rows, db = [torch.zeros_like(q) for _ in range(3)], torch.full((2, H, N), 7.0, device="cuda"), torch.zeros(2, H, device="cuda")
+            sa.sigmoid_attn_bwd_bias_grad(q, k, v, do, *grads, rows, -math.log(N), causal, None, db=db)
+            both.append((grads[0], rows, db))
+    finally:
+        sa.sattn_set_bwd_merged(0)
+    for a, b in zip(*both):
+        assert bool(a.isfinite().all()) and torch.equal(a, b)
+    assert bool((both[0][1][:, :, N // 2] == 0).all())
