@@ -100,12 +100,7 @@ __device__ __forceinline__ void short_dkdv(const BwdParams& p, const ShortHead& 
   const int key0 = 32 * kblk, key = key0 + l32, key_ld = key < N ? key : N - 1;
   bf16x8 x1[KD], x2[KD];
 #pragma unroll
-  for (int kk = 0; kk < KD; ++kk) {
-    // (no V row past the end: dP and dS of such a key are zero, and it adds nothing to dQ)
-    const u32x4 x = *(const u32x4*)(vb + (int64_t)key_ld * p.v.ss + 16 * kk + 8 * h);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) ((u32x4&)x2[kk])[i] = key < N ? x[i] : 0u;
-  }
+  for (int kk = 0; kk < KD; ++kk) x2[kk] = as_bf16x8(*(const u32x4*)(vb + (int64_t)key_ld * p.v.ss + 16 * kk + 8 * h));
   f32x16 dk[DT], dv[DT];
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt)
@@ -124,8 +119,9 @@ __device__ __forceinline__ void short_dkdv(const BwdParams& p, const ShortHead& 
   }
   const uint32_t ds_wr = lds_ds + key * 128 + ((h ^ SwzX<64>::f(key)) << 4);
 
-  // Rows past the end repeat row N-1 in Q and K, which waves read without a further barrier; in dO they are
-  // zeros.  dO's zeros let the queries there add nothing to dK and dV, V's above the keys nothing to dQ.
+  // Rows past the end repeat row N-1 in Q, K and V and are zeros in dO (where the repeated row would make an
+  // infinite element of it a NaN in dV).  P and dS of queries there and dS of keys there are zero by selection,
+  // whatever the logit and dP are.
   SATTN_WAIT_VMCNT(0);
   stage(2, n_tiles);
   __syncthreads();
@@ -149,6 +145,8 @@ __device__ __forceinline__ void short_dkdv(const BwdParams& p, const ShortHead& 
       f2[kk] = as_bf16x8(lds_read_b128(at + TILE + row[kk]));
     }
   };
+  const int ragged = N & 31 ? N >> 5 : -1;
+  const uint32_t key_bits = key < N ? 0xffffffffu : 0u;
   const int rounds = (N + 127) / 128, c_end = key0 < N ? n_chunks : 0;  // (a wave past the end has no chunk)
   for (int rnd = 0; rnd < rounds; ++rnd) {
     const int c_lo = CAUSAL ? max(4 * rnd, kblk) : 4 * rnd, c_hi = min(4 * rnd + 4, c_end);
@@ -183,10 +181,11 @@ __device__ __forceinline__ void short_dkdv(const BwdParams& p, const ShortHead& 
         pr[r] = __builtin_amdgcn_rcpf(1.0f + e);
         ds[r] = __builtin_fmaf(-pr[r], pr[r], pr[r]) * dp[r];
       }
-      if (CAUSAL && c == kblk) {
+      if ((CAUSAL && c == kblk) || c == ragged) {
+        const int from = CAUSAL && c == kblk ? l32 : 0, to = c == ragged ? N & 31 : 32;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const bool keep = key_of_reg(r) + 8 * h >= l32;
+          const bool keep = key_of_reg(r) + 8 * h >= from && key_of_reg(r) + 8 * h < to;
           pr[r] = keep ? pr[r] : 0.f;
           ds[r] = keep ? ds[r] : 0.f;
         }
@@ -200,10 +199,10 @@ __device__ __forceinline__ void short_dkdv(const BwdParams& p, const ShortHead& 
           dk[dt] = mfma32(t1[ks][dt], dsb[ks], dk[dt]);
         }
       if constexpr (DQ) {
-      // dS, keys by queries: rows of 64 queries of a key, two such tiles
-      const uint32_t to = (ds_wr ^ ((c & 1) << 6)) + ((c >> 1) & 1) * (MAXN * 128);
-      lds_write_b128(to, __builtin_bit_cast(u32x4, dsb[0]));
-      lds_write_b128(to ^ 32, __builtin_bit_cast(u32x4, dsb[1]));
+        // dS, keys by queries: rows of 64 queries of a key, two such tiles
+        const uint32_t to = (ds_wr ^ ((c & 1) << 6)) + ((c >> 1) & 1) * (MAXN * 128);
+        lds_write_b128(to, __builtin_bit_cast(u32x4, dsb[0]) & key_bits);
+        lds_write_b128(to ^ 32, __builtin_bit_cast(u32x4, dsb[1]) & key_bits);
       }
     }
     if (rnd == 0) {

@@ -53,7 +53,7 @@ def _as_oracle(got, ref):
     """Equal where the oracle has an infinity or a NaN, within the bf16 bar elsewhere."""
     got, finite = got.float().cpu().numpy(), np.isfinite(ref)
     assert np.array_equal(got[~finite], ref[~finite].astype(np.float32), equal_nan=True)
-    assert np.abs(got[finite] - ref[finite]).max() <= TOL * np.abs(ref[finite]).max()
+    assert np.abs(got[finite] - ref[finite]).max(initial=0.0) <= TOL * np.abs(ref[finite]).max(initial=0.0)
 
 
 def _oracle(x, b, causal):
@@ -103,3 +103,18 @@ def test_infinite_query_element_and_the_bias_gradient(d, N, causal):
     for a, b in zip(*both):
         assert bool(a.isfinite().all()) and torch.equal(a, b)
     assert bool((both[0][1][:, :, N // 2] == 0).all())
+
+
+@pytest.mark.parametrize("tensor", [1, 2, 3], ids=["k", "v", "dout"])
+@pytest.mark.parametrize("row", [0, -1])
+@pytest.mark.parametrize("B,d,N", WHOLE + SHARED)
+def test_infinite_key_value_or_output_gradient_element(B, d, N, row, tensor):
+    """Positive rows throughout, so that the oracle's sums are infinities of one sign and not differences of two."""
+    x = [t.abs() for t in _inputs(B, d, N)]
+    x[tensor][:, :, row, 3] = math.inf
+    dev = [t.cuda() for t in x]
+    grads = [torch.full_like(dev[0], 7.0) for _ in range(3)]
+    sa.sigmoid_attn_bwd(*dev, *grads, -math.log(N), False)
+    for b in (0, B - 1):
+        for g, ref in zip(grads, _oracle(x, b, False)):
+            _as_oracle(g[b:b + 1, :2], ref)
