@@ -202,8 +202,10 @@ int sattn_headconcat_norm_bwd(const void* x, const void* dy, const float* stats,
  * the V ring in LDS: 4 or 8 waves of 32 query rows (two waves per SIMD), or, at d = 128 on long
  * key loops, 4 waves of 64 query rows (one wave per SIMD, half the LDS traffic per MFMA).  The
  * bf16 forward entry points (sigmoid, softmax, variable-length, ...) choose them per problem
- * from d, B*H*N, the mask and the number of compute units.  sattn_fwd_waves returns that
- * choice as 4, 8, or 64 for the four 64-row waves (the softmax comparison kernel and
+ * from d, B*H*N, the mask and the number of compute units.  Short sequences (at most 256 tokens,
+ * 128 at d = 128) may take a kernel without a ring instead, whose workgroup holds the K and V of a head
+ * (sattn_fwd_short in sattn_bench.h reports it); the two queries here describe the kernels that
+ * stream K and V.  sattn_fwd_waves returns their choice as 4, 8, or 64 for the four 64-row waves (the softmax comparison kernel and
  * non-causal ALiBi run the 8-wave shape where 64 is returned); sattn_fwd_v_slots returns the V
  * ring depth (3; 2: two 4-wave workgroups per compute unit); both return a negative error code
  * for bad arguments.  The outputs are bit-identical for all shapes: the arithmetic of a query

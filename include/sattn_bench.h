@@ -51,6 +51,15 @@ int sattn_bwd_one_grid(int B, int H, int N, int d, int causal, int packed);
 /* The same for head dimension 128, not packed (at 64 the choice is another one). */
 int sattn_bwd_merged(int B, int H, int N, int causal);
 
+/* Which bf16 self-attention problems (one K/V head per query head; packed: N = max_seqlen) take the
+ * kernels whose workgroups hold a head whole.  sattn_fwd_short: the waves of a forward workgroup, 4 or
+ * 8, for sigmoid_attn_fwd / sigmoid_attn_varlen_fwd without ALiBi; sattn_bwd_short: the workgroups of the
+ * backward, B*H (one a head) to 2*B*H (two a head, one for dK and dV and one for dQ), with
+ * alibi / bias_grad non-zero where slopes are given / the row sums of dS are asked for.  0 where the
+ * kernels run that stream the other side; errors as sattn_bwd_one_grid. */
+int sattn_fwd_short(int B, int H, int N, int d);
+int sattn_bwd_short(int B, int H, int N, int d, int causal, int alibi, int bias_grad);
+
 /* Comparison aids (Section 4 and Appendix F.2 compare the sigmoid kernels with softmax kernels
  * built the same way).  Same arguments, results and error behaviour as sigmoid_attn_fwd /
  * sigmoid_attn_bwd / softmax_attn_fwd / softmax_attn_bwd; the kernels run every pipeline step

@@ -134,6 +134,10 @@ def load_library():
     lib.sattn_set_bwd_merged.restype = i
     lib.sattn_bwd_one_grid.argtypes = [i, i, i, i, i, i]
     lib.sattn_bwd_one_grid.restype = i
+    lib.sattn_fwd_short.argtypes = [i, i, i, i]
+    lib.sattn_fwd_short.restype = i
+    lib.sattn_bwd_short.argtypes = [i, i, i, i, i, i, i]
+    lib.sattn_bwd_short.restype = i
     lib.sattn_bwd_merged.argtypes = [i, i, i, i]
     lib.sattn_bwd_merged.restype = i
     lib.sattn_set_clock_probe.argtypes = [_vp, i]
@@ -429,7 +433,8 @@ def sigmoid_attn_cross_aligned_bwd(q, k, v, dout, dq, dk, dv, bias, causal=False
 
 
 def sattn_fwd_waves(B, H, N, d, causal=False):
-    """Waves (32 query rows each) per workgroup the bf16 forward kernels use for this problem."""
+    """Waves (32 query rows each) per workgroup the bf16 forward kernels that stream K and V use for this
+    problem (short sequences: see sattn_fwd_short)."""
     rc = load_library().sattn_fwd_waves(B, H, N, d, int(bool(causal)))
     if rc < 0:
         _raise(rc, "sattn_fwd_waves")
@@ -437,10 +442,27 @@ def sattn_fwd_waves(B, H, N, d, causal=False):
 
 
 def sattn_fwd_v_slots(B, H, N, d, causal=False):
-    """Depth of the V ring (2 or 3 tiles) the bf16 forward kernels use for this problem."""
+    """Depth of the V ring (2 or 3 tiles) the bf16 forward kernels that stream K and V use for this problem."""
     rc = load_library().sattn_fwd_v_slots(B, H, N, d, int(bool(causal)))
     if rc < 0:
         _raise(rc, "sattn_fwd_v_slots")
+    return rc
+
+
+def sattn_fwd_short(B, H, N, d):
+    """Waves per workgroup of the forward that holds a head whole, 0 where this bf16 self-attention problem
+    (packed: N = max_seqlen) takes a kernel that streams K and V."""
+    rc = load_library().sattn_fwd_short(int(B), int(H), int(N), int(d))
+    _raise(min(rc, 0), "sattn_fwd_short")
+    return rc
+
+
+def sattn_bwd_short(B, H, N, d, causal=False, alibi=False, bias_grad=False):
+    """Workgroups of the backward that holds a head whole (one or two a head), 0 where this bf16 self-attention
+    problem (packed: N = max_seqlen) takes the two passes."""
+    rc = load_library().sattn_bwd_short(int(B), int(H), int(N), int(d), int(bool(causal)), int(bool(alibi)),
+                                        int(bool(bias_grad)))
+    _raise(min(rc, 0), "sattn_bwd_short")
     return rc
 
 

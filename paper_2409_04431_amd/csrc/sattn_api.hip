@@ -254,7 +254,9 @@ bool pick_fwd_short(int64_t heads, int N, int d) {
 // heads 12.5 us against 13.2, 64 heads 13.1 / 13.8 (causal, 128 heads: 16.4 / 14.7; N128: 9.3 / 7.2).  With
 // the row sums of dS (`rows`) every head takes two workgroups, which pays up to 128 tokens (64 heads
 // 9.3 / 7.3, 384: 18.1 / 15.3; d128 512 heads 54.7 / 50.3), not beyond (384 heads N250 43.5 / 44.3).
-bool pick_bwd_short(int64_t heads, int N, int d, int causal, bool rows) {
+// Not for ALiBi under the mask or with the row sums: the passes add its terms in orders of their own.
+bool pick_bwd_short(int64_t heads, int N, int d, int causal, bool alibi, bool rows) {
+  if (alibi && (causal || rows)) return false;
   if (g_bwd_merged.load(std::memory_order_relaxed) != 0 || N > (d == 64 && !rows ? 256 : 128)) return false;
   if (heads > (1 << 21)) return false;  // two workgroups a head of up to 512 work-items, which a launch counts in 32 bits
   return d == 128 || N <= 128 || causal || 2 * heads > compute_units();
@@ -575,8 +577,8 @@ int bwd_impl(const BwdArgs& a) {
     if (rc) return rc;
     p.nlse2 = nlse2; p.dvec = dvec; p.npad = npad;
   }
-  if (!SOFTMAX && PIN && !in_place && Hkv == a.H && Nk == a.N && a.parts == (kBwdDkDv | kBwdDq) && !(alibi && (a.causal || a.db_rows)) &&
-      pick_bwd_short((int64_t)a.B * a.H, a.N, a.d, a.causal, a.db_rows != nullptr)) {
+  if (!SOFTMAX && PIN && !in_place && Hkv == a.H && Nk == a.N && a.parts == (kBwdDkDv | kBwdDq) &&
+      pick_bwd_short((int64_t)a.B * a.H, a.N, a.d, a.causal, alibi, a.db_rows != nullptr)) {
     const int whole = a.db_rows ? 0 : short_whole_heads((int64_t)a.B * a.H, a.N, a.d);
     rc = a.d == 128 ? launch_bwd_short<128>(p, a.causal, alibi, whole, st) : launch_bwd_short<64>(p, a.causal, alibi, whole, st);
     return rc == SATTN_OK && a.db ? reduce_rows(a, p, st) : rc;
@@ -998,6 +1000,18 @@ int sattn_bwd_one_grid(int B, int H, int N, int d, int causal, int packed) {
   return pick_bwd_merged(B, H, N, causal, d == 64, packed != 0) ? 1 : 0;
 }
 
+int sattn_bwd_short(int B, int H, int N, int d, int causal, int alibi, int bias_grad) {
+  if (B <= 0 || H <= 0 || N <= 0) return SATTN_ERR_SHAPE;
+  if (d != 64 && d != 128) return SATTN_ERR_UNSUPPORTED;
+  const int64_t heads = (int64_t)B * H;
+  if (!pick_bwd_short(heads, N, d, causal, alibi != 0, bias_grad != 0)) return 0;
+  return (int)(2 * heads) - (bias_grad ? 0 : short_whole_heads(heads, N, d));
+}
+int sattn_fwd_short(int B, int H, int N, int d) {
+  if (B <= 0 || H <= 0 || N <= 0) return SATTN_ERR_SHAPE;
+  if (d != 64 && d != 128) return SATTN_ERR_UNSUPPORTED;
+  return pick_fwd_short((int64_t)B * H, N, d) ? (N > 128 ? 8 : 4) : 0;
+}
 int sattn_bwd_merged(int B, int H, int N, int causal) { return sattn_bwd_one_grid(B, H, N, 128, causal, 0); }
 
 int sattn_set_bwd_merged(int mode) {

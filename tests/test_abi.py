@@ -143,6 +143,30 @@ def test_backward_one_grid_choice(lib):
     assert sa.sattn_bwd_merged(4, 12, 1024)
 
 
+def test_choice_of_the_kernels_that_hold_a_head_whole(lib):
+    # (256 compute units, which the library also assumes without a device)
+    assert sa.sattn_fwd_short(2, 2, 128, 64) == 4 and sa.sattn_fwd_short(2, 2, 128, 128) == 4
+    assert sa.sattn_fwd_short(9, 17, 256, 64) == 8 and sa.sattn_fwd_short(3, 17, 256, 64) == 0
+    assert sa.sattn_fwd_short(64, 12, 257, 64) == 0 and sa.sattn_fwd_short(64, 12, 129, 128) == 0
+    # all heads shared by two workgroups, whole, and those beyond a whole round shared
+    assert sa.sattn_bwd_short(3, 17, 128, 64) == 102 and sa.sattn_bwd_short(9, 17, 256, 64) == 153
+    assert sa.sattn_bwd_short(21, 17, 256, 64) == 256 + 2 * 101
+    # declined: unmasked, up to half as many heads as units; row sums beyond 128 tokens; ALiBi under the mask or with them
+    assert sa.sattn_bwd_short(3, 17, 200, 64) == 0 and sa.sattn_bwd_short(3, 17, 200, 64, True) == 102
+    assert sa.sattn_bwd_short(9, 17, 129, 64, bias_grad=True) == 0 and sa.sattn_bwd_short(9, 17, 128, 64, bias_grad=True) == 306
+    assert sa.sattn_bwd_short(9, 17, 128, 64, alibi=True) > 0 and sa.sattn_bwd_short(9, 17, 128, 64, True, True) == 0
+    assert sa.sattn_bwd_short(9, 17, 128, 64, alibi=True, bias_grad=True) == 0
+    assert lib.sattn_fwd_short(0, 1, 16, 64) == -2 and lib.sattn_fwd_short(1, 1, 16, 96) == -3
+    assert lib.sattn_bwd_short(1, 0, 16, 64, 0, 0, 0) == -2 and lib.sattn_bwd_short(1, 1, 16, 96, 0, 0, 0) == -3
+    try:
+        sa.sattn_set_bwd_merged(2)
+        sa.sattn_set_fwd_waves(4)
+        assert sa.sattn_bwd_short(9, 17, 128, 64) == 0 and sa.sattn_fwd_short(9, 17, 128, 64) == 0
+    finally:
+        sa.sattn_set_bwd_merged(0)
+        sa.sattn_set_fwd_waves(0)
+
+
 def test_forward_shape_choice(lib):
     # d = 64 always takes 4-wave workgroups; d = 128 while the grid is small (one per compute unit,
     # three-slot V ring) or the key loop short (two per compute unit, two-slot V ring)
