@@ -31,7 +31,7 @@ extern "C" {
  * process-wide (an atomic that every forward launch reads): set it from one thread while no
  * other thread launches, or launches in flight on other threads may take either shape.  0 (the
  * automatic choice) also takes the kernel for sequences of at most 256 tokens, 128 at d = 128,
- * whose heads a workgroup holds whole.  Apart from 65, results do not depend on it. */
+ * whose heads a workgroup holds whole, while neither setter forces anything.  Apart from 65, results do not depend on it. */
 int sattn_set_fwd_waves(int waves);
 int sattn_set_fwd_v_slots(int v_slots);
 

@@ -245,7 +245,8 @@ bool pick_bwd_merged(int B, int H, int N, int causal, bool two_per_cu, bool pack
 // from more heads than half the units on, where the two workgroups a head of the other kernels no longer
 // each find a compute unit to themselves (us, those / this: N250 16 heads 7.8 / 8.9, 144 heads 10.9 / 9.5).
 bool pick_fwd_short(int64_t heads, int N, int d) {
-  if (g_fwd_waves.load(std::memory_order_relaxed) != 0 || heads > (1 << 21)) return false;
+  if (g_fwd_waves.load(std::memory_order_relaxed) != 0 || g_fwd_vslots.load(std::memory_order_relaxed) != 0) return false;
+  if (heads > (1 << 21)) return false;
   return N <= 128 || (d == 64 && N <= 256 && 2 * heads > compute_units());
 }
 

@@ -162,9 +162,14 @@ def test_choice_of_the_kernels_that_hold_a_head_whole(lib):
         sa.sattn_set_bwd_merged(2)
         sa.sattn_set_fwd_waves(4)
         assert sa.sattn_bwd_short(9, 17, 128, 64) == 0 and sa.sattn_fwd_short(9, 17, 128, 64) == 0
+        sa.sattn_set_fwd_waves(0)
+        for slots in (2, 3):  # a forced V ring is that of a kernel which has one
+            sa.sattn_set_fwd_v_slots(slots)
+            assert sa.sattn_fwd_short(9, 17, 128, 128) == 0
     finally:
         sa.sattn_set_bwd_merged(0)
         sa.sattn_set_fwd_waves(0)
+        sa.sattn_set_fwd_v_slots(0)
 
 
 def test_forward_shape_choice(lib):
