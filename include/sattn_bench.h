@@ -117,7 +117,8 @@ int sattn_mfma_bf16_probe(int blocks, int iters, float* sink, void* stream);
  * lies well below the nominal peak clock that the 2.5 PFLOP/s figure assumes.  out[8w+2..5] are
  * the ticks since the kernel's start at which wave 0 of the workgroup issued its first tile
  * product, entered its steady-state loop, left it, and began to store its outputs; out[8w+6]
- * the tiles it ran in that loop and out[8w+7] the tiles of the workgroup.  Workgroups that exit
+ * the tiles it ran in that loop (where a workgroup holds a head whole: of 64 rows, in its loop over the
+ * other side) and out[8w+7] the tiles of the workgroup.  Workgroups that exit
  * at once (blocks beyond a sequence's length) write nothing: clear the buffer first.  8-byte
  * aligned. */
 int sattn_set_clock_probe(void* device_buffer, int capacity);

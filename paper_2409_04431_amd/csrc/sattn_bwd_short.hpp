@@ -148,6 +148,8 @@ __device__ __forceinline__ void short_dkdv(const BwdParams& p, const ShortHead& 
   const int ragged = N & 31 ? N >> 5 : -1;
   const uint32_t key_bits = key < N ? 0xffffffffu : 0u;
   const int rounds = (N + 127) / 128, c_end = key0 < N ? n_chunks : 0;  // (a wave past the end has no chunk)
+  clk.steady_tiles = (c_end - (CAUSAL ? min(kblk, c_end) : 0) + 1) / 2;
+  clock_probe_mark(p.clock, clk, kMarkSteadyBegin);
   for (int rnd = 0; rnd < rounds; ++rnd) {
     const int c_lo = CAUSAL ? max(4 * rnd, kblk) : 4 * rnd, c_hi = min(4 * rnd + 4, c_end);
     if (c_lo < c_hi) rows_of(c_lo);
@@ -205,12 +207,8 @@ __device__ __forceinline__ void short_dkdv(const BwdParams& p, const ShortHead& 
         lds_write_b128(to ^ 32, __builtin_bit_cast(u32x4, dsb[1]) & key_bits);
       }
     }
-    if (rnd == 0) {
-      clock_probe_mark(p.clock, clk, kMarkSteadyBegin);
-      SATTN_WAIT_VMCNT(0);  // the other queries have landed
-    }
+    if (rnd == 0) SATTN_WAIT_VMCNT(0);  // the other queries have landed
     __syncthreads();
-    if (rnd == 0) clock_probe_mark(p.clock, clk, kMarkSteadyEnd);
     if (rnd == 0 && n_tiles > 2 && n_tiles * 64 > N) short_pad<D, NW>(lds0 + (n_tiles - 1) * SLOT + TILE, n_tiles - 1, N, tid);
     if constexpr (DQ) {
     // dQ of these 128 queries: this wave's tile of features, all keys
@@ -258,6 +256,7 @@ __device__ __forceinline__ void short_dkdv(const BwdParams& p, const ShortHead& 
     }
     __syncthreads();
   }
+  clock_probe_mark(p.clock, clk, kMarkSteadyEnd);
   clock_probe_mark(p.clock, clk, kMarkStore);
   const uint32_t obuf = lds0 + wave * (2 * RowStore<D>::BYTES);
   static_assert(NW * 2 * RowStore<D>::BYTES <= short_lds_bytes<D, NW>(), "outputs leave through the same LDS");
@@ -316,6 +315,8 @@ __device__ __forceinline__ void short_dq(const BwdParams& p, const ShortHead& hd
     }
   };
   if (c_hi > 0) rows_of(0);
+  clk.steady_tiles = (c_hi + 1) / 2;
+  clock_probe_mark(p.clock, clk, kMarkSteadyBegin);
 #pragma nounroll
   for (int c = 0; c < c_hi; ++c) {
     const uint32_t at = lds0 + (c >> 1) * SLOT + (c & 1) * (32 * D * 2);
@@ -354,6 +355,7 @@ __device__ __forceinline__ void short_dq(const BwdParams& p, const ShortHead& hd
         dq[dt] = mfma32(join_tr(lds_read_tr16(off + at_lane.tr[dt][0]), lds_read_tr16(off + at_lane.tr[dt][1])), dsb[ks], dq[dt]);
       }
   }
+  clock_probe_mark(p.clock, clk, kMarkSteadyEnd);
   if constexpr (DB) {
     float rs = (dbs[0] + dbs[1]) + (dbs[2] + dbs[3]);
     rs += __shfl_xor(rs, 32);  // the two halves of the wave: different keys of the same query row

@@ -67,6 +67,8 @@ __global__ void __launch_bounds__(64 * NW, D == 64 ? 4 : 2) attn_fwd_short_kerne
     __syncthreads();
   }
   const int c_hi = q0 < N ? (CAUSAL ? qblk + 1 : n_chunks) : 0;
+  clk.steady_tiles = (c_hi + 1) / 2;
+  clock_probe_mark(p.clock, clk, kMarkSteadyBegin);
 #pragma nounroll
   for (int c = 0; c < c_hi; ++c) {
     const uint32_t at = lds0 + (c >> 1) * SLOT + (c & 1) * (32 * D * 2);
@@ -92,6 +94,7 @@ __global__ void __launch_bounds__(64 * NW, D == 64 ? 4 : 2) attn_fwd_short_kerne
         o[dt] = mfma32(join_tr(lds_read_tr16(off + at_lane.tr[dt][0]), lds_read_tr16(off + at_lane.tr[dt][1])), pb[ks], o[dt]);
       }
   }
+  clock_probe_mark(p.clock, clk, kMarkSteadyEnd);
   __syncthreads();
   clock_probe_mark(p.clock, clk, kMarkStore);
   RowStore<D>::run(o, 1.0f, lds0 + wave * RowStore<D>::BYTES, lane, hd.of(p.o) + (int64_t)q0 * p.o.ss, p.o.ss, N - q0);

@@ -92,3 +92,28 @@ def test_bias_gradient_equals_two_launches(d, lengths, causal):
         two, one = _both(lambda *r: sa.sigmoid_attn_bwd_bias_grad(*dense, *r[:4], -math.log(longest), causal, None, db=r[4]), like)
         for a, b in zip(two, one):
             assert torch.equal(a, b) and not torch.isnan(b).any()
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("B,d,N", [(21, 64, 250), (3, 64, 100), (9, 128, 97), (21, 64, 33)])
+def test_clock_probe_stamps_are_in_order(B, d, N, causal):
+    x = [torch.randn(B, HEADS, N, d, device="cuda").bfloat16() for _ in range(4)]
+    grads = [torch.empty_like(x[0]) for _ in range(3)]
+    calls = [(lambda: sa.sigmoid_attn_bwd(*x, *grads, -6.0, causal), sa.sattn_bwd_short(B, HEADS, N, d, causal))]
+    if sa.sattn_fwd_short(B, HEADS, N, d):
+        calls.append((lambda: sa.sigmoid_attn_fwd(*x[:3], grads[0], -6.0, causal), B * HEADS))
+    for call, n_wg in calls:
+        assert n_wg > 0
+        buf = torch.zeros(8 * (n_wg + 8), dtype=torch.int64, device="cuda")
+        try:
+            sa.sattn_set_clock_probe(buf)
+            call()
+            torch.cuda.synchronize()
+        finally:
+            sa.sattn_set_clock_probe(None)
+        rec = buf.cpu().view(-1, 8)
+        assert bool((rec[n_wg:] == 0).all())
+        rec = rec[:n_wg]
+        marks = rec[:, 2:6]
+        assert bool((marks[:, 0] > 0).all()) and bool((marks[:, 1:] >= marks[:, :-1]).all()) and bool((marks[:, 3] <= rec[:, 1]).all())
+        assert bool((rec[:, 6] >= 1).all()) and bool((rec[:, 6] <= rec[:, 7]).all()) and bool((rec[:, 7] == (N + 63) // 64).all())
