@@ -20,6 +20,8 @@
 // N250 107 / 79.8; B32 H12 N128 18.1 / 13.6; B64 H16 N64 31.4 / 16.5; B4 H4 N64 7.5 / 5.3; B32 H16 N128 d128
 // 54.7 / 35.9; B16 H16 N70 d128 22.3 / 13.2; B64 H32 N64 d128 137 / 70.
 #pragma once
+#include <type_traits>
+
 #include "sattn_bwd.hpp"
 
 namespace sattn {
@@ -146,66 +148,80 @@ __device__ __forceinline__ void short_dkdv(const BwdParams& p, const ShortHead& 
     }
   };
   const int ragged = N & 31 ? N >> 5 : -1;
-  const uint32_t key_bits = key < N ? 0xffffffffu : 0u;
+  // One chunk of 32 queries; `next`: the one whose rows are fetched under it.
+  auto chunk = [&](int c, int next, auto masked) __attribute__((always_inline)) {
+    const uint32_t at = lds0 + (c >> 1) * SLOT + (c & 1) * (32 * D * 2);
+    f32x16 s, dp;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = dp[r] = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < KD; ++kk) {
+      s = mfma32(f1[kk], x1[kk], s);
+      dp = mfma32(f2[kk], x2[kk], dp);
+    }
+    // (the transposed fragments of this chunk and the rows of the next one come in under the arithmetic)
+    bf16x8 t1[2][DT], t2[2][DT];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) {
+        const uint32_t off = at + ks * 16 * (D * 2);
+        t2[ks][dt] = join_tr(lds_read_tr16(off + TILE + tr[dt][0]), lds_read_tr16(off + TILE + tr[dt][1]));
+        t1[ks][dt] = join_tr(lds_read_tr16(off + tr[dt][0]), lds_read_tr16(off + tr[dt][1]));
+      }
+    rows_of(next);
+    float pr[16], ds[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float w = ALIBI ? __builtin_fmaf(hd.sl2, __builtin_fabsf((float)(32 * c + 8 * h + key_of_reg(r) - key)), nbias) : nbias;
+      const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], p.nscale_log2, w));
+      pr[r] = __builtin_amdgcn_rcpf(1.0f + e);
+      ds[r] = __builtin_fmaf(-pr[r], pr[r], pr[r]) * dp[r];
+    }
+    if (decltype(masked)::value || (CAUSAL && (c == kblk || c == ragged))) {
+      const int from = CAUSAL && c == kblk ? l32 : 0;
+      // (a key past the end, l32 >= N & 31, may keep queries: its dK and dV are not stored, its dS leaves as zeros)
+      const uint32_t span = (c == ragged ? N & 31 : 32) - from, first = 8 * h - from;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const bool keep = key_of_reg(r) + first < span;
+        pr[r] = keep ? pr[r] : 0.f;
+        ds[r] = keep ? ds[r] : 0.f;
+      }
+    }
+    bf16x8 pb[2] = {pack8(pr), pack8(pr + 8)}, dsb[2] = {pack8(ds), pack8(ds + 8)};
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) {
+        dv[dt] = mfma32(t2[ks][dt], pb[ks], dv[dt]);
+        dk[dt] = mfma32(t1[ks][dt], dsb[ks], dk[dt]);
+      }
+    if constexpr (DQ) {
+      // dS, keys by queries: rows of 64 queries of a key, two such tiles
+      const uint32_t to = (ds_wr ^ ((c & 1) << 6)) + ((c >> 1) & 1) * (MAXN * 128);
+      lds_write_b128(to, __builtin_bit_cast(u32x4, dsb[0]));
+      lds_write_b128(to ^ 32, __builtin_bit_cast(u32x4, dsb[1]));
+    }
+  };
   const int rounds = (N + 127) / 128, c_end = key0 < N ? n_chunks : 0;  // (a wave past the end has no chunk)
   clk.steady_tiles = (c_end - (CAUSAL ? min(kblk, c_end) : 0) + 1) / 2;
   clock_probe_mark(p.clock, clk, kMarkSteadyBegin);
   for (int rnd = 0; rnd < rounds; ++rnd) {
     const int c_lo = CAUSAL ? max(4 * rnd, kblk) : 4 * rnd, c_hi = min(4 * rnd + 4, c_end);
     if (c_lo < c_hi) rows_of(c_lo);
+    // The ragged last chunk is a copy of the body of its own: the selection as a branch inside the loop, also where
+    // nothing is ragged, takes 2 to 9 % of the time (us: B64 H16 N128 d64 30.4 / 28.6, N64 18.8 / 17.3, B32 H16 N128 d128
+    // 41.4 / 39.2).  Under the mask the loop has that branch anyway, and a third copy is slower to fetch than it saves
+    // (N100, 384 heads: 13.1 / 13.8).
+    const int plain = !CAUSAL && ragged >= 0 ? min(c_hi, ragged) : c_hi;
+    int c = c_lo;
 #pragma nounroll
-    for (int c = c_lo; c < c_hi; ++c) {
-      const uint32_t at = lds0 + (c >> 1) * SLOT + (c & 1) * (32 * D * 2);
-      f32x16 s, dp;
+    for (; c < plain; ++c) chunk(c, min(c + 1, c_hi - 1), std::false_type{});
+    if (!CAUSAL && c < c_hi) chunk(c, c, std::true_type{});
+    if (DQ && key >= N && key0 < N) {  // a row of dS, this lane's half: the writes of a wave are in order
 #pragma unroll
-      for (int r = 0; r < 16; ++r) s[r] = dp[r] = 0.f;
-#pragma unroll
-      for (int kk = 0; kk < KD; ++kk) {
-        s = mfma32(f1[kk], x1[kk], s);
-        dp = mfma32(f2[kk], x2[kk], dp);
-      }
-      // (the transposed fragments of this chunk and the rows of the next one come in under the arithmetic)
-      bf16x8 t1[2][DT], t2[2][DT];
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) {
-          const uint32_t off = at + ks * 16 * (D * 2);
-          t2[ks][dt] = join_tr(lds_read_tr16(off + TILE + tr[dt][0]), lds_read_tr16(off + TILE + tr[dt][1]));
-          t1[ks][dt] = join_tr(lds_read_tr16(off + tr[dt][0]), lds_read_tr16(off + tr[dt][1]));
-        }
-      rows_of(min(c + 1, c_hi - 1));
-      float pr[16], ds[16];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float w = ALIBI ? __builtin_fmaf(hd.sl2, __builtin_fabsf((float)(32 * c + 8 * h + key_of_reg(r) - key)), nbias) : nbias;
-        const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(s[r], p.nscale_log2, w));
-        pr[r] = __builtin_amdgcn_rcpf(1.0f + e);
-        ds[r] = __builtin_fmaf(-pr[r], pr[r], pr[r]) * dp[r];
-      }
-      if ((CAUSAL && c == kblk) || c == ragged) {
-        const int from = CAUSAL && c == kblk ? l32 : 0, to = c == ragged ? N & 31 : 32;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const bool keep = key_of_reg(r) + 8 * h >= from && key_of_reg(r) + 8 * h < to;
-          pr[r] = keep ? pr[r] : 0.f;
-          ds[r] = keep ? ds[r] : 0.f;
-        }
-      }
-      bf16x8 pb[2] = {pack8(pr), pack8(pr + 8)}, dsb[2] = {pack8(ds), pack8(ds + 8)};
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) {
-          dv[dt] = mfma32(t2[ks][dt], pb[ks], dv[dt]);
-          dk[dt] = mfma32(t1[ks][dt], dsb[ks], dk[dt]);
-        }
-      if constexpr (DQ) {
-        // dS, keys by queries: rows of 64 queries of a key, two such tiles
-        const uint32_t to = (ds_wr ^ ((c & 1) << 6)) + ((c >> 1) & 1) * (MAXN * 128);
-        lds_write_b128(to, __builtin_bit_cast(u32x4, dsb[0]) & key_bits);
-        lds_write_b128(to ^ 32, __builtin_bit_cast(u32x4, dsb[1]) & key_bits);
-      }
+      for (int i = 0; i < 8; ++i) lds_write_b128((ds_wr ^ ((i & 3) << 5)) + (i >> 2) * (MAXN * 128), u32x4{0, 0, 0, 0});
     }
     if (rnd == 0) SATTN_WAIT_VMCNT(0);  // the other queries have landed
     __syncthreads();
@@ -314,11 +330,7 @@ __device__ __forceinline__ void short_dq(const BwdParams& p, const ShortHead& hd
       f2[kk] = as_bf16x8(lds_read_b128(at + TILE + at_lane.row[kk]));
     }
   };
-  if (c_hi > 0) rows_of(0);
-  clk.steady_tiles = (c_hi + 1) / 2;
-  clock_probe_mark(p.clock, clk, kMarkSteadyBegin);
-#pragma nounroll
-  for (int c = 0; c < c_hi; ++c) {
+  auto chunk = [&](int c, int next, auto masked) __attribute__((always_inline)) {
     const uint32_t at = lds0 + (c >> 1) * SLOT + (c & 1) * (32 * D * 2);
     f32x16 s, dp;
 #pragma unroll
@@ -328,7 +340,7 @@ __device__ __forceinline__ void short_dq(const BwdParams& p, const ShortHead& hd
       s = mfma32(f1[kk], x1[kk], s);
       dp = mfma32(f2[kk], x2[kk], dp);
     }
-    rows_of(min(c + 1, c_hi - 1));
+    rows_of(next);
     float ds[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -337,7 +349,7 @@ __device__ __forceinline__ void short_dq(const BwdParams& p, const ShortHead& hd
       const float w = __builtin_amdgcn_rcpf(1.0f + e);
       ds[r] = __builtin_fmaf(-w, w, w) * dp[r];
     }
-    if (CAUSAL ? c == qblk : c == ragged) {
+    if constexpr (decltype(masked)::value) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) ds[r] = key_of_reg(r) + 8 * h < keep ? ds[r] : 0.f;
     }
@@ -354,7 +366,15 @@ __device__ __forceinline__ void short_dq(const BwdParams& p, const ShortHead& hd
         const uint32_t off = at + ks * 16 * (D * 2);
         dq[dt] = mfma32(join_tr(lds_read_tr16(off + at_lane.tr[dt][0]), lds_read_tr16(off + at_lane.tr[dt][1])), dsb[ks], dq[dt]);
       }
-  }
+  };
+  if (c_hi > 0) rows_of(0);
+  clk.steady_tiles = (c_hi + 1) / 2;
+  clock_probe_mark(p.clock, clk, kMarkSteadyBegin);
+  const int plain = CAUSAL ? c_hi - 1 : ragged >= 0 ? min(c_hi, ragged) : c_hi;  // (the last of them is on the diagonal)
+  int c = 0;
+#pragma nounroll
+  for (; c < plain; ++c) chunk(c, min(c + 1, c_hi - 1), std::false_type{});
+  if (c < c_hi) chunk(c, c, std::true_type{});
   clock_probe_mark(p.clock, clk, kMarkSteadyEnd);
   if constexpr (DB) {
     float rs = (dbs[0] + dbs[1]) + (dbs[2] + dbs[3]);
