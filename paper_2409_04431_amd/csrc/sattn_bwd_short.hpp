@@ -46,10 +46,16 @@ __device__ __forceinline__ void short_pad(uint32_t tile, int t, int N, int tid) 
     lds_write_b128(tile + ((N & 63) + i / (D / 8)) * (D * 2) + (i % (D / 8)) * 16, u32x4{0, 0, 0, 0});
 }
 
-// The 32 rows of a wave.  Under the mask the waves of a SIMD (w, w + 4) get blocks whose work adds up
-// to the same.
+// The 32 keys of a wave, or its 32 queries of `n` blocks in all (blocks from n on are past the end).  Under the mask
+// the waves of a SIMD (w, w + 4) get blocks whose work adds up to the same, or to at most that of the longest block
+// where there are fewer than eight: a key block's work falls with its place, a query block's rises (forward, d64 N192, 288
+// heads, of the streaming kernel's time: 1.12 with query blocks dealt out like key blocks, 0.98 so).
 template <int NW, bool CAUSAL>
-__device__ __forceinline__ int short_block(int wave) { return (CAUSAL && NW == 8 && wave >= 4) ? 11 - wave : wave; }
+__device__ __forceinline__ int short_key_block(int wave) { return (CAUSAL && NW == 8 && wave >= 4) ? 11 - wave : wave; }
+template <int NW, bool CAUSAL>
+__device__ __forceinline__ int short_query_block(int wave, int n) {
+  return (CAUSAL && NW == 8) ? (wave < 4 ? n - 1 - wave : n - 4 + wave) & 7 : wave;
+}
 
 // Per-lane LDS offsets: rows of a 32-row chunk, transposed pairs of a 64-row tile.
 template <int D>
@@ -98,7 +104,7 @@ __device__ __forceinline__ void short_dkdv(const BwdParams& p, const ShortHead& 
     for (int t = 0; t < n_tiles; ++t) sk.issue(lds_k + t * TILE, N, wave, lane);
   }
   stage(0, min(n_tiles, 2));
-  const int kblk = short_block<NW, CAUSAL>(wave);
+  const int kblk = short_key_block<NW, CAUSAL>(wave);
   const int key0 = 32 * kblk, key = key0 + l32, key_ld = key < N ? key : N - 1;
   bf16x8 x1[KD], x2[KD];
 #pragma unroll
@@ -298,7 +304,7 @@ __device__ __forceinline__ void short_dq(const BwdParams& p, const ShortHead& hd
       sv.issue(lds0 + t * SLOT + TILE, N, wave, lane);
     }
   }
-  const int qblk = short_block<NW, CAUSAL>(wave), q0 = 32 * qblk, q_ld = min(q0 + l32, N - 1);
+  const int qblk = short_query_block<NW, CAUSAL>(wave, n_chunks), q0 = 32 * qblk, q_ld = min(q0 + l32, N - 1);
   const __bf16 *qb = hd.of(p.q), *dob = hd.of(p.dout);
   bf16x8 x1[KD], x2[KD];
 #pragma unroll

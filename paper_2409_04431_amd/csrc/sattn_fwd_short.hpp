@@ -47,7 +47,7 @@ __global__ void __launch_bounds__(64 * NW, D == 64 ? 4 : 2) attn_fwd_short_kerne
       sv.issue(lds0 + t * SLOT + TILE, N, wave, lane);
     }
   }
-  const int qblk = short_block<NW, CAUSAL>(wave), q0 = 32 * qblk, q_ld = min(q0 + l32, N - 1);
+  const int qblk = short_query_block<NW, CAUSAL>(wave, n_chunks), q0 = 32 * qblk, q_ld = min(q0 + l32, N - 1);
   const __bf16* qb = hd.of(p.q);
   bf16x8 x1[KD];
 #pragma unroll
