@@ -57,7 +57,7 @@ int sattn_bwd_merged(int B, int H, int N, int causal);
  * backward, B*H (one a head) to 2*B*H (two a head, one for dK and dV and one for dQ), with
  * alibi / bias_grad non-zero where slopes are given / the row sums of dS are asked for.  0 where the
  * kernels run that stream the other side; errors as sattn_bwd_one_grid. */
-int sattn_fwd_short(int B, int H, int N, int d);
+int sattn_fwd_short(int B, int H, int N, int d, int causal);
 int sattn_bwd_short(int B, int H, int N, int d, int causal, int alibi, int bias_grad);
 
 /* Comparison aids (Section 4 and Appendix F.2 compare the sigmoid kernels with softmax kernels

@@ -134,7 +134,7 @@ def load_library():
     lib.sattn_set_bwd_merged.restype = i
     lib.sattn_bwd_one_grid.argtypes = [i, i, i, i, i, i]
     lib.sattn_bwd_one_grid.restype = i
-    lib.sattn_fwd_short.argtypes = [i, i, i, i]
+    lib.sattn_fwd_short.argtypes = [i, i, i, i, i]
     lib.sattn_fwd_short.restype = i
     lib.sattn_bwd_short.argtypes = [i, i, i, i, i, i, i]
     lib.sattn_bwd_short.restype = i
@@ -449,10 +449,10 @@ def sattn_fwd_v_slots(B, H, N, d, causal=False):
     return rc
 
 
-def sattn_fwd_short(B, H, N, d):
+def sattn_fwd_short(B, H, N, d, causal=False):
     """Waves per workgroup of the forward that holds a head whole, 0 where this bf16 self-attention problem
     (packed: N = max_seqlen) takes a kernel that streams K and V."""
-    rc = load_library().sattn_fwd_short(int(B), int(H), int(N), int(d))
+    rc = load_library().sattn_fwd_short(int(B), int(H), int(N), int(d), int(bool(causal)))
     _raise(min(rc, 0), "sattn_fwd_short")
     return rc
 

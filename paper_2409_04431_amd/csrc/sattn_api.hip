@@ -241,13 +241,22 @@ bool pick_bwd_merged(int B, int H, int N, int causal, bool two_per_cu, bool pack
   return (places - pairs) * 25 > places;
 }
 
-// The forward that holds a head whole (sattn_fwd_short.hpp): up to 128 keys always; up to 256 at d = 64
-// from more heads than half the units on, where the two workgroups a head of the other kernels no longer
-// each find a compute unit to themselves (us, those / this: N250 16 heads 7.8 / 8.9, 144 heads 10.9 / 9.5).
-bool pick_fwd_short(int64_t heads, int N, int d) {
+// The forward that holds a head whole (sattn_fwd_short.hpp).  Up to 128 keys always, but for a few causal
+// heads of at most 48 tokens at d = 128 (one round of workgroups; us, streaming / this: N33 4 heads 5.4 / 5.8, N48
+// 1.04 times as long, N64 0.96; of 257 to 512 heads N33 0.71).  Up to 256 keys at d = 64 from more heads than half the
+// units on, where the two workgroups a head of the other kernels no longer each find a compute unit to
+// themselves (N250 16 heads 7.8 / 8.9, 144 heads 10.9 / 9.5), but where unmasked heads of seven or eight
+// blocks are one to one and a half a unit: some units hold two heads and some one, where the streaming kernel's
+// smaller workgroups still share them out (N240 1.03 to 1.08 times as long with 257 to 383 heads, N208
+// 1.00; 384 heads 0.99; causal 0.85 to 0.93).  Packed batches of one to one and a half heads a unit go 0.77 to
+// 1.16 times as long, by how their lengths fall on the units, 0.95 on average.
+bool pick_fwd_short(int64_t heads, int N, int d, int causal) {
   if (g_fwd_waves.load(std::memory_order_relaxed) != 0 || g_fwd_vslots.load(std::memory_order_relaxed) != 0) return false;
   if (heads > (1 << 21)) return false;
-  return N <= 128 || (d == 64 && N <= 256 && 2 * heads > compute_units());
+  const int cus = compute_units();
+  if (N <= 128) return d == 64 || !causal || N > 48 || heads > cus;
+  if (d != 64 || N > 256 || 2 * heads <= cus) return false;
+  return causal || N <= 192 || heads <= cus || 2 * heads >= 3 * cus;
 }
 
 // The backward that holds a head whole (sattn_bwd_short.hpp), for every sequence short enough but where
@@ -438,7 +447,7 @@ int fwd_impl(const FwdArgs& a) {
     if (p.n_split > 0)
       return a.d == 128 ? launch_fwd_few<128>(p, a.causal, alibi, st) : launch_fwd_few<64>(p, a.causal, alibi, st);
   }
-  if (!SOFTMAX && PIN && Nk == a.N && Hkv == a.H && !alibi && pick_fwd_short((int64_t)a.B * a.H, a.N, a.d))
+  if (!SOFTMAX && PIN && Nk == a.N && Hkv == a.H && !alibi && pick_fwd_short((int64_t)a.B * a.H, a.N, a.d, a.causal))
     return a.d == 128 ? launch_fwd_short<128>(p, a.causal, st) : launch_fwd_short<64>(p, a.causal, st);
   const FwdShape shape = pick_fwd_shape(a.B, a.H, a.N, a.d, a.causal, has64);
   // The 64-row causal kernel deals a head's blocks out in pairs of equal work (longest with
@@ -1008,10 +1017,10 @@ int sattn_bwd_short(int B, int H, int N, int d, int causal, int alibi, int bias_
   if (!pick_bwd_short(heads, N, d, causal, alibi != 0, bias_grad != 0)) return 0;
   return (int)(2 * heads) - (bias_grad ? 0 : short_whole_heads(heads, N, d));
 }
-int sattn_fwd_short(int B, int H, int N, int d) {
+int sattn_fwd_short(int B, int H, int N, int d, int causal) {
   if (B <= 0 || H <= 0 || N <= 0) return SATTN_ERR_SHAPE;
   if (d != 64 && d != 128) return SATTN_ERR_UNSUPPORTED;
-  return pick_fwd_short((int64_t)B * H, N, d) ? (N > 128 ? 8 : 4) : 0;
+  return pick_fwd_short((int64_t)B * H, N, d, causal) ? (N > 128 ? 8 : 4) : 0;
 }
 int sattn_bwd_merged(int B, int H, int N, int causal) { return sattn_bwd_one_grid(B, H, N, 128, causal, 0); }
 

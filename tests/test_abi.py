@@ -148,6 +148,15 @@ def test_choice_of_the_kernels_that_hold_a_head_whole(lib):
     assert sa.sattn_fwd_short(2, 2, 128, 64) == 4 and sa.sattn_fwd_short(2, 2, 128, 128) == 4
     assert sa.sattn_fwd_short(9, 17, 256, 64) == 8 and sa.sattn_fwd_short(3, 17, 256, 64) == 0
     assert sa.sattn_fwd_short(64, 12, 257, 64) == 0 and sa.sattn_fwd_short(64, 12, 129, 128) == 0
+    # d = 64, unmasked, seven or eight blocks: not from one to one and a half heads a unit
+    for N in (193, 256):
+        assert [sa.sattn_fwd_short(1, h, N, 64) for h in (128, 129, 256, 257, 383, 384)] == [0, 8, 8, 0, 0, 8]
+        assert sa.sattn_fwd_short(1, 300, N, 64, True) == 8
+    assert sa.sattn_fwd_short(1, 300, 192, 64) == 8
+    # d = 128, causal, up to 48 tokens: not in one round
+    assert [sa.sattn_fwd_short(1, h, 48, 128, True) for h in (1, 256, 257)] == [0, 0, 4]
+    assert sa.sattn_fwd_short(1, 4, 48, 128) == 4 and sa.sattn_fwd_short(1, 4, 49, 128, True) == 4
+    assert sa.sattn_fwd_short(1, 4, 48, 64, True) == 4
     # all heads shared by two workgroups, whole, and those beyond a whole round shared
     assert sa.sattn_bwd_short(3, 17, 128, 64) == 102 and sa.sattn_bwd_short(9, 17, 256, 64) == 153
     assert sa.sattn_bwd_short(21, 17, 256, 64) == 256 + 2 * 101
@@ -156,7 +165,7 @@ def test_choice_of_the_kernels_that_hold_a_head_whole(lib):
     assert sa.sattn_bwd_short(9, 17, 129, 64, bias_grad=True) == 0 and sa.sattn_bwd_short(9, 17, 128, 64, bias_grad=True) == 306
     assert sa.sattn_bwd_short(9, 17, 128, 64, alibi=True) > 0 and sa.sattn_bwd_short(9, 17, 128, 64, True, True) == 0
     assert sa.sattn_bwd_short(9, 17, 128, 64, alibi=True, bias_grad=True) == 0
-    assert lib.sattn_fwd_short(0, 1, 16, 64) == -2 and lib.sattn_fwd_short(1, 1, 16, 96) == -3
+    assert lib.sattn_fwd_short(0, 1, 16, 64, 0) == -2 and lib.sattn_fwd_short(1, 1, 16, 96, 0) == -3
     assert lib.sattn_bwd_short(1, 0, 16, 64, 0, 0, 0) == -2 and lib.sattn_bwd_short(1, 1, 16, 96, 0, 0, 0) == -3
     try:
         sa.sattn_set_bwd_merged(2)

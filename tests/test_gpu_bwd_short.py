@@ -100,7 +100,7 @@ def test_clock_probe_stamps_are_in_order(B, d, N, causal):
     x = [torch.randn(B, HEADS, N, d, device="cuda").bfloat16() for _ in range(4)]
     grads = [torch.empty_like(x[0]) for _ in range(3)]
     calls = [(lambda: sa.sigmoid_attn_bwd(*x, *grads, -6.0, causal), sa.sattn_bwd_short(B, HEADS, N, d, causal))]
-    if sa.sattn_fwd_short(B, HEADS, N, d):
+    if sa.sattn_fwd_short(B, HEADS, N, d, causal):
         calls.append((lambda: sa.sigmoid_attn_fwd(*x[:3], grads[0], -6.0, causal), B * HEADS))
     for call, n_wg in calls:
         assert n_wg > 0
