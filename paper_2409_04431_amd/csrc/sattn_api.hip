@@ -260,16 +260,18 @@ bool pick_fwd_short(int64_t heads, int N, int d, int causal) {
 }
 
 // The backward that holds a head whole (sattn_bwd_short.hpp), for every sequence short enough but where
-// the two passes' four workgroups a head all find a place at once and nothing is masked: N250 d64 16
-// heads 12.5 us against 13.2, 64 heads 13.1 / 13.8 (causal, 128 heads: 16.4 / 14.7; N128: 9.3 / 7.2).  With
-// the row sums of dS (`rows`) every head takes two workgroups, which pays up to 128 tokens (64 heads
-// 9.3 / 7.3, 384: 18.1 / 15.3; d128 512 heads 54.7 / 50.3), not beyond (384 heads N250 43.5 / 44.3).
-// Not for ALiBi under the mask or with the row sums: the passes add its terms in orders of their own.
+// the two passes' four workgroups a head all find a place at once and nothing is masked (d64 N250 16 heads
+// 12.5 us against 13.2, 64 heads 13.1 / 13.8; causal 0.85 of the passes' time with 72 heads, 0.97 with 64, but N256,
+// where nothing is ragged and the passes run no step in its compiler-scheduled form, 1.05 to 1.07 up to 64
+// heads and 0.87 with 72; N128: 9.3 / 7.2 us).  With the row sums of dS (`rows`) every head takes two workgroups,
+// which pays up to 128 tokens (64 heads 9.3 / 7.3, 384: 18.1 / 15.3; d128 512 heads 54.7 / 50.3), not beyond (384 heads
+// N250 43.5 / 44.3).  Not for ALiBi under the mask or with the row sums: the passes add its terms in orders of their own.
 bool pick_bwd_short(int64_t heads, int N, int d, int causal, bool alibi, bool rows) {
   if (alibi && (causal || rows)) return false;
   if (g_bwd_merged.load(std::memory_order_relaxed) != 0 || N > (d == 64 && !rows ? 256 : 128)) return false;
   if (heads > (1 << 21)) return false;  // two workgroups a head of up to 512 work-items, which a launch counts in 32 bits
-  return d == 128 || N <= 128 || causal || 2 * heads > compute_units();
+  if (d == 128 || N <= 128) return true;
+  return causal ? N < 256 || 4 * heads > compute_units() : 2 * heads > compute_units();
 }
 // Its heads that take one workgroup.  What is left over after whole rounds of the chip takes two, one
 // for dK and dV and one for dQ, where these still fit one round (us, one / two workgroups for

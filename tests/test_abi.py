@@ -162,6 +162,9 @@ def test_choice_of_the_kernels_that_hold_a_head_whole(lib):
     assert sa.sattn_bwd_short(21, 17, 256, 64) == 256 + 2 * 101
     # declined: unmasked, up to half as many heads as units; row sums beyond 128 tokens; ALiBi under the mask or with them
     assert sa.sattn_bwd_short(3, 17, 200, 64) == 0 and sa.sattn_bwd_short(3, 17, 200, 64, True) == 102
+    # causal at exactly 256 tokens: only from more heads than a quarter of the units on
+    assert sa.sattn_bwd_short(1, 64, 256, 64, True) == 0 and sa.sattn_bwd_short(1, 65, 256, 64, True) == 130
+    assert sa.sattn_bwd_short(1, 4, 255, 64, True) == 8
     assert sa.sattn_bwd_short(9, 17, 129, 64, bias_grad=True) == 0 and sa.sattn_bwd_short(9, 17, 128, 64, bias_grad=True) == 306
     assert sa.sattn_bwd_short(9, 17, 128, 64, alibi=True) > 0 and sa.sattn_bwd_short(9, 17, 128, 64, True, True) == 0
     assert sa.sattn_bwd_short(9, 17, 128, 64, alibi=True, bias_grad=True) == 0
