@@ -233,48 +233,48 @@ __device__ __forceinline__ void short_dkdv(const BwdParams& p, const ShortHead& 
     __syncthreads();
     if (rnd == 0 && n_tiles > 2 && n_tiles * 64 > N) short_pad<D, NW>(lds0 + (n_tiles - 1) * SLOT + TILE, n_tiles - 1, N, tid);
     if constexpr (DQ) {
-    // dQ of these 128 queries: this wave's tile of features, all keys
-    const int dt = wave % DT;
-    const uint32_t kt0 = lds_k + tr[0][0], kt1 = lds_k + tr[0][1];
-    const uint32_t flip = (uint32_t)(4 * dt) << 4;
+      // dQ of these 128 queries: this wave's tile of features, all keys
+      const int dt = wave % DT;
+      const uint32_t kt0 = lds_k + tr[0][0], kt1 = lds_k + tr[0][1];
+      const uint32_t flip = (uint32_t)(4 * dt) << 4;
 #pragma unroll
-    for (int i = 0; i < N_SUB; ++i) {
-      const int sub = wave / DT + i * SUB_STEP, c = 4 * rnd + sub;
-      if (c >= n_chunks) continue;
-      const int n_kb = CAUSAL ? c + 1 : n_chunks;  // blocks of 32 keys
-      const uint32_t from = lds_ds + (sub >> 1) * (MAXN * 128), half = (sub & 1) << 6;
-      f32x16 dq;
+      for (int i = 0; i < N_SUB; ++i) {
+        const int sub = wave / DT + i * SUB_STEP, c = 4 * rnd + sub;
+        if (c >= n_chunks) continue;
+        const int n_kb = CAUSAL ? c + 1 : n_chunks;  // blocks of 32 keys
+        const uint32_t from = lds_ds + (sub >> 1) * (MAXN * 128), half = (sub & 1) << 6;
+        f32x16 dq;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) dq[r] = 0.f;
-      bf16x8 ka[2], wa[2];
-      auto fetch = [&](int j) {
+        for (int r = 0; r < 16; ++r) dq[r] = 0.f;
+        bf16x8 ka[2], wa[2];
+        auto fetch = [&](int j) {
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-          const uint32_t ko = (2 * j + ks) * 16 * (D * 2), so = from + (2 * j + ks) * 16 * 128;
-          ka[ks] = join_tr(lds_read_tr16((kt0 ^ flip) + ko), lds_read_tr16((kt1 ^ flip) + ko));
-          wa[ks] = join_tr(lds_read_tr16(so + (ds_rd[0] ^ half)), lds_read_tr16(so + (ds_rd[1] ^ half)));
-        }
-      };
-      fetch(0);
+          for (int ks = 0; ks < 2; ++ks) {
+            const uint32_t ko = (2 * j + ks) * 16 * (D * 2), so = from + (2 * j + ks) * 16 * 128;
+            ka[ks] = join_tr(lds_read_tr16((kt0 ^ flip) + ko), lds_read_tr16((kt1 ^ flip) + ko));
+            wa[ks] = join_tr(lds_read_tr16(so + (ds_rd[0] ^ half)), lds_read_tr16(so + (ds_rd[1] ^ half)));
+          }
+        };
+        fetch(0);
 #pragma nounroll
-      for (int j = 0; j < n_kb; ++j) {
-        const bf16x8 k0 = ka[0], k1 = ka[1], w0 = wa[0], w1 = wa[1];
-        fetch(min(j + 1, n_kb - 1));
-        dq = mfma32(k0, w0, dq);
-        dq = mfma32(k1, w1, dq);
-      }
-      const int q = 32 * c + l32;
-      if (q < N) {
-        __bf16* out = hd.of(p.dq) + (int64_t)q * p.dq.ss + 32 * dt + 4 * h;
+        for (int j = 0; j < n_kb; ++j) {
+          const bf16x8 k0 = ka[0], k1 = ka[1], w0 = wa[0], w1 = wa[1];
+          fetch(min(j + 1, n_kb - 1));
+          dq = mfma32(k0, w0, dq);
+          dq = mfma32(k1, w1, dq);
+        }
+        const int q = 32 * c + l32;
+        if (q < N) {
+          __bf16* out = hd.of(p.dq) + (int64_t)q * p.dq.ss + 32 * dt + 4 * h;
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          u32x2 w;
-          w[0] = pack_bf16(dq[4 * g] * p.inv_sqrt_d, dq[4 * g + 1] * p.inv_sqrt_d);
-          w[1] = pack_bf16(dq[4 * g + 2] * p.inv_sqrt_d, dq[4 * g + 3] * p.inv_sqrt_d);
-          *(u32x2*)(out + 8 * g) = w;
+          for (int g = 0; g < 4; ++g) {
+            u32x2 w;
+            w[0] = pack_bf16(dq[4 * g] * p.inv_sqrt_d, dq[4 * g + 1] * p.inv_sqrt_d);
+            w[1] = pack_bf16(dq[4 * g + 2] * p.inv_sqrt_d, dq[4 * g + 3] * p.inv_sqrt_d);
+            *(u32x2*)(out + 8 * g) = w;
+          }
         }
       }
-    }
     }
     __syncthreads();
   }
@@ -287,8 +287,9 @@ __device__ __forceinline__ void short_dkdv(const BwdParams& p, const ShortHead& 
   clk.tiles = n_tiles;
 }
 
-// dQ alone (DB: and the row sums of dS, in the order of the dQ pass): a wave owns 32 queries (Q, dO fragments, the dQ^T accumulators) and goes through the keys,
-// whose rows P^T and dS^T have in registers: S^T = K Q^T, dP^T = V dO^T, dQ^T += K^T dS^T.
+// dQ alone (DB: and the row sums of dS, in the order of the dQ pass): a wave owns 32 queries (Q, dO fragments, the
+// dQ^T accumulators) and goes through the keys, whose rows P^T and dS^T have in registers: S^T = K Q^T, dP^T = V dO^T,
+// dQ^T += K^T dS^T.
 template <int D, int NW, bool CAUSAL, bool ALIBI, bool DB>
 __device__ __forceinline__ void short_dq(const BwdParams& p, const ShortHead& hd, uint32_t lds0, ClockStart& clk) {
   constexpr int KD = D / 16, DT = D / 32, TILE = 64 * D * 2, SLOT = 2 * TILE;
