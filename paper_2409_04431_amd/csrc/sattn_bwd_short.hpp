@@ -16,9 +16,9 @@
 // order, filled by the second wave of a SIMD; the next chunk's rows are read under the arithmetic of
 // this one: N250 38.9 -> 36.5 us), and around it 4 to 5 us of first loads at the memory's rate, one
 // workgroup's 160 KB of LDS leaving no room for another's.  Up to 128 keys two workgroups share a compute unit.
-// Measured (us, one grid of the two passes / this): B32 H12 N250 d64 43.5 / 34.3, causal 40.9 / 32.7; B64 H16
-// N250 107 / 79.8; B32 H12 N128 18.1 / 13.6; B64 H16 N64 31.4 / 16.5; B4 H4 N64 7.5 / 5.3; B32 H16 N128 d128
-// 54.7 / 35.9; B16 H16 N70 d128 22.3 / 13.2; B64 H32 N64 d128 137 / 70.
+// Measured (us, the two passes / this): d64 384 heads N250 44.5 / 37.5 (causal 41.6 / 33.4), N128 19.4 / 14.7; 1024 heads
+// N250 109 / 84 (103 / 74), N64 32.4 / 17.4; 16 heads N64 7.7 / 5.7; d128 512 heads N128 57.3 / 37.0, 1024 N100 101 /
+// 66.7, 2048 N64 144 / 75.
 #pragma once
 #include <type_traits>
 
@@ -128,8 +128,8 @@ __device__ __forceinline__ void short_dkdv(const BwdParams& p, const ShortHead& 
   const uint32_t ds_wr = lds_ds + key * 128 + ((h ^ SwzX<64>::f(key)) << 4);
 
   // Rows past the end repeat row N-1 in Q, K and V and are zeros in dO (where the repeated row would make an
-  // infinite element of it a NaN in dV).  P and dS of queries there and dS of keys there are zero by selection,
-  // whatever the logit and dP are.
+  // infinite element of it a NaN in dV).  P and dS of queries there are zero by selection, and dS of keys there is
+  // overwritten with zeros in LDS, whatever the logit and dP are.
   SATTN_WAIT_VMCNT(0);
   stage(2, n_tiles);
   __syncthreads();

@@ -8,9 +8,10 @@
 // keeps it at 84 to 100 registers (d = 64), so that four waves share a SIMD and hide each other's waits.
 //
 // What bounds it: up to 128 keys the memory (1024 heads of 64 tokens d 64: 67 MB in 6.7 us with the
-// launch), at 250 vector issue and the first loads.  Measured (us, four waves of sattn_fwd.hpp / this):
-// d 64 B64 H16 N64 9.6 / 6.7, N128 17.7 / 13.5, N250 34.6 / 30.2, B32 H12 N128 8.2 / 7.1, N250 17.1 / 16.8 (causal
-// 16.0 / 14.5), B4 H4 N128 6.1 / 5.0; d 128 B64 H32 N64 30.3 / 24.2, B64 H16 N100 26.3 / 22.4, B4 H4 N128 7.9 / 6.5.
+// launch), at 250 vector issue and the first loads.  Measured (us, the choice among the kernels of sattn_fwd.hpp / this):
+// d 64 1024 heads N64 10.4 / 7.2, N128 19.3 / 14.3, N250 37.9 / 36.6 (causal 32.8 / 29.0), 384 heads N128 8.9 / 7.5,
+// N250 17.6 / 17.5 (causal 16.5 / 14.9), 16 heads N128 6.2 / 5.2; d 128 2048 heads N64 33.2 / 24.9, 1024 N100 26.8 / 23.3,
+// 16 heads N128 8.3 / 6.6.
 #pragma once
 #include "sattn_bwd_short.hpp"
 #include "sattn_fwd.hpp"
